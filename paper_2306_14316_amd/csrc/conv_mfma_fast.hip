@@ -16,10 +16,8 @@
 //   - every non-MFMA instruction of the K loop is placed, in program order,
 //     between two MFMAs of the wave's dependent chain, where it issues for free.
 #include "conv_mfma_tile.h"
-#include "conv_split.h"
 #include "runtime_cache.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace im2win {
@@ -817,147 +815,6 @@ static hipError_t launch_fast_i(const MfmaParams &P, uint32_t blocks, hipStream_
                     : launch_fast_t<HF, WF, CB, JX, CW, OCC, false>(P, blocks, st, plan);
 }
 
-// ---- bf16-piece instances --------------------------------------------------------------------
-// Fills the parameters for tiles of TN pixels: the strip width that needs the fewest patch positions.
-// False when the patch does not fit what the instance reserves or an offset does not fit 31 bits.
-template <int HF, int WF, int CFG>
-static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, bool implicit, size_t *lds)
-{
-    using KC = SplitK<HF, WF, CFG>;
-    using T = SplitTile<KC::WIDE>;
-    constexpr int TM = T::WGM * T::FM * 32, TN = T::WGN * T::FN * 32;
-    constexpr int smax = split_positions<HF, WF, CFG>() - 1;
-    // (Both calls ask for what either needs, so that they take the same kernel and give the same bits.)
-    if (sh.s > 65536) return false;
-    // (strided layers: where only 8 channels at a time fit, the fp32 pipeline is as fast or faster: 3x3 stride 2,
-    // 128 -> 128 at 56x56, N=32: 58 against 74 us)
-    if (CFG == 2 && HF == WF && HF <= 5 && HF != 4 && sh.s > 1) return false;
-    const int rstep = std::max(1, HF / sh.s);
-    long long best = -1, best_img = 0;
-    for (int want : {512, 64, 48, 32, 28, 24, 16, 12, 8}) {
-        const int ns = (sh.Wo - 1) / want + 1, w = (sh.Wo - 1) / ns + 1, wl = sh.Wo - (ns - 1) * w;
-        if (wl < 1 || wl < w / 2) continue;
-        const long long PW = (long long)(w - 1) * sh.s + WF;
-        if (std::min<long long>(sh.Wi, (long long)(wl - 1) * sh.s + WF - sh.p) < 4) continue;   // runs of at least four words
-        long long need = 0, imgs = 0, items = 0;
-        for (int ww : {w, wl}) {
-            const long long R = std::min<long long>((TN + ww - 2) / ww + 1, (long long)sh.N * sh.Ho);
-            const long long I = std::min<long long>((R + sh.Ho - 2) / sh.Ho + 1, sh.N);
-            const long long pw = (long long)(ww - 1) * sh.s + WF, rows = (R - 1) * sh.s + HF + (I - 1) * std::max(0, HF - sh.s);
-            const long long reads = (R - I + (rstep - 1) * I) / rstep + I;
-            need = std::max(need, rows * PW);
-            imgs = std::max(imgs, I);
-            items = std::max(items, KC::CG * std::max(rows * ((pw + 3) / 4), reads * ((pw * HF + 3) / 4)));
-        }
-        if (need > smax || items > KC::JQ * 256 || (best >= 0 && need >= best)) continue;
-        best = need; best_img = imgs;
-        Q.w = w; Q.wl = wl; Q.nstrips = ns; Q.PW = (int)PW;
-    }
-    if (best < 0) return false;
-    const unsigned long long plane = implicit ? (unsigned long long)sh.Hi * sh.Wi : (unsigned long long)sh.Ho * sh.rowlen;
-    const unsigned long long larger = std::max((unsigned long long)sh.Hi * sh.Wi, (unsigned long long)sh.Ho * sh.rowlen);
-    if ((unsigned long long)best_img * sh.Ci * larger * 4ull >= (1ull << 31)) return false;
-    if ((unsigned long long)sh.K * 4ull * TM >= (1ull << 31)) return false;
-    if (((unsigned long long)sh.Co * best_img + 64ull) * (unsigned long long)sh.Ho * sh.Wo * 4ull >= (1ull << 32)) return false;
-    const long long LF = (long long)(sh.Ho - 1) * sh.s + HF;
-    if (LF > INT32_MAX / 2) return false;
-    Q.src = P.win; Q.flt = P.flt; Q.out = P.out;
-    Q.N = sh.N; Q.Ci = sh.Ci; Q.Ho = sh.Ho; Q.Wo = sh.Wo; Q.Co = sh.Co; Q.s = sh.s; Q.K = sh.K;
-    Q.Hi = sh.Hi; Q.Wi = sh.Wi; Q.p = sh.p; Q.rowlen = sh.rowlen;
-    Q.plane = (uint32_t)plane; Q.howo = P.howo; Q.src_elems = P.win_elems; Q.out_elems = P.out_elems;
-    Q.tiles_m = (sh.Co + TM - 1) / TM;
-    const uint32_t rows = (uint32_t)(sh.N * sh.Ho);
-    Q.tiles_s = (rows * (uint32_t)Q.w + TN - 1) / TN;
-    Q.nblocks = (Q.tiles_s * (uint32_t)(Q.nstrips - 1) + (rows * (uint32_t)Q.wl + TN - 1) / TN) * (uint32_t)Q.tiles_m;
-    Q.LF = (int)LF; Q.npos = (int)best;
-    Q.d_w = make_fastdiv((uint32_t)Q.w); Q.d_wl = make_fastdiv((uint32_t)Q.wl); Q.d_ho = make_fastdiv((uint32_t)sh.Ho);
-    Q.rstep = rstep; Q.GF = (sh.Ho - 1 + rstep - 1) / rstep + 1;
-    Q.d_rs = make_fastdiv((uint32_t)rstep); Q.d_gf = make_fastdiv((uint32_t)Q.GF); Q.d_pw = make_fastdiv((uint32_t)Q.PW); Q.d_lf = make_fastdiv((uint32_t)LF);
-    Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m); Q.d_ts = make_fastdiv(Q.tiles_s);
-    *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 1) * 48;
-    return true;
-}
-
-// The same kernel name with the parameters of the bf16-piece body (conv_split.h).  HF, WF and IMP mean what they mean
-// above; CB, JX, CW and OCC are those of the fp32 instance of the same filter; PER and TAIL number the tile shape.
-template <int HF, int WF, int CB, int JX, int CW, int OCC, bool IMP, bool PER, bool TAIL, bool HALF, bool RAG>
-__global__ __launch_bounds__(512, 2) void conv_mfma_fast_kernel(SplitParams P)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    conv_split_body<HF, WF, (PER ? 1 : 0) + (TAIL ? 2 : 0), IMP>(P, smem);
-}
-
-template <int HF, int WF, int CB, int JX, int CW, int OCC, bool IMP, int CFG>
-static hipError_t launch_split_t(const SplitParams &Q, size_t lds, int dev, int ncu, hipStream_t st, LaunchPlan *plan)
-{
-    constexpr bool B0 = (CFG & 1) != 0, B1 = (CFG & 2) != 0;
-    const uint32_t grid = std::min(Q.nblocks, (uint32_t)ncu);   // one workgroup per compute unit; it takes every grid-th tile
-    if (plan) {
-        plan_record(plan, dim3(grid), 512, lds, "conv_mfma_fast_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, false, true>",
-                    HF, WF, CB, JX, CW, OCC, tf(IMP), tf(B0), tf(B1));
-        return hipSuccess;
-    }
-    void (*kern)(SplitParams) = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, B0, B1, false, true>;
-    static KernelCache kc;
-    const hipError_t e = allow_dynamic_lds(kc, reinterpret_cast<const void *>(kern), lds, dev);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, Q);
-    return hipGetLastError();
-}
-
-// hipErrorNotSupported where no tile shape fits or the fp32 pipeline is the faster one.
-template <int HF, int WF, int CB, int JX, int CW, int OCC, bool IMP>
-static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t blocks, hipStream_t st, LaunchPlan *plan)
-{
-    int dev = 0, ncu = 0;
-    hipError_t e = device_cus(&dev, &ncu);
-    if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
-    if (e != hipSuccess) return e;
-    // Which is faster: estimates in ns, fitted to 3x3, 5x5, 7x7, 4x4, 1x7, 7x1, 1x3 and 3x1 layers of 16 to 512 channels
-    // (within about 15 %).  Measured, fp32 pipeline / this body in us: 3x3 64 channels 56x56 N=8 19 / 19-27, N=16 34 / 30,
-    // N=32 61 / 47; 3x3 256 channels 14x14 N=16 37 / 52, N=128 213 / 142; 5x5 96 -> 256 24x24 N=16 79 / 52; 7x1 128 channels
-    // 28x28 142 / 72; 1x3 128 channels 28x28 51 / 45; 4x4 stride 2 64 -> 128 64x64 130 / 91.  The fp32 pipeline: its 64x64
-    // tiles at 490 GFLOP/s per compute unit and 0.8 us each; the 3x3 instances cut leftover tiles up, so their rounds
-    // count in fractions, and the others' half.
-    auto rounds = [&](uint32_t tiles) {   // (a last round that leaves units idle runs at a higher clock: half of the loss is made up)
-        const double r = (double)tiles / ncu, up = (double)((tiles + ncu - 1) / ncu);
-        return 0.5 * (up + std::max(r, up > 1.5 ? 0.0 : 0.6));
-    };
-    const double ro = HF == 3 && WF == 3 ? std::max((double)blocks / ncu, 0.2) : std::max(0.5 * ((double)blocks / ncu + (blocks + ncu - 1) / ncu), 0.6);
-    const double old = ro * ((double)sh.K * 8192.0 / 490.0 + 800.0);
-    if (old < 12000.0) return hipErrorNotSupported;   // (nothing below starts and ends in less)
-    SplitParams Q[4];
-    size_t lds[4];
-    const bool ok[4] = {split_params<HF, WF, 0>(Q[0], P, sh, IMP, &lds[0]), split_params<HF, WF, 1>(Q[1], P, sh, IMP, &lds[1]),
-                        split_params<HF, WF, 2>(Q[2], P, sh, IMP, &lds[2]), split_params<HF, WF, 3>(Q[3], P, sh, IMP, &lds[3])};
-    int pick = -1;
-    double least = 0.95 * old;
-    auto consider = [&](int i, bool wide, int CG) {
-        if (!ok[i]) return;
-        const double steps = (double)((sh.Ci + 8 * CG - 1) / (8 * CG)) * ((CG * HF * WF + 1) / 2);
-        const double t = 4000.0 + rounds(Q[i].nblocks) * (wide ? steps * 517.0 + 6000.0 : steps * 350.0 + 3500.0);
-        if (t < least) { least = t; pick = i; }
-    };
-    consider(0, SplitK<HF, WF, 0>::WIDE, SplitK<HF, WF, 0>::CG);
-    consider(1, SplitK<HF, WF, 1>::WIDE, SplitK<HF, WF, 1>::CG);
-    consider(2, SplitK<HF, WF, 2>::WIDE, SplitK<HF, WF, 2>::CG);
-    consider(3, SplitK<HF, WF, 3>::WIDE, SplitK<HF, WF, 3>::CG);
-    switch (pick) {
-        case 0: return launch_split_t<HF, WF, CB, JX, CW, OCC, IMP, 0>(Q[0], lds[0], dev, ncu, st, plan);
-        case 1: return launch_split_t<HF, WF, CB, JX, CW, OCC, IMP, 1>(Q[1], lds[1], dev, ncu, st, plan);
-        case 2: return launch_split_t<HF, WF, CB, JX, CW, OCC, IMP, 2>(Q[2], lds[2], dev, ncu, st, plan);
-        case 3: return launch_split_t<HF, WF, CB, JX, CW, OCC, IMP, 3>(Q[3], lds[3], dev, ncu, st, plan);
-        default: return hipErrorNotSupported;
-    }
-}
-
-template <int HF, int WF, int CB, int JX, int CW, int OCC>
-static hipError_t launch_split_i(const MfmaParams &P, const Shape &sh, uint32_t blocks, hipStream_t st, bool implicit, LaunchPlan *plan)
-{
-    return implicit ? launch_split<HF, WF, CB, JX, CW, OCC, true>(P, sh, blocks, st, plan)
-                    : launch_split<HF, WF, CB, JX, CW, OCC, false>(P, sh, blocks, st, plan);
-}
-
 // Returns hipErrorNotSupported when the layer does not meet the fast path's conditions.
 // implicit: P.win is the NCHW input (P.Hi, P.Wi, P.p, P.in_plane set; P.win_elems = its size).
 // filter_fetch_floats: 4, or 2 / 1 for the load-width ablation instances (8- and 4-byte filter
@@ -992,16 +849,7 @@ hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks,
         if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 1, 3, false>(P, blocks, st, plan);
     }
     if (filter_fetch_floats == 4) {
-        hipError_t e = hipErrorNotSupported;
-        const int f = sh.Hf < 16 && sh.Wf < 16 ? sh.Hf * 16 + sh.Wf : 0;
-        if (f == 0x33 && sh.Ci >= 8) e = launch_split_i<3, 3, 8, 1, 4, 3>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x55 && sh.Ci >= 4) e = launch_split_i<5, 5, 4, 1, 4, 2>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x77 && sh.Ci >= 2) e = launch_split_i<7, 7, 2, 2, 2, 2>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x17 && sh.Ci >= 8) e = launch_split_i<1, 7, 8, 1, 4, 3>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x71 && sh.Ci >= 8) e = launch_split_i<7, 1, 8, 2, 4, 2>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x13 && sh.Ci >= 16) e = launch_split_i<1, 3, 16, 1, 4, 2>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x31 && sh.Ci >= 16) e = launch_split_i<3, 1, 16, 1, 4, 2>(P, sh, blocks, st, implicit, plan);
-        if (f == 0x44 && sh.Ci >= 4) e = launch_split_i<4, 4, 4, 2, 4, 2>(P, sh, blocks, st, implicit, plan);
+        const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
         if (e != hipErrorNotSupported) return e;
     }
     // (Ci need not be a multiple of the K block: the last block is then zero-filled)

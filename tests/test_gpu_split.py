@@ -13,46 +13,45 @@ pytestmark = pytest.mark.gpu
 
 
 def _split(shape, workspace_free=False):
-    info = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)
-    return info["block"] == 512 and info["kernel"].startswith("conv_mfma_fast_kernel<")
+    return im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)["kernel"].startswith("conv_split_kernel<")
 
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p); the two flags of the tile shape (false, false / true, false: long filter
-# stages, 64 x 256 / 64 x 128 tiles; true, true / false, true: larger patches)
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p); the configuration (0 / 1: long filter stages, 64 x 256 / 64 x 128 tiles; 2 and 3:
+# larger patches)
 SHAPES = [
-    ((16, 32, 43, 50, 65, 3, 3, 1, 0), "false, false"),    # one channel past a tile, two K blocks
-    ((17, 100, 56, 38, 33, 3, 3, 1, 2), "false, false"),   # a last K block of 4 channels, padding
-    ((23, 128, 53, 21, 32, 3, 3, 1, 1), "true, false"),
-    ((22, 100, 44, 11, 65, 3, 3, 1, 3), "true, false"),    # padding as wide as the filter: windows of zeros
-    ((22, 40, 16, 58, 65, 3, 3, 1, 3), "false, true"),     # 8 channels at a time: an odd tap against zero pixels
-    ((24, 128, 21, 48, 65, 3, 3, 1, 0), "true, true"),
-    ((11, 40, 60, 36, 65, 5, 5, 1, 0), "false, true"),
-    ((21, 8, 59, 57, 65, 5, 5, 1, 4), "false, true"),      # one K block per tile
-    ((11, 32, 46, 32, 32, 5, 5, 1, 3), "true, false"),
-    ((21, 16, 47, 38, 32, 5, 5, 1, 3), "true, true"),
-    ((19, 8, 55, 49, 32, 7, 7, 1, 1), "false, false"),
-    ((20, 40, 52, 8, 65, 7, 7, 1, 3), "true, false"),
-    ((21, 40, 55, 26, 65, 7, 7, 2, 4), "false, true"),     # stride 2
-    ((24, 16, 42, 43, 65, 7, 7, 2, 2), "false, true"),
-    ((17, 100, 44, 39, 33, 1, 7, 1, 3), "false, false"),
-    ((14, 128, 41, 60, 65, 1, 7, 2, 1), "false, true"),    # a stride wider than the filter is high: rows between the windows
-    ((6, 128, 57, 51, 32, 1, 7, 1, 1), "true, false"),
-    ((19, 64, 31, 49, 33, 7, 1, 1, 4), "false, false"),
-    ((21, 128, 60, 49, 32, 7, 1, 2, 2), "false, true"),
-    ((22, 100, 50, 59, 128, 1, 3, 1, 0), "true, true"),
-    ((13, 128, 52, 28, 65, 3, 1, 1, 2), "true, true"),
-    ((23, 16, 46, 38, 33, 4, 4, 1, 4), "false, false"),
-    ((19, 64, 59, 51, 33, 4, 4, 2, 4), "true, false"),
-    ((24, 32, 48, 50, 65, 4, 4, 2, 4), "true, true"),
+    ((16, 32, 43, 50, 65, 3, 3, 1, 0), 0),    # one channel past a tile, two K blocks
+    ((17, 100, 56, 38, 33, 3, 3, 1, 2), 0),   # a last K block of 4 channels, padding
+    ((23, 128, 53, 21, 32, 3, 3, 1, 1), 1),
+    ((22, 100, 44, 11, 65, 3, 3, 1, 3), 1),    # padding as wide as the filter: windows of zeros
+    ((22, 40, 16, 58, 65, 3, 3, 1, 3), 2),     # 8 channels at a time: an odd tap against zero pixels
+    ((24, 128, 21, 48, 65, 3, 3, 1, 0), 3),
+    ((11, 40, 60, 36, 65, 5, 5, 1, 0), 2),
+    ((21, 8, 59, 57, 65, 5, 5, 1, 4), 2),      # one K block per tile
+    ((11, 32, 46, 32, 32, 5, 5, 1, 3), 1),
+    ((21, 16, 47, 38, 32, 5, 5, 1, 3), 3),
+    ((19, 8, 55, 49, 32, 7, 7, 1, 1), 0),
+    ((20, 40, 52, 8, 65, 7, 7, 1, 3), 1),
+    ((21, 40, 55, 26, 65, 7, 7, 2, 4), 2),     # stride 2
+    ((24, 16, 42, 43, 65, 7, 7, 2, 2), 2),
+    ((17, 100, 44, 39, 33, 1, 7, 1, 3), 0),
+    ((14, 128, 41, 60, 65, 1, 7, 2, 1), 2),    # a stride wider than the filter is high: rows between the windows
+    ((6, 128, 57, 51, 32, 1, 7, 1, 1), 1),
+    ((19, 64, 31, 49, 33, 7, 1, 1, 4), 0),
+    ((21, 128, 60, 49, 32, 7, 1, 2, 2), 2),
+    ((22, 100, 50, 59, 128, 1, 3, 1, 0), 3),
+    ((13, 128, 52, 28, 65, 3, 1, 1, 2), 3),
+    ((23, 16, 46, 38, 33, 4, 4, 1, 4), 0),
+    ((19, 64, 59, 51, 33, 4, 4, 2, 4), 1),
+    ((24, 32, 48, 50, 65, 4, 4, 2, 4), 3),
 ]
 
 
-@pytest.mark.parametrize("shape,tile", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v.replace(", ", "-"))
-def test_both_calls(shape, tile):
+@pytest.mark.parametrize("shape,cfg", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_both_calls(shape, cfg):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     assert _split(shape) and _split(shape, True)
     name = im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
-    assert name.endswith(", false, %s, false, true>" % tile), name
+    assert name == "conv_split_kernel<%d, %d, %d, false>" % (Hf, Wf, cfg), name
     I, F = workloads.random_layer_inputs(9100 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     print("pieces", shape, name, flush=True)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)

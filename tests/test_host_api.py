@@ -127,7 +127,7 @@ def test_binding_rejects_host_tensors(lib):
 def test_launch_info_names_the_dispatch(lib):
     """The planning calls run the library's own dispatch and launch nothing (no GPU needed: the
     grid is then planned for 256 compute units)."""
-    want = {1: "conv_mfma_kernel<9, false>", 2: "conv_mfma_fast_kernel<3, 3, 8,", 3: "conv_mfma_fast_kernel<3, 3, 8,",
+    want = {1: "conv_mfma_kernel<9, false>", 2: "conv_split_kernel<3, 3, 0, false>", 3: "conv_split_kernel<3, 3, 0, false>",
             4: "conv_mfma_shallow_kernel<7, 7, 3,", 5: "conv_mfma_shallow_kernel<11, 11, 3,"}
     for idx, prefix in want.items():
         L = workloads.layer(idx)
@@ -146,12 +146,14 @@ def test_launch_info_names_the_dispatch(lib):
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_NO_MFMA)["kernel"] == "conv_basic_kernel"
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_NO_PIPELINE)["kernel"] == "conv_mfma_kernel<9, false>"
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_VALU_MICROKERNEL)["kernel"] == "conv_mfma_kernel<9, true>"
-    for v, cw in ((im2win.VARIANT_DEFAULT, 4), (im2win.VARIANT_NARROW_LOADS, 2), (im2win.VARIANT_SCALAR_LOADS, 1)):
+    assert im2win.conv2d_im2win_fwd_launch_info(4, *L.dims[1:])["kernel"].startswith("conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3,")   # few tiles
+    for v, cw in ((im2win.VARIANT_NARROW_LOADS, 2), (im2win.VARIANT_SCALAR_LOADS, 1)):
         assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=v)["kernel"].startswith(
             "conv_mfma_fast_kernel<3, 3, 8, 1, %d, 3," % cw)
-    assert ", true, " in im2win.conv2d_im2win_fwd_launch_info(*L.dims, workspace_free=True)["kernel"]
+    assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, workspace_free=True)["kernel"] == "conv_split_kernel<3, 3, 0, true>"
+    assert im2win.conv2d_im2win_fwd_launch_info(128, 60, 56, 56, 64, 3, 3, 1, 1)["kernel"] == "conv_split_kernel<3, 3, 0, false>"
     # a channel count off the K block still takes the pipelined kernel (its ragged instance)
-    assert im2win.conv2d_im2win_fwd_launch_info(128, 60, 56, 56, 64, 3, 3, 1, 1)["kernel"] == \
+    assert im2win.conv2d_im2win_fwd_launch_info(3, 13, 12, 12, 96, 3, 3, 1, 0)["kernel"] == \
         "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, false, true>"
     assert im2win.conv2d_im2win_fwd_launch_info(8, 7, 56, 56, 64, 3, 3, 1, 1)["kernel"] == "conv_mfma_kernel<9, false>"
     # 1x1 layers: their own kernel; 1x7 / 7x1 / 1x3 / 3x1: instances of the pipelined kernel; other asymmetric filters:
@@ -160,8 +162,8 @@ def test_launch_info_names_the_dispatch(lib):
     assert im2win.conv2d_im2win_fwd_launch_info(64, 256, 28, 28, 256, 1, 1, 1, 0, workspace_free=True)["kernel"] == "conv_mfma_1x1_kernel<32, false, 2, 1>"
     assert im2win.conv2d_im2win_fwd_launch_info(64, 256, 28, 28, 256, 1, 1, 2, 0)["kernel"] == "conv_mfma_1x1_kernel<32, true, 2, 1>"   # strided
     assert im2win.conv2d_im2win_fwd_launch_info(64, 252, 28, 28, 256, 1, 1, 1, 0)["kernel"] == "conv_mfma_pipe_kernel<1, 1>"
-    assert im2win.conv2d_im2win_fwd_launch_info(64, 64, 28, 28, 64, 1, 7, 1, 0)["kernel"].startswith("conv_mfma_fast_kernel<1, 7, 8, 1, 4, 3, false,")
-    assert im2win.conv2d_im2win_fwd_launch_info(64, 64, 28, 28, 64, 7, 1, 1, 3, workspace_free=True)["kernel"].startswith("conv_mfma_fast_kernel<7, 1, 8, 2, 4, 2, true,")
+    assert im2win.conv2d_im2win_fwd_launch_info(4, 64, 28, 28, 64, 1, 7, 1, 0)["kernel"].startswith("conv_mfma_fast_kernel<1, 7, 8, 1, 4, 3, false,")
+    assert im2win.conv2d_im2win_fwd_launch_info(4, 64, 28, 28, 64, 7, 1, 1, 3, workspace_free=True)["kernel"].startswith("conv_mfma_fast_kernel<7, 1, 8, 2, 4, 2, true,")
     # 11x11 on three channels: 16-byte operand reads on the two-call path when the stride is a multiple of four
     assert im2win.conv2d_im2win_fwd_launch_info(128, 3, 227, 227, 96, 11, 11, 4, 0)["kernel"] == "conv_mfma_shallow_kernel<11, 11, 3, 3, 2, 4, false, 1, false, true>"
     assert im2win.conv2d_im2win_fwd_launch_info(128, 3, 227, 227, 96, 11, 11, 4, 0, workspace_free=True)["kernel"] == "conv_mfma_shallow_kernel<11, 11, 3, 3, 2, 4, true, 1, false, false>"
