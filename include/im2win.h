@@ -81,9 +81,9 @@ im2win_status im2win_transform(const float *input_dev, float *window_dev,
  * computed as a GEMM with M = Co, N = N*Ho*Wo, K = Ci*Hf*Wf on the fp32 matrix
  * cores (fp32 multiply, fp32 accumulate; summation order is unspecified), or, where
  * that is faster, on the bf16 matrix cores with every operand cut into three bf16
- * pieces that hold its 24 bits and fp32 accumulation (smaller error; an operand below
- * 2^-110 in magnitude is held to an absolute 2^-134).  Words of the im2win tensor that
- * repeat an input word may be read from any of their copies.
+ * pieces that hold its 24 bits, whatever its magnitude, and fp32 accumulation (smaller
+ * error).  Words of the im2win tensor that repeat an input word may be read from any of
+ * their copies.
  * Hi, Wi and pad are those given to im2win_transform, so that both calls derive
  * the same shapes.
  *   window_dev  device, as written by im2win_transform, read only

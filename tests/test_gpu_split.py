@@ -87,6 +87,31 @@ def test_error_is_below_the_fp32_matrix_cores(shape):
     assert l2 <= l2_32
 
 
+# powers of two on the input and on the filter: normal and subnormal fp32 words below the last bf16 piece, subnormal
+# results, operands and sums near the top of the range
+SCALES = [(-112, 0), (-118, 4), (-124, 10), (4, -124), (-140, 20), (-63, -63), (105, 0), (120, -120), (-120, 120), (60, 60)]
+
+
+@pytest.mark.parametrize("ei,ef", SCALES)
+def test_no_operand_loses_bits(ei, ef):
+    """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape = (16, 32, 43, 50, 65, 3, 3, 1, 0)
+    assert _split(shape) and _split(shape, True)
+    I, F = workloads.random_layer_inputs(9400, N, Ci, Hi, Wi, Co, Hf, Wf)
+    I, F = torch.ldexp(I.double(), torch.tensor(ei)).float(), torch.ldexp(F.double(), torch.tensor(ef)).float()
+    O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
+    dW, dI, dF = run_transform(I, Hf, Wf, s, p), I.cuda(), F.cuda()
+    d32 = torch.full(O_ref.shape, float("nan"), dtype=torch.float32, device="cuda")
+    got, got2 = torch.full_like(d32, float("nan")), torch.full_like(d32, float("nan"))
+    im2win.conv2d_im2win_fwd_variant(dW, dF, d32, *shape, im2win.VARIANT_NO_PIPELINE)
+    im2win.conv2d_im2win_fwd(dW, dF, got, *shape)
+    im2win.conv2d_im2win_implicit_fwd(dI, dF, got2, *shape)
+    torch.cuda.synchronize()
+    l2 = [conv_errors(o.cpu().numpy(), O_ref, B_ref)[1] for o in (got, got2, d32)]
+    print("2^%d x 2^%d: relative L2 error, pieces %.2e %.2e, fp32 %.2e" % (ei, ef, *l2))
+    assert max(l2[:2]) <= 1.1 * l2[2]   # (where the fp32 fallback computes the outputs, both are fp32 chains of K products)
+
+
 def test_infinities_nan_and_the_largest_values():
     """An infinite or NaN input, and values whose rounded first piece is infinite, reach exactly the outputs that
     plain fp32 arithmetic gives them (the one-thread-per-output kernel), in both calls."""
