@@ -63,7 +63,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     Q.rstep = rstep; Q.GF = (sh.Ho - 1 + rstep - 1) / rstep + 1;
     Q.d_rs = make_fastdiv((uint32_t)rstep); Q.d_gf = make_fastdiv((uint32_t)Q.GF); Q.d_pw = make_fastdiv((uint32_t)Q.PW); Q.d_lf = make_fastdiv((uint32_t)LF);
     Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m); Q.d_ts = make_fastdiv(Q.tiles_s);
-    *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 1) * 48;
+    *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 1) * 48 + kPassBytes;
     return true;
 }
 

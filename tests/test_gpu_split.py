@@ -112,6 +112,27 @@ def test_no_operand_loses_bits(ei, ef):
     assert max(l2[:2]) <= 1.1 * l2[2]   # (where the fp32 fallback computes the outputs, both are fp32 chains of K products)
 
 
+def _assert_like_basic(shape, I, F):
+    """Both calls against the one-thread-per-output fp32 kernel: the same infinities and NaN, the same finite values."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    dW, dF = run_transform(I, Hf, Wf, s, p), F.cuda()
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    ref = torch.empty((N, Co, Ho, Wo), device="cuda")
+    im2win.conv2d_im2win_fwd_basic(dW, dF, ref, *shape)
+    got, got2 = torch.zeros_like(ref), torch.zeros_like(ref)
+    im2win.conv2d_im2win_fwd(dW, dF, got, *shape)
+    im2win.conv2d_im2win_implicit_fwd(I.cuda(), dF, got2, *shape)
+    torch.cuda.synchronize()
+    for o in (got, got2):
+        assert torch.equal(torch.isnan(o), torch.isnan(ref))
+        assert torch.equal(torch.isinf(o), torch.isinf(ref))
+        assert torch.equal(o[torch.isinf(o)], ref[torch.isinf(ref)])
+        fin = torch.isfinite(ref)
+        a, b = o[fin].double(), ref[fin].double()
+        assert bool(((a - b).abs() <= 1e-4 * b.abs().clamp(min=1.0)).all())   # (K = 288 sums of order one; 1e-4 of the sum of magnitudes)
+    return ref
+
+
 def test_infinities_nan_and_the_largest_values():
     """An infinite or NaN input, and values whose rounded first piece is infinite, reach exactly the outputs that
     plain fp32 arithmetic gives them (the one-thread-per-output kernel), in both calls."""
@@ -126,18 +147,69 @@ def test_infinities_nan_and_the_largest_values():
     F[:, 7] *= 0.25
     F[4, 3, 1, 1] = 0.0                      # infinity times zero
     F[64, 0, 0, 0] = float("inf")
-    dW, dF = run_transform(I, Hf, Wf, s, p), F.cuda()
-    ref = torch.empty((N, Co, Hi, Wi), device="cuda")
-    im2win.conv2d_im2win_fwd_basic(dW, dF, ref, *shape)
-    got, got2 = torch.zeros_like(ref), torch.zeros_like(ref)
-    im2win.conv2d_im2win_fwd(dW, dF, got, *shape)
-    im2win.conv2d_im2win_implicit_fwd(I.cuda(), dF, got2, *shape)
-    torch.cuda.synchronize()
+    ref = _assert_like_basic(shape, I, F)
     assert torch.isnan(ref).any() and torch.isinf(ref).any()
-    for o in (got, got2):
-        assert torch.equal(torch.isnan(o), torch.isnan(ref))
-        assert torch.equal(torch.isinf(o), torch.isinf(ref))
-        assert torch.equal(o[torch.isinf(o)], ref[torch.isinf(ref)])
-        fin = torch.isfinite(ref)
-        a, b = o[fin].double(), ref[fin].double()
-        assert bool(((a - b).abs() <= 1e-4 * b.abs().clamp(min=1.0)).all())   # (K = 288 sums of order one; 1e-4 of the sum of magnitudes)
+
+
+def test_the_ends_of_the_range_meet():
+    """The lowest fp32 value (masks) against zero, tiny and ordinary weights, infinity against a subnormal weight, a NaN
+    whose payload is in the low bits only, sums that pass 2^127 on the way: as in the fp32 kernel."""
+    shape = N, Ci, Hi, Wi, Co, Hf, Wf, s, p = (22, 32, 29, 50, 65, 3, 3, 1, 1)
+    assert _split(shape)
+    I, F = workloads.random_layer_inputs(9301, N, Ci, Hi, Wi, Co, Hf, Wf)
+    low = torch.finfo(torch.float32).min
+    I[0, 3, 10, 10] = low
+    I[1, 3] = low                            # a whole masked channel
+    F[:, 3] *= 0.1                           # (sums of nine stay finite)
+    F[5, 3] = 0.0
+    F[6, 3] = 2.0 ** -125
+    F[7, 3] = 2.0 ** -140
+    I[2, 4, 5, 5] = float("inf")
+    F[8, 4] = 2.0 ** -140
+    I[4, 5, 7, 7] = torch.tensor([0x7F800001], dtype=torch.int32).view(torch.float32)[0]
+    I[6, 6, 20, 20:22] = 2.0 ** 126          # each product fits, the sum of two does not
+    F[9, 6] = 2.5
+    I[7, 9, 3, 3], F[10, 9] = 2.0 ** 60, 2.0 ** 50    # a sum past 2^96 of small operands
+    ref = _assert_like_basic(shape, I, F)
+    assert torch.isnan(ref[4]).any() and torch.isinf(ref[2, 8]).any() and torch.isinf(ref[6, 9]).any()
+    assert torch.isfinite(ref[1, 5]).all() and (ref[1, 5].abs() < 2.0 ** 48).all()   # (settled by dot_fp32)
+
+
+@pytest.mark.parametrize("data", ["NaN weight", "NaN image", "infinite pixel", "all NaN", "all 2^100"])
+def test_time_on_data_that_is_not_finite(data):
+    """Infinite and NaN outputs cost a second pass over their tiles, not a scalar sum each (which took 7 to 180 times as long)."""
+    shape = N, Ci, Hi, Wi, Co, Hf, Wf, s, p = (20, 64, 56, 56, 64, 3, 3, 1, 1)
+    assert _split(shape) and _split(shape, True)
+    I, F = workloads.random_layer_inputs(9302, N, Ci, Hi, Wi, Co, Hf, Wf)
+    dO = torch.empty((N, Co, Hi, Wi), device="cuda")
+
+    def times(I, F):
+        dW, dI, dF = run_transform(I, Hf, Wf, s, p), I.cuda(), F.cuda()
+        out = []
+        for call in (lambda: im2win.conv2d_im2win_fwd(dW, dF, dO, *shape), lambda: im2win.conv2d_im2win_implicit_fwd(dI, dF, dO, *shape)):
+            best = float("inf")
+            for _ in range(5):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(10):
+                    call()
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b))
+            out.append(best)
+        return out
+
+    plain = times(I, F)
+    if data == "NaN weight":
+        F[3, 5, 1, 1] = float("nan")
+    elif data == "NaN image":
+        I[3] = float("nan")
+    elif data == "infinite pixel":
+        I[3, 2, 20, 20] = float("inf")
+    elif data == "all NaN":
+        I[:] = float("nan")
+    else:
+        I = torch.ldexp(I.double(), torch.tensor(100)).float()
+    odd = times(I, F)
+    print("%s: %.1f -> %.1f us, %.1f -> %.1f" % (data, plain[0] * 100, odd[0] * 100, plain[1] * 100, odd[1] * 100))
+    assert odd[0] <= 4 * plain[0] and odd[1] <= 4 * plain[1]   # (measured: 2.0 to 2.5)
