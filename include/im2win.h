@@ -82,9 +82,10 @@ im2win_status im2win_transform(const float *input_dev, float *window_dev,
  * cores (fp32 multiply, fp32 accumulate; summation order is unspecified), or, where
  * that is faster, on the bf16 matrix cores with every operand cut into three bf16
  * pieces that hold its 24 bits, whatever its magnitude, and fp32 accumulation (smaller
- * error; where a sum is infinite, NaN or passes 2^96 the tiles are computed a second time,
- * up to 2.5 times the time in all).  Words of the im2win tensor that repeat an input word may be read from any of
- * their copies.
+ * error; where a sum is infinite, NaN or passes 2^96 the tiles are computed a second
+ * time, up to 2.5 times the time in all).  Of the words of the im2win tensor that repeat
+ * an input word one is read, the same on every call: as im2win_transform writes them they
+ * are equal.
  * Hi, Wi and pad are those given to im2win_transform, so that both calls derive
  * the same shapes.
  *   window_dev  device, as written by im2win_transform, read only

@@ -171,7 +171,8 @@ def _conv(fn_name, window, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pa
 
 
 def conv2d_im2win_fwd(window, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, stream=None):
-    """output <- convolution over the im2win tensor on the fp32 matrix cores."""
+    """output <- convolution over the im2win tensor, as im2win_transform wrote it, on the fp32 matrix cores or, where that is
+    faster, on the bf16 matrix cores with three pieces per operand (fp32 inputs, accumulation and results)."""
     _conv("conv2d_im2win_fwd", window, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, stream)
 
 

@@ -15,7 +15,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     using KC = SplitK<HF, WF, CFG>;
     using T = SplitTile<KC::WIDE>;
     constexpr int TM = T::WGM * T::FM * 32, TN = T::WGN * T::FN * 32;
-    constexpr int smax = split_positions<HF, WF, CFG>() - 1;
+    constexpr int smax = split_positions<HF, WF, CFG>() - 2;
     // (Both calls ask for what either needs, so that they take the same kernel and give the same bits.)
     if (sh.s > 65536) return false;
     // (strided layers: where only 8 channels at a time fit, the fp32 pipeline is as fast or faster: 3x3 stride 2,
@@ -63,7 +63,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     Q.rstep = rstep; Q.GF = (sh.Ho - 1 + rstep - 1) / rstep + 1;
     Q.d_rs = make_fastdiv((uint32_t)rstep); Q.d_gf = make_fastdiv((uint32_t)Q.GF); Q.d_pw = make_fastdiv((uint32_t)Q.PW); Q.d_lf = make_fastdiv((uint32_t)LF);
     Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m); Q.d_ts = make_fastdiv(Q.tiles_s);
-    *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 1) * 48 + kPassBytes;
+    *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 2) * 48 + kPassBytes;
     return true;
 }
 

@@ -69,6 +69,27 @@ def test_both_calls(shape, cfg):
     assert torch.equal(outs[0].view(torch.int32), outs[2].view(torch.int32))   # same pieces, same order
 
 
+@pytest.mark.parametrize("shape", [(16, 32, 43, 50, 65, 3, 3, 1, 0), (24, 128, 21, 48, 65, 3, 3, 1, 0), (11, 40, 60, 36, 65, 5, 5, 1, 0),
+                                   (24, 16, 42, 43, 65, 7, 7, 2, 2), (19, 64, 59, 51, 33, 4, 4, 2, 4), (19, 64, 31, 49, 33, 7, 1, 1, 4)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_a_tensor_whose_copies_differ(shape):
+    """im2win_transform writes an input word several times and the kernel reads one of the copies, always the same one: a tensor
+    of other origin, whose copies differ, gives one result and not another on each call."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    assert _split(shape)
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    g = torch.Generator().manual_seed(9500 + sum(shape))
+    dW, dF = torch.randn((N, Ci, Ho, (Wi + 2 * p) * Hf), generator=g).cuda(), torch.randn((Co, Ci, Hf, Wf), generator=g).cuda()
+    print("differing copies", shape, flush=True)
+    outs = torch.full((4, N, Co, Ho, Wo), float("nan"), device="cuda")
+    for o in outs:
+        im2win.conv2d_im2win_fwd(dW, dF, o, *shape)
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all()
+    for o in outs[1:]:
+        assert torch.equal(o.view(torch.int32), outs[0].view(torch.int32))
+
+
 @pytest.mark.parametrize("shape", [(16, 32, 43, 50, 65, 3, 3, 1, 0), (23, 128, 53, 21, 32, 3, 3, 1, 1), (24, 16, 42, 43, 65, 7, 7, 2, 2)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_error_is_below_the_fp32_matrix_cores(shape):
