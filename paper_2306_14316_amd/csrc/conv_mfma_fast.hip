@@ -822,6 +822,11 @@ static hipError_t launch_fast_i(const MfmaParams &P, uint32_t blocks, hipStream_
 hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks, hipStream_t st, bool implicit,
                                  int filter_fetch_floats, LaunchPlan *plan)
 {
+    // (before the limits below, which are the fp32 pipeline's and turn one call of a large layer away but not the other)
+    if (filter_fetch_floats == 4) {
+        const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
+        if (e != hipErrorNotSupported) return e;
+    }
     // Filter rows are fetched in 16-byte (7x7: 8-byte) pieces from a 16-byte (8-byte) aligned filter.
     // With K = Ci*Hf*Wf not a multiple of four the rows themselves start at odd multiples of four
     // bytes: the buffer loads take that (the ablation instances ask for aligned rows).
@@ -847,10 +852,6 @@ hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks,
     if (filter_fetch_floats == 1 && !implicit && sh.Hf == 3 && sh.Wf == 3 && sh.Ci % 8 == 0 && rows16) {   // ablation: 4-byte filter chunks
         if (P.S <= 256) return launch_fast_t<3, 3, 8, 1, 1, 3, false>(P, blocks, st, plan);
         if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 1, 3, false>(P, blocks, st, plan);
-    }
-    if (filter_fetch_floats == 4) {
-        const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
-        if (e != hipErrorNotSupported) return e;
     }
     // (Ci need not be a multiple of the K block: the last block is then zero-filled)
     if (sh.Hf == 3 && sh.Wf == 3 && sh.Ci >= 8 && al16) {

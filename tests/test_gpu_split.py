@@ -69,6 +69,28 @@ def test_both_calls(shape, cfg):
     assert torch.equal(outs[0].view(torch.int32), outs[2].view(torch.int32))   # same pieces, same order
 
 
+def test_an_image_beyond_the_fp32_pipeline():
+    """Strips of more than 4 GiB, which the fp32 pipeline turns away: both calls run the piece kernel; the first and last rows
+    in full, sampled outputs elsewhere."""
+    shape = N, Ci, Hi, Wi, Co, Hf, Wf, s, p = (1, 64, 1400, 1400, 33, 3, 3, 1, 0)
+    assert _split(shape) and _split(shape, True)
+    I, F = workloads.random_layer_inputs(9600, N, Ci, Hi, Wi, Co, Hf, Wf)
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    dO = run_conv(run_transform(I, Hf, Wf, s, p), F, N, Ci, Hi, Wi, s, p)
+    dO2 = torch.full_like(dO, float("nan"))
+    im2win.conv2d_im2win_implicit_fwd(I.cuda(), F.cuda(), dO2, *shape)
+    torch.cuda.synchronize()
+    assert torch.equal(dO.view(torch.int32), dO2.view(torch.int32)) and bool(torch.isfinite(dO).all())
+    got = dO.cpu().numpy()
+    for rows in (slice(0, 3), slice(Ho - 3, Ho)):
+        O_ref, B_ref = oracle.conv2d_direct(np.ascontiguousarray(I[:, :, rows.start:rows.stop + Hf - 1].numpy()), F.numpy(), s, p)
+        assert_conv_close(got[:, :, rows], O_ref, B_ref)
+    rng = np.random.default_rng(9600)
+    idx = np.stack([rng.integers(0, n, 20000) for n in (N, Co, Ho, Wo)], axis=1).astype(np.int32)
+    O_s, B_s = oracle.conv2d_direct_at(I.numpy(), F.numpy(), s, p, idx)
+    assert (np.abs(got[tuple(idx.T)].astype(np.float64) - O_s) <= 1e-4 * B_s).all()
+
+
 @pytest.mark.parametrize("shape", [(16, 32, 43, 50, 65, 3, 3, 1, 0), (24, 128, 21, 48, 65, 3, 3, 1, 0), (11, 40, 60, 36, 65, 5, 5, 1, 0),
                                    (24, 16, 42, 43, 65, 7, 7, 2, 2), (19, 64, 59, 51, 33, 4, 4, 2, 4), (19, 64, 31, 49, 33, 7, 1, 1, 4)],
                          ids=lambda s: "x".join(map(str, s)))

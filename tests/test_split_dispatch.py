@@ -30,6 +30,13 @@ def test_both_calls_take_the_same_instance(filt):
         a, b = (i["kernel"].rstrip(">").split(", ") for i in plans)
         assert a[3] == "false" and b[3] == "true" and a[:3] == b[:3], (shape, a, b)
         assert plans[0]["grid"] == plans[1]["grid"] and plans[0]["lds_bytes"] == plans[1]["lds_bytes"] <= 160 * 1024
+    # images whose strips pass the 4 GiB that the fp32 pipeline can address, or whose tensors do
+    for shape in ((1, 64, 1400, 1400, 64, Hf, Wf, 1, 0), (1, 32, 2048, 2048, 64, Hf, Wf, 1, 0), (1, 16, 2048, 2048, 64, Hf, Wf, 2, 0),
+                  (2, 500, 400, 400, 64, Hf, Wf, 1, 0)):
+        if shape[0] * shape[1] * (shape[2] - Hf + 1) * shape[3] * Hf >= 2 ** 31:
+            continue
+        plans = [im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] for w in (False, True)]
+        assert plans[0].startswith("conv_split") == plans[1].startswith("conv_split"), (shape, plans)
     assert split > 100
 
 
