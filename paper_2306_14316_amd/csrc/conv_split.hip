@@ -18,8 +18,10 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     constexpr int smax = split_positions<HF, WF, CFG>() - 2;
     // (Both calls ask for what either needs, so that they take the same kernel and give the same bits.)
     if (sh.s > 65536) return false;
-    // (strided layers: where only 8 channels at a time fit, the fp32 pipeline is as fast or faster: 3x3 stride 2,
-    // 128 -> 128 at 56x56, N=32: 58 against 74 us)
+    // (Strided layers of which only 8 channels at a time fit stay on the fp32 pipeline.  In us, fp32 pipeline / pieces: 3x3 stride 2
+    // 128 -> 128 at 56x56, N=32 68 / 79; 64 -> 64 at 112x112, N=128 309 / 319; 256 -> 256 at 28x28, N=64 110 / 131; 90 -> 26 at 41x41,
+    // N=86 46 / 54; 5x5 stride 2 64 -> 64 at 56x56, N=16 29 / 61; 96 -> 128 at 48x48, N=64 170 / 187.  Not everywhere: 3x3 56 -> 201 at
+    // 94x94, N=28 251 / 125, 5x5 48 -> 96 at 56x56, N=128 208 / 151, which the estimates below do not tell from the others.)
     if (CFG == 2 && HF == WF && HF <= 5 && HF != 4 && sh.s > 1) return false;
     const int rstep = std::max(1, HF / sh.s);
     long long best = -1, best_img = 0;
@@ -123,12 +125,15 @@ static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t bl
         const double t = 4000.0 + rounds(Q[i].nblocks) * (wide ? steps * 517.0 + 6000.0 : steps * 350.0 + 3500.0);
         if (t < least) { least = t; pick = i; }
     };
-    consider(0, SplitK<HF, WF, 0>::WIDE, SplitK<HF, WF, 0>::CG);
+    constexpr bool LONG = SplitK<HF, WF, 0>::CG < 4;   // (1x3 and 3x1: 0 is 3 with one item per thread, for tiles of a few pixels)
+    if (LONG) consider(0, SplitK<HF, WF, 0>::WIDE, SplitK<HF, WF, 0>::CG);
     consider(1, SplitK<HF, WF, 1>::WIDE, SplitK<HF, WF, 1>::CG);
     consider(2, SplitK<HF, WF, 2>::WIDE, SplitK<HF, WF, 2>::CG);
     consider(3, SplitK<HF, WF, 3>::WIDE, SplitK<HF, WF, 3>::CG);
     switch (pick) {
-        case 0: return launch_split_t<HF, WF, 0, IMP>(Q[0], lds[0], dev, ncu, st, plan);
+        case 0:
+            if constexpr (LONG) return launch_split_t<HF, WF, 0, IMP>(Q[0], lds[0], dev, ncu, st, plan);
+            else return hipErrorNotSupported;
         case 1: return launch_split_t<HF, WF, 1, IMP>(Q[1], lds[1], dev, ncu, st, plan);
         case 2: return launch_split_t<HF, WF, 2, IMP>(Q[2], lds[2], dev, ncu, st, plan);
         case 3: return launch_split_t<HF, WF, 3, IMP>(Q[3], lds[3], dev, ncu, st, plan);

@@ -228,6 +228,12 @@ MANY_TILE_SHAPES = [
     (24, 32, 56, 56, 128, 3, 3, 1, 1),   # two M tiles per pixel tile
     (42, 8, 64, 64, 64, 5, 5, 1, 0),     # 5x5 instance
     (40, 4, 128, 128, 64, 7, 7, 2, 0),   # 7x7 stride-2 instance
+    # (the second, third and fourth have moved to the bf16-piece kernel; these run the persistent fp32 instances)
+    (26, 8, 45, 70, 128, 5, 5, 1, 1),    # 5x5
+    (19, 8, 104, 104, 128, 5, 5, 2, 3),  # 5x5 stride 2
+    (213, 8, 16, 22, 64, 4, 4, 1, 3),    # 4x4
+    (177, 16, 27, 27, 64, 7, 1, 1, 3),   # 7x1
+    (180, 32, 7, 36, 128, 1, 3, 1, 3),   # 1x3
 ]
 
 

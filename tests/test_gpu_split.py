@@ -1,5 +1,5 @@
-"""The bf16-piece body of the pipelined kernel: every filter shape, tile shape and stage length the dispatch
-selects, at ragged channel, row and pixel counts, through both calls; its precision; infinities and NaN."""
+"""The bf16-piece kernels: every instance the dispatch selects (test_split_dispatch.py holds the list to that), at ragged
+channel, row and pixel counts, through both calls; precision; infinities and NaN."""
 import numpy as np
 import pytest
 import torch
@@ -16,33 +16,72 @@ def _split(shape, workspace_free=False):
     return im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)["kernel"].startswith("conv_split_kernel<")
 
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p); the configuration (0 / 1: long filter stages, 64 x 256 / 64 x 128 tiles; 2 and 3:
-# larger patches)
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the configuration (0 / 1: long filter stages, 64 x 256 / 64 x 128 tiles; 2 and 3: larger
+# patches): every instance at channel counts off its K block and tile, with padding, on short images (a tile spans several)
+# and at the strides it takes
 SHAPES = [
-    ((16, 32, 43, 50, 65, 3, 3, 1, 0), 0),    # one channel past a tile, two K blocks
-    ((17, 100, 56, 38, 33, 3, 3, 1, 2), 0),   # a last K block of 4 channels, padding
-    ((23, 128, 53, 21, 32, 3, 3, 1, 1), 1),
-    ((22, 100, 44, 11, 65, 3, 3, 1, 3), 1),    # padding as wide as the filter: windows of zeros
-    ((22, 40, 16, 58, 65, 3, 3, 1, 3), 2),     # 8 channels at a time: an odd tap against zero pixels
-    ((24, 128, 21, 48, 65, 3, 3, 1, 0), 3),
-    ((11, 40, 60, 36, 65, 5, 5, 1, 0), 2),
-    ((21, 8, 59, 57, 65, 5, 5, 1, 4), 2),      # one K block per tile
-    ((11, 32, 46, 32, 32, 5, 5, 1, 3), 1),
-    ((21, 16, 47, 38, 32, 5, 5, 1, 3), 3),
-    ((19, 8, 55, 49, 32, 7, 7, 1, 1), 0),
-    ((20, 40, 52, 8, 65, 7, 7, 1, 3), 1),
-    ((21, 40, 55, 26, 65, 7, 7, 2, 4), 2),     # stride 2
-    ((24, 16, 42, 43, 65, 7, 7, 2, 2), 2),
-    ((17, 100, 44, 39, 33, 1, 7, 1, 3), 0),
-    ((14, 128, 41, 60, 65, 1, 7, 2, 1), 2),    # a stride wider than the filter is high: rows between the windows
-    ((6, 128, 57, 51, 32, 1, 7, 1, 1), 1),
-    ((19, 64, 31, 49, 33, 7, 1, 1, 4), 0),
-    ((21, 128, 60, 49, 32, 7, 1, 2, 2), 2),
+    ((54, 404, 61, 6, 100, 1, 3, 1, 0), 2),
+    ((26, 283, 23, 16, 20, 1, 3, 1, 4), 1),
+    ((99, 298, 7, 31, 20, 1, 3, 1, 0), 1),
     ((22, 100, 50, 59, 128, 1, 3, 1, 0), 3),
+    ((68, 131, 8, 116, 20, 1, 3, 1, 0), 3),
+    ((17, 100, 44, 39, 33, 1, 7, 1, 3), 0),
+    ((78, 63, 6, 89, 20, 1, 7, 1, 0), 0),
+    ((6, 128, 57, 51, 32, 1, 7, 1, 1), 1),
+    ((66, 232, 9, 38, 20, 1, 7, 1, 0), 1),
+    ((14, 128, 41, 60, 65, 1, 7, 2, 1), 2),   # a stride wider than the filter is high: rows between the windows
+    ((114, 126, 7, 70, 20, 1, 7, 2, 1), 2),
+    ((49, 109, 94, 6, 20, 1, 7, 1, 4), 3),
+    ((83, 506, 7, 26, 20, 3, 1, 1, 2), 1),
+    ((113, 252, 10, 7, 20, 3, 1, 1, 3), 1),
+    ((41, 282, 9, 52, 33, 3, 1, 1, 1), 2),
+    ((52, 303, 19, 6, 20, 3, 1, 1, 4), 2),
     ((13, 128, 52, 28, 65, 3, 1, 1, 2), 3),
+    ((106, 93, 10, 65, 20, 3, 1, 1, 0), 3),
+    ((16, 32, 43, 50, 65, 3, 3, 1, 0), 0),   # one channel past a tile, two K blocks
+    ((17, 100, 56, 38, 33, 3, 3, 1, 2), 0),   # a last K block of 4 channels, padding
+    ((22, 100, 44, 11, 65, 3, 3, 1, 3), 1),   # padding as wide as the filter: windows of zeros
+    ((23, 128, 53, 21, 32, 3, 3, 1, 1), 1),
+    ((22, 40, 16, 58, 65, 3, 3, 1, 3), 2),   # 8 channels at a time: an odd tap against zero pixels
+    ((42, 40, 8, 119, 65, 3, 3, 1, 0), 2),
+    ((24, 128, 21, 48, 65, 3, 3, 1, 0), 3),
+    ((80, 44, 9, 76, 20, 3, 3, 1, 1), 3),
     ((23, 16, 46, 38, 33, 4, 4, 1, 4), 0),
+    ((38, 38, 12, 124, 20, 4, 4, 1, 0), 0),
+    ((11, 47, 32, 62, 20, 4, 4, 1, 2), 1),
     ((19, 64, 59, 51, 33, 4, 4, 2, 4), 1),
+    ((65, 60, 14, 105, 20, 4, 4, 2, 0), 1),
+    ((107, 48, 9, 44, 65, 4, 4, 2, 2), 2),
+    ((64, 63, 56, 51, 20, 4, 4, 3, 2), 2),
+    ((119, 75, 15, 68, 20, 4, 4, 3, 4), 2),
     ((24, 32, 48, 50, 65, 4, 4, 2, 4), 3),
+    ((65, 24, 14, 113, 65, 4, 4, 2, 2), 3),
+    ((1, 46, 98, 114, 130, 5, 5, 1, 4), 0),
+    ((11, 32, 46, 32, 32, 5, 5, 1, 3), 1),
+    ((54, 45, 9, 41, 33, 5, 5, 1, 2), 1),
+    ((11, 40, 60, 36, 65, 5, 5, 1, 0), 2),
+    ((21, 8, 59, 57, 65, 5, 5, 1, 4), 2),   # one K block per tile
+    ((21, 16, 47, 38, 32, 5, 5, 1, 3), 3),
+    ((65, 16, 7, 70, 20, 5, 5, 1, 3), 3),
+    ((17, 42, 42, 78, 20, 7, 1, 1, 2), 0),
+    ((19, 64, 31, 49, 33, 7, 1, 1, 4), 0),
+    ((2, 139, 102, 80, 20, 7, 1, 1, 3), 1),
+    ((26, 120, 9, 78, 20, 7, 1, 1, 3), 1),
+    ((31, 144, 5, 51, 65, 7, 1, 1, 3), 2),
+    ((21, 128, 60, 49, 32, 7, 1, 2, 2), 2),
+    ((49, 107, 86, 23, 20, 7, 1, 2, 1), 2),
+    ((10, 42, 75, 58, 20, 7, 1, 1, 4), 3),
+    ((94, 43, 8, 66, 20, 7, 1, 1, 3), 3),
+    ((19, 8, 55, 49, 32, 7, 7, 1, 1), 0),
+    ((83, 14, 11, 60, 65, 7, 7, 1, 2), 0),
+    ((20, 40, 52, 8, 65, 7, 7, 1, 3), 1),
+    ((91, 16, 5, 53, 20, 7, 7, 1, 3), 1),
+    ((21, 40, 55, 26, 65, 7, 7, 2, 4), 2),   # stride 2
+    ((24, 16, 42, 43, 65, 7, 7, 2, 2), 2),
+    ((58, 34, 87, 52, 20, 7, 7, 3, 1), 2),
+    ((81, 8, 12, 100, 20, 7, 7, 1, 0), 3),
+    ((48, 7, 39, 96, 33, 7, 7, 2, 4), 3),
+    ((67, 18, 27, 81, 20, 7, 7, 2, 4), 3),
 ]
 
 

@@ -1,10 +1,12 @@
 """Host side of the bf16-piece kernels (no GPU): the two calls of a layer always take the same instance, whatever the
-sizes, and what the plan asks for fits the chip."""
+sizes, what the plan asks for fits the chip, and the GPU tests run every instance that the plan selects."""
 import random
 
 import pytest
 
 import paper_2306_14316_amd as im2win
+from perf import cases
+from test_gpu_split import SHAPES
 
 FILTERS = [(3, 3), (5, 5), (7, 7), (1, 7), (7, 1), (1, 3), (3, 1), (4, 4)]
 
@@ -38,6 +40,27 @@ def test_both_calls_take_the_same_instance(filt):
         plans = [im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] for w in (False, True)]
         assert plans[0].startswith("conv_split") == plans[1].startswith("conv_split"), (shape, plans)
     assert split > 100
+
+
+def test_every_selected_instance_has_a_gpu_test():
+    """Plans layers at random over a wide range and over that of the performance cases."""
+    tested = {(*shape[5:7], cfg) for shape, cfg in SHAPES}
+    rng, seen = random.Random(5), set()
+    for i in range(80000):
+        if i % 4 == 0:
+            c = cases.draw(rng)
+            shape = tuple(c[k] for k in ("N", "Ci", "Hi", "Wi", "Co", "Hf", "Wf", "stride", "pad"))
+        else:
+            Hf, Wf = rng.choice(FILTERS)
+            Hi, s, p = int(2 ** rng.uniform(2, 8)), rng.choice([1, 1, 1, 2, 3]), rng.randint(0, 4)
+            Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(2, 8))
+            shape = (int(2 ** rng.uniform(0, 8)), int(2 ** rng.uniform(1, 10)), Hi, Wi, rng.choice([1, 20, 33, 65, 100, 130, 300]), Hf, Wf, s, p)
+            if Hi + 2 * p < Hf or Wi + 2 * p < Wf or shape[0] * max(shape[1], shape[4]) * (Hi + 2 * p) * Hf * (Wi + 2 * p) >= 2 ** 31:
+                continue
+        name = im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
+        if name.startswith("conv_split_kernel<"):
+            seen.add(tuple(int(v) for v in name[len("conv_split_kernel<"):].split(", ")[:3]))
+    assert len(seen) >= 28 and seen <= tested, (len(seen), sorted(seen - tested))
 
 
 def test_a_kernel_name_is_one_kernel():
