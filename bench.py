@@ -212,8 +212,8 @@ def layer_report(L, t):
     }
 
 
-def time_variants(L, steps):
-    """Convolution-only timing of each ablation variant on one layer (HIP events, average of `steps`)."""
+def time_variants(L, steps, only=None):
+    """Convolution-only timing of each ablation variant (or of those in `only`) on one layer (HIP events, average of `steps`)."""
     import torch
     import paper_2306_14316_amd as im2win
     from paper_2306_14316_amd import workloads
@@ -224,14 +224,16 @@ def time_variants(L, steps):
     dW = torch.empty(sz["window_elems"], dtype=torch.float32, device="cuda")
     dO = torch.empty(sz["output_elems"], dtype=torch.float32, device="cuda")
     im2win.im2win_transform(dI, dW, N, Ci, Hi, Wi, Hf, Wf, s, p)
-    names = {0: "default", 3: "narrow_loads (8-byte instead of 16-byte filter fetches)",
-             5: "scalar_loads (4-byte filter fetches)",
+    names = {0: "default: " + kernel_names(L)[0]["kernel"], 3: "narrow_loads (fp32 pipeline, 8-byte instead of 16-byte filter fetches)",
+             5: "scalar_loads (fp32 pipeline, 4-byte filter fetches)",
              1: "no_pipeline (one LDS stage, no prefetch; matrix cores)",
              4: "valu_microkernel (no_pipeline's tiling with a 4x4 register tile per thread on the vector ALUs)",
              2: "no_mfma (Algorithm 2: one thread per output, no LDS, no register tile)"}
     out = {}
     _ramp(lambda: im2win.conv2d_im2win_fwd(dW, dF, dO, N, Ci, Hi, Wi, Co, Hf, Wf, s, p))
     for v, name in names.items():
+        if only is not None and v not in only:
+            continue
         k = steps if v != 2 else max(2, steps // 10)
         try:
             for _ in range(10 if v != 2 else 1):
@@ -496,7 +498,9 @@ def main():
             r["transform_frac_of_measured_copy"] = r["transform_gbs_avg"] / best_stream
         out["layers"] = reps
     if a.ablation:
-        out["ablation"] = [time_variants(workloads.layer(i), max(5, min(a.steps, 30))) for i in (2, 3)]
+        # (the load widths once more at batch 8, where the default is the fp32 pipeline with 16-byte fetches)
+        out["ablation"] = [time_variants(workloads.layer(i), max(5, min(a.steps, 30))) for i in (2, 3)] + \
+                          [time_variants(workloads.with_batch(workloads.layer(i), 8), max(5, min(a.steps, 30)), (0, 3, 5)) for i in (2, 3)]
     if a.baselines:
         out["baselines"] = [time_baselines(l, max(5, min(a.steps, 20))) for l in workloads.LAYERS[1:]]
         if a.table2:   # the paper's comparison (Section 4.3) on its own twelve layers

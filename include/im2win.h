@@ -122,13 +122,16 @@ im2win_status conv2d_im2win_fwd_basic(const float *window_dev, const float *filt
  *                                    micro-kernel of Section 3.3 on the vector ALUs);
  *                                    compare with NO_PIPELINE, which differs from it in
  *                                    the arithmetic unit only;
- *   IM2WIN_VARIANT_NARROW_LOADS,     the default kernel with the filter rows fetched in
- *   IM2WIN_VARIANT_SCALAR_LOADS      8-byte / 4-byte instead of 16-byte pieces (the vector
+ *   IM2WIN_VARIANT_NARROW_LOADS,     the pipelined fp32 kernel with the filter rows fetched
+ *   IM2WIN_VARIANT_SCALAR_LOADS      in 8-byte / 4-byte instead of 16-byte pieces (the vector
  *                                    loads of Section 3.3 at half and quarter width; the
  *                                    strips are staged in 4-byte words in every variant,
- *                                    their runs being 4-byte aligned only); the pipelined
- *                                    3x3 kernel alone has such instances, other layers
- *                                    run the default kernel;
+ *                                    their runs being 4-byte aligned only).  There are such
+ *                                    instances for 3x3 filters, Ci a multiple of 8; other
+ *                                    layers run the default kernel.  Compare with DEFAULT on
+ *                                    a layer where that is the same kernel (a small batch;
+ *                                    conv2d_im2win_fwd_launch_info names it), not the bf16
+ *                                    pieces;
  *   IM2WIN_VARIANT_NO_MFMA           none of the above at once -- no LDS, no register
  *                                    tile, no matrix cores: one thread per output
  *                                    (Algorithm 2, conv2d_im2win_fwd_basic).
@@ -149,10 +152,10 @@ im2win_status conv2d_im2win_fwd_variant(const float *window_dev, const float *fi
 
 /*
  * Workspace-free variant: the same convolution computed straight from the NCHW
- * input.  Each workgroup builds the im2win strips of its tile (Section 3.1, Eq. 2)
- * in LDS instead of reading them from an im2win tensor, so no workspace and no
- * transform call are needed; the MFMA loop and the result are those of
- * conv2d_im2win_fwd.  Any layer is accepted.  Layers the pipelined kernel takes
+ * input.  Each workgroup builds the im2win strips of its tile (Section 3.1, Eq. 2),
+ * or the patch they come from, in LDS instead of reading an im2win tensor, so no
+ * workspace and no transform call are needed; the MFMA loop and the result are those
+ * of conv2d_im2win_fwd.  Any layer is accepted.  Layers the pipelined kernel takes
  * (3x3 filters with Ci a multiple of 8, 5x5 with Ci a multiple of 4, 7x7 with
  * Ci even, filter_dev 16-byte aligned) run at the speed of conv2d_im2win_fwd
  * alone; the others (three-channel stem layers among them) take the generic,

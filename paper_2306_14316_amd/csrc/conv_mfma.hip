@@ -592,14 +592,13 @@ hipError_t launch_conv_mfma(const float *win, const float *flt, float *out, cons
 
     const uint32_t tiles_n = (P.npix + NB - 1) / NB;
     const uint32_t blocks = tiles_n * (uint32_t)P.tiles_m;
+    // (the load-width variants: the default kernel where there is no such instance)
     if (variant == kVariantDefault || variant == kVariantNarrowLoads || variant == kVariantScalarLoads) {
         hipError_t fe = launch_conv_mfma_shallow(win, flt, out, sh, st, false, plan);
         if (fe != hipErrorNotSupported) return fe;
         fe = launch_conv_mfma_fast(P, sh, blocks, st, false,
                                    variant == kVariantNarrowLoads ? 2 : (variant == kVariantScalarLoads ? 1 : 4), plan);
         if (fe != hipErrorNotSupported) return fe;
-    }
-    if (variant == kVariantDefault) {
         const hipError_t oe = launch_conv_mfma_1x1(win, flt, out, sh, st, false, plan);
         if (oe != hipErrorNotSupported) return oe;
         const hipError_t pe = launch_generic_pipe(P, sh, blocks, st, plan);

@@ -822,11 +822,6 @@ static hipError_t launch_fast_i(const MfmaParams &P, uint32_t blocks, hipStream_
 hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks, hipStream_t st, bool implicit,
                                  int filter_fetch_floats, LaunchPlan *plan)
 {
-    // (before the limits below, which are the fp32 pipeline's and turn one call of a large layer away but not the other)
-    if (filter_fetch_floats == 4) {
-        const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
-        if (e != hipErrorNotSupported) return e;
-    }
     // Filter rows are fetched in 16-byte (7x7: 8-byte) pieces from a 16-byte (8-byte) aligned filter.
     // With K = Ci*Hf*Wf not a multiple of four the rows themselves start at odd multiples of four
     // bytes: the buffer loads take that (the ablation instances ask for aligned rows).
@@ -839,20 +834,24 @@ hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks,
     const unsigned long long img_bytes =
         implicit ? (unsigned long long)sh.Ci * sh.Hi * (unsigned long long)sh.Wi * 4ull
                  : (unsigned long long)sh.Ci * sh.Ho * (unsigned long long)sh.rowlen * 4ull;
-    if (img_bytes * (unsigned long long)(P.rmax + 1) >= (1ull << 32)) return hipErrorNotSupported;
-    // filter words likewise: 32-bit byte offsets from the tile's first filter row
-    if ((unsigned long long)sh.K * 4ull * MB >= (1ull << 32)) return hipErrorNotSupported;
-    // output words: 32-bit byte offsets from (image of the tile's first pixel, first channel of the wave)
-    if (((unsigned long long)sh.Co * (unsigned long long)P.rmax + 64ull) * (unsigned long long)sh.Ho * sh.Wo * 4ull >= (1ull << 32))
-        return hipErrorNotSupported;
-    if (filter_fetch_floats == 2 && !implicit && sh.Hf == 3 && sh.Wf == 3 && sh.Ci % 8 == 0 && rows16) {   // ablation: 8-byte filter chunks
-        if (P.S <= 256) return launch_fast_t<3, 3, 8, 1, 2, 3, false>(P, blocks, st, plan);
-        if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 2, 3, false>(P, blocks, st, plan);
+    const bool in_reach = img_bytes * (unsigned long long)(P.rmax + 1) < (1ull << 32) &&
+        // filter words likewise: 32-bit byte offsets from the tile's first filter row
+        (unsigned long long)sh.K * 4ull * MB < (1ull << 32) &&
+        // output words: 32-bit byte offsets from (image of the tile's first pixel, first channel of the wave)
+        ((unsigned long long)sh.Co * (unsigned long long)P.rmax + 64ull) * (unsigned long long)sh.Ho * sh.Wo * 4ull < (1ull << 32);
+    if (filter_fetch_floats != 4 && in_reach && !implicit && sh.Hf == 3 && sh.Wf == 3 && sh.Ci % 8 == 0 && rows16) {
+        if (filter_fetch_floats == 2) {   // ablation: 8-byte filter chunks
+            if (P.S <= 256) return launch_fast_t<3, 3, 8, 1, 2, 3, false>(P, blocks, st, plan);
+            if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 2, 3, false>(P, blocks, st, plan);
+        } else {                          // ablation: 4-byte filter chunks
+            if (P.S <= 256) return launch_fast_t<3, 3, 8, 1, 1, 3, false>(P, blocks, st, plan);
+            if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 1, 3, false>(P, blocks, st, plan);
+        }
     }
-    if (filter_fetch_floats == 1 && !implicit && sh.Hf == 3 && sh.Wf == 3 && sh.Ci % 8 == 0 && rows16) {   // ablation: 4-byte filter chunks
-        if (P.S <= 256) return launch_fast_t<3, 3, 8, 1, 1, 3, false>(P, blocks, st, plan);
-        if (P.S <= 512) return launch_fast_t<3, 3, 8, 2, 1, 3, false>(P, blocks, st, plan);
-    }
+    // (before the fp32 pipeline's limits, which turn one call of a large layer away but not the other)
+    const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
+    if (e != hipErrorNotSupported) return e;
+    if (!in_reach) return hipErrorNotSupported;
     // (Ci need not be a multiple of the K block: the last block is then zero-filled)
     if (sh.Hf == 3 && sh.Wf == 3 && sh.Ci >= 8 && al16) {
         if (P.S <= 256) return launch_fast_i<3, 3, 8, 1, 4, 3>(P, blocks, st, implicit, plan);

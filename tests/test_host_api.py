@@ -146,6 +146,12 @@ def test_launch_info_names_the_dispatch(lib):
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_NO_MFMA)["kernel"] == "conv_basic_kernel"
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_NO_PIPELINE)["kernel"] == "conv_mfma_kernel<9, false>"
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=im2win.VARIANT_VALU_MICROKERNEL)["kernel"] == "conv_mfma_kernel<9, true>"
+    # other layers: the default kernel, whichever that is
+    for shape in ((128, 96, 24, 24, 256, 5, 5, 1, 0), (64, 128, 28, 28, 128, 1, 3, 1, 1), (64, 256, 28, 28, 256, 1, 1, 1, 0),
+                  (64, 64, 28, 28, 64, 1, 5, 1, 0), (128, 100, 28, 28, 64, 3, 3, 1, 1), (128, 3, 224, 224, 64, 3, 3, 1, 0)):
+        plans = [im2win.conv2d_im2win_fwd_launch_info(*shape, variant=v) for v in
+                 (im2win.VARIANT_DEFAULT, im2win.VARIANT_NARROW_LOADS, im2win.VARIANT_SCALAR_LOADS)]
+        assert plans[0] == plans[1] == plans[2], (shape, plans)
     assert im2win.conv2d_im2win_fwd_launch_info(4, *L.dims[1:])["kernel"].startswith("conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3,")   # few tiles
     for v, cw in ((im2win.VARIANT_NARROW_LOADS, 2), (im2win.VARIANT_SCALAR_LOADS, 1)):
         assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, variant=v)["kernel"].startswith(
