@@ -183,7 +183,7 @@ def kernel_names(L):
 def conv_peak_tflops(launch):
     """Matrix peak of the instruction a convolution kernel runs on, in convolution flops: the fp32 instruction's, or a
     sixth of the bf16 one's for the kernels that sum six bf16 products per fp32 product."""
-    return PEAK_BF16_MATRIX_TFLOPS / 6 if launch["kernel"].startswith("conv_split_kernel") else PEAK_FP32_MATRIX_TFLOPS
+    return PEAK_BF16_MATRIX_TFLOPS / 6 if launch["kernel"].startswith("conv_split_") else PEAK_FP32_MATRIX_TFLOPS
 
 
 def layer_report(L, t):

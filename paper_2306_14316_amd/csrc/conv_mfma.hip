@@ -572,7 +572,9 @@ hipError_t launch_conv_implicit(const float *in, const float *flt, float *out, c
     P.implicit = 1;
     P.win_elems = (size_t)sh.N * sh.Ci * sh.Hi * (size_t)sh.Wi;   // the tensor P.win points at is the input
     const uint32_t blocks = ((P.npix + NB - 1) / NB) * (uint32_t)P.tiles_m;
-    hipError_t fe = launch_conv_mfma_shallow(in, flt, out, sh, st, true, plan);
+    hipError_t fe = launch_conv_split_stem(in, flt, out, sh, st, true, plan);
+    if (fe != hipErrorNotSupported) return fe;
+    fe = launch_conv_mfma_shallow(in, flt, out, sh, st, true, plan);
     if (fe != hipErrorNotSupported) return fe;
     fe = launch_conv_mfma_fast(P, sh, blocks, st, true, 4, plan);
     if (fe != hipErrorNotSupported) return fe;
@@ -594,7 +596,9 @@ hipError_t launch_conv_mfma(const float *win, const float *flt, float *out, cons
     const uint32_t blocks = tiles_n * (uint32_t)P.tiles_m;
     // (the load-width variants: the default kernel where there is no such instance)
     if (variant == kVariantDefault || variant == kVariantNarrowLoads || variant == kVariantScalarLoads) {
-        hipError_t fe = launch_conv_mfma_shallow(win, flt, out, sh, st, false, plan);
+        hipError_t fe = launch_conv_split_stem(win, flt, out, sh, st, false, plan);
+        if (fe != hipErrorNotSupported) return fe;
+        fe = launch_conv_mfma_shallow(win, flt, out, sh, st, false, plan);
         if (fe != hipErrorNotSupported) return fe;
         fe = launch_conv_mfma_fast(P, sh, blocks, st, false,
                                    variant == kVariantNarrowLoads ? 2 : (variant == kVariantScalarLoads ? 1 : 4), plan);

@@ -1,0 +1,103 @@
+"""The bf16-piece kernel of three-channel layers: every instance the dispatch selects (test_split_dispatch.py holds the list to that) at
+ragged sizes through both calls, its error against the fp32 matrix cores, the range of its operands, infinities and NaN."""
+import pytest
+import torch
+
+import oracle
+import paper_2306_14316_amd as im2win
+from paper_2306_14316_amd import workloads
+from parity_util import assert_conv_close, conv_errors, run_transform
+from test_gpu_split import _assert_like_basic
+
+pytestmark = pytest.mark.gpu
+
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the instance: blocks of 32 channels, parts of K, blocks of 32 pixels per workgroup
+SHAPES = [
+    ((9, 3, 85, 91, 17, 7, 7, 2, 3), (1, 2, 4)),      # odd widths, a last tile of a few pixels
+    ((21, 3, 32, 32, 32, 7, 7, 2, 0), (1, 2, 4)),     # 13 pixels a row: eleven rows to a tile
+    ((9, 3, 91, 85, 33, 7, 7, 2, 3), (2, 2, 2)),      # one channel past a block
+    ((1, 3, 33, 36, 130, 7, 7, 2, 1), (2, 2, 2)),     # three groups of channels, the last block of two
+    ((41, 3, 139, 144, 64, 7, 7, 2, 3), (2, 1, 4)),   # several tiles per workgroup
+    ((60, 3, 118, 113, 50, 7, 7, 2, 8), (2, 1, 4)),   # padding wider than the filter: windows of zeros
+    ((33, 3, 31, 64, 96, 7, 7, 2, 3), (3, 2, 2)),
+    ((1, 3, 7, 47, 70, 7, 7, 2, 0), (3, 2, 2)),       # one row, one tile
+    ((16, 3, 227, 225, 20, 11, 11, 4, 0), (1, 4, 2)),
+    ((300, 3, 11, 530, 31, 11, 11, 4, 0), (1, 4, 2)),  # one row per image: a tile may span two images
+    ((1, 3, 60, 230, 5, 11, 11, 4, 5), (2, 4, 1)),
+    ((55, 3, 39, 40, 64, 11, 11, 4, 5), (2, 4, 1)),   # eight pixels a row
+    ((9, 3, 130, 127, 96, 11, 11, 4, 2), (3, 4, 1)),
+    ((7, 3, 63, 67, 131, 11, 11, 4, 0), (3, 4, 1)),   # two groups of channels
+]
+
+
+def _plan(shape, workspace_free=False):
+    return im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)["kernel"]
+
+
+def _run(shape, I, F):
+    """Output of both calls (with guards around each), and of the fp32 kernel."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    n = N * Co * Ho * Wo
+    dW, dI, dF = run_transform(I, Hf, Wf, s, p), I.cuda(), F.cuda()
+    buf = torch.full((4, n + 64), float("nan"), device="cuda")
+    outs = [b[32:32 + n] for b in buf]
+    print("stem pieces", shape, _plan(shape), flush=True)
+    im2win.conv2d_im2win_fwd(dW, dF, outs[0], *shape)
+    im2win.conv2d_im2win_fwd(dW, dF, outs[1], *shape)
+    im2win.conv2d_im2win_implicit_fwd(dI, dF, outs[2], *shape)
+    im2win.conv2d_im2win_fwd_variant(dW, dF, outs[3], *shape, im2win.VARIANT_NO_PIPELINE)
+    torch.cuda.synchronize()
+    assert torch.isnan(buf[:, :32]).all() and torch.isnan(buf[:, 32 + n:]).all()   # nothing written outside
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))       # no races on LDS
+    assert torch.equal(outs[0].view(torch.int32), outs[2].view(torch.int32))       # same pieces, same order
+    return outs[0].cpu().numpy().reshape(N, Co, Ho, Wo), outs[3].cpu().numpy().reshape(N, Co, Ho, Wo)
+
+
+@pytest.mark.parametrize("shape,instance", SHAPES, ids=lambda v: "x".join(map(str, v)))
+def test_both_calls(shape, instance):
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    for w in (False, True):
+        assert _plan(shape, w) == "conv_split_stem_kernel<%d, %d, %d, %d, %s>" % (Hf, *instance, "true" if w else "false")
+    I, F = workloads.random_layer_inputs(9700 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
+    O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
+    got, fp32 = _run(shape, I, F)
+    assert_conv_close(got, O_ref, B_ref)
+    l2, l2_32 = conv_errors(got, O_ref, B_ref)[1], conv_errors(fp32, O_ref, B_ref)[1]
+    print("relative L2 error: pieces %.2e, fp32 %.2e" % (l2, l2_32))
+    assert l2 <= l2_32
+
+
+@pytest.mark.parametrize("ei,ef", [(-118, 4), (4, -124), (-140, 20), (105, 0), (-120, 120), (60, 60)])
+@pytest.mark.parametrize("shape", [SHAPES[4][0], SHAPES[6][0], SHAPES[12][0]], ids=lambda v: "x".join(map(str, v)))
+def test_no_operand_loses_bits(shape, ei, ef):
+    """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    I, F = workloads.random_layer_inputs(9800, N, Ci, Hi, Wi, Co, Hf, Wf)
+    I, F = torch.ldexp(I.double(), torch.tensor(ei)).float(), torch.ldexp(F.double(), torch.tensor(ef)).float()
+    O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
+    got, fp32 = _run(shape, I, F)
+    assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0][0], SHAPES[4][0], SHAPES[8][0], SHAPES[12][0]], ids=lambda v: "x".join(map(str, v)))
+def test_infinities_nan_and_the_ends_of_the_range(shape):
+    """As in plain fp32 (the one-thread-per-output kernel), in both calls: also beside windows (the padded parts of a chunk hold zeros)."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    I, F = workloads.random_layer_inputs(9900, N, Ci, Hi, Wi, Co, Hf, Wf)
+    I.abs_()                                 # (weights of 2^50 on both signs would cancel: 1e-4 of the result is not 1e-4 of the magnitudes)
+    low = torch.finfo(torch.float32).min
+    I[0, 2, 10, 10] = float("inf")
+    I[1, 1, 0, Wi - 1] = float("-inf")
+    I[2, 0, Hi - 1, 0] = float("nan")
+    I[3, 1, 20, 20] = 3.4028e38              # rounds to infinity in bf16
+    I[4, 2, 5, 5], I[4, 0, 6, 6] = float("inf"), float("-inf")
+    I[5, 2, 31, 17] = low                    # a mask
+    I[6, 1, 33, 40] = 2.0 ** 60
+    I[7, 0, 12, 13] = torch.tensor([0x7F800001], dtype=torch.int32).view(torch.float32)[0]
+    F[:, 2] *= 0.25
+    F[2, 2] = 0.0                            # infinity and the mask times zero
+    F[3, 2] = 2.0 ** -140
+    F[4, 1] = 2.0 ** 50                      # a sum past 2^96
+    ref = _assert_like_basic(shape, I, F)
+    assert torch.isnan(ref).any() and torch.isinf(ref).any()

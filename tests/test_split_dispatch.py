@@ -7,6 +7,7 @@ import pytest
 import paper_2306_14316_amd as im2win
 from perf import cases
 from test_gpu_split import SHAPES
+from test_gpu_split_stem import SHAPES as STEM_SHAPES
 
 FILTERS = [(3, 3), (5, 5), (7, 7), (1, 7), (7, 1), (1, 3), (3, 1), (4, 4)]
 
@@ -73,3 +74,27 @@ def test_a_kernel_name_is_one_kernel():
         for w in (False, True):
             i = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)
             assert blocks.setdefault(i["kernel"], i["block"]) == i["block"], (shape, i)
+
+
+def test_three_channel_layers():
+    """The stem kernel: both calls take the same instance, it fits the chip, the GPU tests run every instance selected, and layers it
+    turns away run what they ran."""
+    tested = {(shape[5], *instance) for shape, instance in STEM_SHAPES}
+    rng, seen = random.Random(11), set()
+    for i in range(20000):
+        f, s = rng.choice([(7, 2), (7, 2), (11, 4), (11, 4), (7, 1), (7, 3), (11, 2), (11, 8)])
+        Hi, p = int(2 ** rng.uniform(2, 10)), rng.randint(0, 6)
+        Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(2, 10))
+        shape = (int(2 ** rng.uniform(0, 8)), 3, Hi, Wi, rng.choice([1, 24, 32, 33, 64, 65, 96, 97, 200]), f, f, s, p)
+        if Hi + 2 * p < f or Wi + 2 * p < f or shape[0] * 96 * (Hi + 2 * p) * f * (Wi + 2 * p) >= 2 ** 31:
+            continue
+        plans = [im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w) for w in (False, True)]
+        a, b = (q["kernel"].rstrip(">").split(", ") for q in plans)
+        assert a[0].startswith("conv_split_stem") == b[0].startswith("conv_split_stem"), (shape, a, b)
+        if not a[0].startswith("conv_split_stem"):
+            assert (f, s) not in ((7, 2), (11, 4)) or Wi + 2 * p < 34 + f or shape[4] <= 64, (shape, a)
+            continue
+        assert a[:4] == b[:4] and a[4] == "false" and b[4] == "true" and plans[0]["grid"] == plans[1]["grid"], (shape, a, b)
+        assert plans[0]["lds_bytes"] <= 160 * 1024 and f * s in (14, 44, 88)
+        seen.add((int(a[0].split("<")[1]), *(int(v) for v in a[1:4])))
+    assert seen == tested, (seen ^ tested)
