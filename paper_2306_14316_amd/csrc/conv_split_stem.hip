@@ -1,5 +1,5 @@
 // bf16-piece convolution (see conv_split.h for the pieces and their precision) of layers with three input channels:
-// 7x7 at stride 2 and 11x11 at strides that are multiples of four.  K is 147 or 363, the pixels are many, and what
+// 7x7 at stride 2, 11x11 at strides that are multiples of four, 3x3.  K is 27 to 363, the pixels are many, and what
 // the piece kernel of the deeper layers spends per tile on its filter stages, its start and its stores would cost more
 // than the MFMAs of such a tile.
 //
@@ -27,6 +27,7 @@
 //     values of K instead of 9.2; windows start 28 bytes apart in the tensor's own order, which no 16-byte read can
 //     take).  Even and odd columns lie apart: neighbouring windows, two columns apart, are then neighbouring chunks,
 //     where 32 bytes between them would use half of the banks;
+//   3x3: a chunk is two columns, each of three words and a zero; windows start eight bytes apart and the fourth column is masked (3 steps);
 //   11x11: the tensor's own order; windows start 88 bytes apart and their 121 words are 15 chunks and one word, whose
 //     chunk is masked (24 steps instead of 22.7).
 #include "conv_split.h"
@@ -42,14 +43,17 @@ struct StemParams : SplitParams {
     FastDiv d_wo, d_howo, d_chf;
 };
 
-// HF x HF windows at stride S (of the LDS image); R blocks of 32 rows, Q parts of K, PX blocks of 32 pixels: one wave each.
-template <int HF_, int R_, int Q_, int PX_>
+// HF x HF windows; R blocks of 32 rows, Q parts of K, PX runs of 32*B pixels: one wave each.
+// B = 4: a lane's four pixels are neighbours and their outputs leave in one store.
+template <int HF_, int R_, int Q_, int PX_, int B_>
 struct Stem {
-    static constexpr int HF = HF_, R = R_, Q = Q_, PX = PX_;
-    static constexpr bool COLS = HF == 7;                    // chunks are columns
-    static constexpr int KHW = HF * HF, NW = R * Q * PX, NT = 64 * NW, TN = 32 * PX;
-    static constexpr int STEPS = COLS ? 11 : 24, SPQ = (STEPS + Q - 1) / Q;
-    static constexpr int CAP = COLS ? (PX == 4 ? 336 : 176) : (PX == 2 ? 392 : 256);   // chunks per channel and piece
+    static constexpr int HF = HF_, R = R_, Q = Q_, PX = PX_, B = B_;
+    static constexpr bool WIDE = B == 4;
+    static constexpr bool COLS = HF == 7, PAIRS = HF == 3;   // chunks are columns, pairs of columns
+    static constexpr int KHW = HF * HF, NW = R * Q * PX, NT = 64 * NW, TN = 32 * PX * B;
+    static constexpr int STEPS = COLS ? 11 : (PAIRS ? 3 : 24), SPQ = (STEPS + Q - 1) / Q;
+    // chunks per channel and piece
+    static constexpr int CAP = COLS ? (PX == 4 ? 336 : 176) : (PAIRS ? (B == 4 ? 284 : 140) : (PX == 2 ? 392 : 256));
     static constexpr uint32_t PCB = CAP * 16, CHB = 3 * PCB, STAGE = 3 * CHB;
     static constexpr uint32_t ODD = PCB / 2;                 // COLS: odd columns
     static constexpr int OWN = 16 / Q;                       // accumulators a wave stores
@@ -57,12 +61,13 @@ struct Stem {
     static constexpr uint32_t PASS = 2 * STAGE + 2 * RED;
     static constexpr size_t LDS = PASS + NW * 8;
     static constexpr int JX = (3 * CAP + NT - 1) / NT;       // chunks a thread stages per tile, at most
-    static_assert(LDS <= 160 * 1024, "");
-    // chunk (channel, index) that lane half h of step i multiplies; index: the column, or the chunk of the window; -1: none
-    static constexpr int chan(int i, int h) { return COLS ? (i < 7 ? h : 2) : (i < 18 ? i / 6 : (i - 18) / 2); }
+    static_assert(LDS <= 160 * 1024 && (Q == 1 || B == 1) && (B == 1 || B == 4), "");
+    // chunk (channel, index) that lane half h of step i multiplies; index: the column, the pair of columns or the chunk of the window; -1: none
+    static constexpr int chan(int i, int h) { return COLS ? (i < 7 ? h : 2) : (PAIRS ? i : (i < 18 ? i / 6 : (i - 18) / 2)); }
     static constexpr int index(int i, int h)
     {
         if (COLS) return i < 7 ? i : (2 * (i - 7) + h < 7 ? 2 * (i - 7) + h : -1);
+        if (PAIRS) return h;
         return i < 18 ? 2 * (i % 6) + h : 12 + 2 * (i % 2) + h;   // (11x11: the fourth quarter takes what the first three leave)
     }
     // filter word (u*HF + v) that value e of a chunk stands for; -1: none
@@ -70,6 +75,7 @@ struct Stem {
     {
         if (idx < 0) return -1;
         if (COLS) return e < HF ? e * HF + idx : -1;
+        if (PAIRS) return e % 4 < HF && 2 * idx + e / 4 < HF ? (e % 4) * HF + 2 * idx + e / 4 : -1;
         const int t = 8 * idx + e;
         return t < KHW ? (t % HF) * HF + t / HF : -1;
     }
@@ -123,7 +129,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         const int n1 = (int)(o.Pend - o.q1 * (uint32_t)P.Wo);
         auto chunks = [&](int pixels) __attribute__((always_inline)) {
             const int cols = (pixels - 1) * P.s + HF;
-            return T::COLS ? (cols + 1) & ~1 : (cols * HF + 7) >> 3;
+            return T::COLS ? (cols + 1) & ~1 : (T::PAIRS ? (cols + 1) >> 1 : (cols * HF + 7) >> 3);
         };
         o.ch0 = chunks((o.q0 == o.q1 ? n1 + 1 : P.Wo) - o.n0);
         o.total = o.q0 == o.q1 ? o.ch0 : o.ch0 + (int)(o.q1 - o.q0 - 1u) * P.chf + chunks(n1 + 1);
@@ -165,6 +171,13 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
 #pragma unroll
                     for (int u = 0; u < HF; ++u)
                         words[j][u] = load1(ok && hh + u >= 0 && hh + u < P.Hi ? (pl + (uint32_t)((hh + u) * P.Wi + ww)) * 4u : kNoWord);
+                } else if constexpr (T::PAIRS) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int ww = col0 + 2 * c + e / 4 - P.p, u = e % 4;
+                        words[j][e] = u == HF ? 0.0f
+                            : load1(live && ww >= 0 && ww < P.Wi && hh + u >= 0 && hh + u < P.Hi ? (pl + (uint32_t)((hh + u) * P.Wi + ww)) * 4u : kNoWord);
+                    }
                 } else {
                     int k = (8 * c) / HF, u = 8 * c - k * HF;
                     k += col0 - P.p;
@@ -178,7 +191,8 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
                     }
                 }
             } else {
-                const uint32_t off = pl + (uint32_t)(m * P.rowlen + col0 * HF) + (uint32_t)c * (T::COLS ? HF : 8);
+                constexpr uint32_t W = T::COLS ? HF : (T::PAIRS ? 6 : 8);   // words of a chunk
+                const uint32_t off = pl + (uint32_t)(m * P.rowlen + col0 * HF) + (uint32_t)c * W;
                 if constexpr (T::COLS) {
                     // (a row's last column of an odd number is read past the row: kept from the tensor's end)
                     const uint32_t vo = live && (off + HF) * 4u <= bytes ? off * 4u : kNoWord;
@@ -187,16 +201,28 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
 #pragma unroll
                     for (int u = 0; u < HF; ++u) { const uint32_t w = u < 4 ? a[u & 3] : b[(u & 3) % 3]; words[j][u] = __builtin_bit_cast(float, w); }
                 } else {
-                    const bool over = live && (off + 8u) * 4u > bytes;   // a row's last chunk, at the tensor's end
+                    const bool over = live && (off + W) * 4u > bytes;   // a row's last chunk, at the tensor's end
+                    float w[8];
                     if (__builtin_amdgcn_ballot_w64(over)) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) words[j][e] = load1(live && (off + (uint32_t)e + 1u) * 4u <= bytes ? (off + (uint32_t)e) * 4u : kNoWord);
+                        for (uint32_t e = 0; e < W; ++e) w[e] = load1(live && (off + e + 1u) * 4u <= bytes ? (off + e) * 4u : kNoWord);
                     } else {
                         const uint32_t vo = live ? off * 4u : kNoWord;
-                        const u32v4 a = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, 0, 0), b = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, 16, 0);
+                        const u32v4 a = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, 0, 0);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) { const uint32_t w = e < 4 ? a[e & 3] : b[e & 3]; words[j][e] = __builtin_bit_cast(float, w); }
+                        for (int e = 0; e < 4; ++e) { const uint32_t x = a[e]; w[e] = __builtin_bit_cast(float, x); }
+                        if constexpr (T::PAIRS) {
+                            const u32v2 b = __builtin_amdgcn_raw_buffer_load_b64(rw, vo, 16, 0);
+#pragma unroll
+                            for (int e = 0; e < 2; ++e) { const uint32_t x = b[e]; w[4 + e] = __builtin_bit_cast(float, x); }
+                        } else {
+                            const u32v4 b = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, 16, 0);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) { const uint32_t x = b[e]; w[4 + e] = __builtin_bit_cast(float, x); }
+                        }
                     }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) words[j][e] = !T::PAIRS ? w[e] : (e % 4 == HF ? 0.0f : w[e / 4 * HF + e % 4]);
                 }
             }
             if constexpr (T::COLS) words[j][7] = 0.0f;
@@ -241,15 +267,19 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         }, std::make_integer_sequence<int, SPQ>{});
     };
 
-    // ---- multiplication: the wave's 32x32 block over its part of K
-    auto multiply = [&](auto qc, uint32_t t, uint32_t at) __attribute__((always_inline)) {
+    auto pixel = [&](int blk) __attribute__((always_inline)) {   // the lane's pixel in a block, from the tile's first
+        return (uint32_t)(px * 32 * T::B + l32 * T::B + blk);
+    };
+
+    // ---- multiplication: a 32x32 block of the wave's over its part of K
+    auto multiply = [&](auto qc, uint32_t t, int blk, uint32_t at) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value, n = T::STEPS - q * SPQ < SPQ ? T::STEPS - q * SPQ : SPQ;
         const Tile o = tile_of(t);
-        const uint32_t pix = min(o.P0 + (uint32_t)(px * 32 + l32), o.Pend);
+        const uint32_t pix = min(o.P0 + pixel(blk), o.Pend);
         const uint32_t row = fdiv(pix, P.d_wo);
         const int i = (int)(row - o.q0), nn = (int)(pix - row * (uint32_t)P.Wo);
         const uint32_t lb = i == 0 ? 0u : (uint32_t)(o.ch0 + (i - 1) * P.chf) * (T::COLS ? 8u : 16u);   // (columns: two to a step of 16 bytes)
-        const uint32_t b = at + lb + (uint32_t)(nn - (i == 0 ? o.n0 : 0)) * (T::COLS ? 16u : (uint32_t)P.s * (HF * 2u));
+        const uint32_t b = at + lb + (uint32_t)(nn - (i == 0 ? o.n0 : 0)) * (T::COLS ? 16u : (uint32_t)P.s * (T::PAIRS ? 8u : HF * 2u));
         uint32_t base[3];   // COLS: of the pair steps, of the third channel, of its last step; otherwise one
         if constexpr (T::COLS) {
             base[0] = b + (uint32_t)h * CHB;
@@ -274,11 +304,14 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         };
         auto mask = [&](auto ic, bf16x8 &x) __attribute__((always_inline)) {
             constexpr int s = q * SPQ + decltype(ic)::value;
-            if constexpr (!T::COLS && T::tap(T::index(s, 1), 7) < 0) {   // the chunk with one word of the window
+            if constexpr (!T::COLS && T::tap(T::index(s, 1), 7) < 0) {   // the chunk that the window ends in
                 u32v4 w = __builtin_bit_cast(u32v4, x);
-                w[0] &= h ? 0xffffu : 0xffffffffu;
+                if constexpr (!T::PAIRS) {
+                    w[0] &= h ? 0xffffu : 0xffffffffu;
+                    w[1] = h ? 0u : w[1];
+                }
 #pragma unroll
-                for (int d = 1; d < 4; ++d) w[d] = h ? 0u : w[d];
+                for (int d = 2; d < 4; ++d) w[d] = h ? 0u : w[d];
                 x = __builtin_bit_cast(bf16x8, w);
             }
         };
@@ -332,9 +365,9 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
     uint32_t lo = 0xffffffffu, hi = 0;   // (uniform) first and last tile with an infinite or NaN output
     const int j0 = (T::OWN == 16 ? 0 : ks * (T::OWN / 4) * 8) + 4 * h;   // the lane's first channel of the block
     const int room = P.Co - m0 - j0;
-    auto store = [&](auto secondc, auto fullc, uint32_t t, bool there, const auto &v) __attribute__((always_inline)) {
+    auto store = [&](auto secondc, auto fullc, uint32_t t, bool there, int blk, const auto &v) __attribute__((always_inline)) {
         const uint32_t P0 = t * T::TN, Pend = min(P0 + T::TN, P.npix) - 1u;
-        const uint32_t pix = P0 + (uint32_t)(px * 32 + l32);
+        const uint32_t pix = P0 + pixel(blk);
         const bool live = there && pix <= Pend;
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
         const uint32_t pin = min(pix, Pend) - img * P.howo;
@@ -379,6 +412,39 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         }
     };
 
+    // The same for the four neighbouring pixels of a lane, 16 bytes per channel (all inside the layer or all outside, in one plane).
+    auto store_wide = [&](auto fullc, uint32_t t, const floatx16 (&v)[T::B]) __attribute__((always_inline)) {
+        const uint32_t P0 = t * T::TN, Pend = min(P0 + T::TN, P.npix) - 1u;
+        const uint32_t pix = P0 + pixel(0);
+        const bool live = pix <= Pend;
+        const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
+        const uint32_t pin = min(pix, Pend) - img * P.howo;
+        const size_t obase = ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo;
+        const size_t left = (P.out_elems - obase) * 4u;
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(P.out + obase, 0, left < kNoStore ? left : kNoStore, 0x00020000);
+        const uint32_t howo4 = P.howo * 4u;
+        const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)j0 * P.howo) * 4u : kNoStore;
+        float odd = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int dj = 8 * (r >> 2) + (r & 3);
+            u32v4 w;   // (element by element: a bit cast applied to a vector element reads element 0)
+#pragma unroll
+            for (int b = 0; b < T::B; ++b) {
+                const float o = v[b][r] * (1.0f / (kScale * kScale));
+                odd = __builtin_elementwise_maximum(odd, __builtin_fabsf(o));
+                w[b] = __builtin_bit_cast(uint32_t, o);
+            }
+            const uint32_t vo = decltype(fullc)::value || dj < room ? voff : kNoStore;
+            // (nothing is scheduled between the store and four idle cycles behind it: its data leave the register file over several cycles)
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_raw_buffer_store_b128(w, ro, vo, (uint32_t)dj * howo4, 0);
+            asm volatile("s_nop 3");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (__builtin_amdgcn_ballot_w64(live && !finite(odd))) { lo = min(lo, t); hi = t; }
+    };
+
     // Sums of the channels that other waves store go to LDS, [block][owner][source][quad][lane]; the wave's own stay.
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
@@ -410,7 +476,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
                 const f32x4 v = *(const lds_f32x4 *)(L + block + red + (uint32_t)(ks * (Q - 1) + s) * SLOT + w * 1024u);
                 own[w * 4] += v.x; own[w * 4 + 1] += v.y; own[w * 4 + 2] += v.z; own[w * 4 + 3] += v.w;
             }
-        store(secondc, fullc, t, there, own);
+        store(secondc, fullc, t, there, 0, own);
     };
 
     if (T::COLS && tid < 6) *(lds_bf16x8 *)(L + (uint32_t)(tid / 3) * T::STAGE + 2u * CHB + (uint32_t)(tid % 3) * PCB + PCB - 16u) = bf16x8{};
@@ -427,12 +493,18 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
                 fetch(t + 2 * gx < stop ? t + 2 * gx : t);
             };
             if constexpr (LATE) next();
-            const floatx16 sum = multiply(qc, t, at);
             if constexpr (Q > 1) {
+                const floatx16 sum = multiply(qc, t, 0, at);
                 finish(secondc, fullc, t == first ? t : t - gx, t != first, red ^ T::RED);
                 hand_over(qc, sum, red);
+            } else if constexpr (T::WIDE && !decltype(secondc)::value) {
+                floatx16 sum[T::B];
+#pragma unroll
+                for (int b = 0; b < T::B; ++b) sum[b] = multiply(qc, t, b, at);
+                store_wide(fullc, t, sum);
             } else {
-                store(secondc, fullc, t, true, sum);
+#pragma unroll
+                for (int b = 0; b < T::B; ++b) store(secondc, fullc, t, true, b, multiply(qc, t, b, at));
             }
             if constexpr (!LATE) next();
             at ^= T::STAGE;
@@ -482,17 +554,17 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
     pass(std::true_type{});
 }
 
-template <int HF, int R, int Q, int PX, bool IMP>
-__global__ __launch_bounds__(64 * R * Q * PX, R * Q * PX / 4) void conv_split_stem_kernel(StemParams P)
+template <int HF, int R, int Q, int PX, int B, bool IMP>
+__global__ __launch_bounds__(64 * R * Q * PX, R * Q * PX < 8 ? 2 : R * Q * PX / 4) void conv_split_stem_kernel(StemParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    conv_stem_body<Stem<HF, R, Q, PX>, IMP>(P, smem);
+    conv_stem_body<Stem<HF, R, Q, PX, B>, IMP>(P, smem);
 }
 
-template <int HF, int R, int Q, int PX>
+template <int HF, int R, int Q, int PX, int B = 1>
 static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, LaunchPlan *plan)
 {
-    using T = Stem<HF, R, Q, PX>;
+    using T = Stem<HF, R, Q, PX, B>;
     int dev = 0, ncu = 0;
     hipError_t e = device_cus(&dev, &ncu);
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
@@ -500,21 +572,22 @@ static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, Lau
     // chunks that a tile may need: P0 anywhere in a row, rows of Wo pixels
     const long long rows = std::min<long long>((T::TN + P.Wo - 2) / P.Wo + 1, T::TN);
     const long long cols = ((long long)T::TN - rows) * P.s + rows * HF;
-    const long long chunks = T::COLS ? cols + rows + 2 : (cols * HF) / 8 + rows + 1;   // (each row is rounded up; zeros; reads past the last)
+    const long long chunks = T::COLS ? cols + rows + 2 : (T::PAIRS ? cols / 2 + rows + 1 : (cols * HF) / 8 + rows + 1);   // (each row is rounded up; zeros; reads past the last)
     if (chunks > T::CAP) return hipErrorNotSupported;
     const unsigned long long imgs = std::min<unsigned long long>((unsigned long long)T::TN / P.howo + 2, (unsigned long long)P.N);
     if (imgs * 3ull * P.plane * 4ull >= (1ull << 31)) return hipErrorNotSupported;
     if (((unsigned long long)P.Co * imgs + 64ull) * P.howo * 4ull >= kNoStore) return hipErrorNotSupported;
+    constexpr uint32_t kPerCu = T::NW < 8 && 2 * T::LDS <= 160 * 1024 ? 2 : 1;
     P.ntiles = (P.npix + T::TN - 1) / T::TN;
     const int mgroups = (P.Co + 32 * R - 1) / (32 * R);
-    uint32_t gx = (uint32_t)ncu / (uint32_t)mgroups;
+    uint32_t gx = (uint32_t)ncu * kPerCu / (uint32_t)mgroups;
     if (gx >= 8) gx &= ~7u;   // (whole rows of the grid per XCD, whatever blockIdx.y)
     gx = std::max(1u, std::min(gx, P.ntiles));
     if (plan) {
-        plan_record(plan, dim3(gx, mgroups), T::NT, T::LDS, "conv_split_stem_kernel<%d, %d, %d, %d, %s>", HF, R, Q, PX, tf(implicit));
+        plan_record(plan, dim3(gx, mgroups), T::NT, T::LDS, "conv_split_stem_kernel<%d, %d, %d, %d, %d, %s>", HF, R, Q, PX, B, tf(implicit));
         return hipSuccess;
     }
-    void (*kern)(StemParams) = implicit ? &conv_split_stem_kernel<HF, R, Q, PX, true> : &conv_split_stem_kernel<HF, R, Q, PX, false>;
+    void (*kern)(StemParams) = implicit ? &conv_split_stem_kernel<HF, R, Q, PX, B, true> : &conv_split_stem_kernel<HF, R, Q, PX, B, false>;
     static KernelCache kc[2];
     if ((e = allow_dynamic_lds(kc[implicit], reinterpret_cast<const void *>(kern), T::LDS, dev)) != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(gx, mgroups), dim3(T::NT), T::LDS, st, P);
@@ -525,7 +598,7 @@ static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, Lau
 hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st, bool implicit, LaunchPlan *plan)
 {
     if (sh.Ci != 3 || sh.Hf != sh.Wf) return hipErrorNotSupported;
-    if (!(sh.Hf == 7 && sh.s == 2) && !(sh.Hf == 11 && sh.s % 4 == 0 && sh.s <= 64)) return hipErrorNotSupported;
+    if (!(sh.Hf == 3 && sh.s <= 2) && !(sh.Hf == 7 && sh.s == 2) && !(sh.Hf == 11 && sh.s % 4 == 0 && sh.s <= 64)) return hipErrorNotSupported;
     StemParams P = {};
     P.src = src; P.flt = flt; P.out = out;
     P.N = sh.N; P.Ci = sh.Ci; P.Ho = sh.Ho; P.Wo = sh.Wo; P.Co = sh.Co; P.s = sh.s; P.K = sh.K;
@@ -537,7 +610,7 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     P.howo = (uint32_t)(sh.Ho * sh.Wo); P.npix = (uint32_t)sh.npix;
     P.src_elems = (size_t)sh.N * 3u * P.plane; P.out_elems = (size_t)sh.npix * sh.Co;
     const int cols = (sh.Wo - 1) * sh.s + sh.Wf;
-    P.chf = sh.Hf == 7 ? (cols + 1) & ~1 : (cols * sh.Hf + 7) >> 3;
+    P.chf = sh.Hf == 7 ? (cols + 1) & ~1 : (sh.Hf == 3 ? (cols + 1) >> 1 : (cols * sh.Hf + 7) >> 3);
     P.d_wo = make_fastdiv((uint32_t)sh.Wo); P.d_ho = make_fastdiv((uint32_t)sh.Ho);
     P.d_howo = make_fastdiv(P.howo); P.d_chf = make_fastdiv((uint32_t)P.chf);
     const int blocks = (sh.Co + 31) / 32;
@@ -545,6 +618,22 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     if (device_cus(&dev, &ncu) != hipSuccess) ncu = 256;   // (planning without a device)
     const uint32_t per_cu = P.npix / (uint32_t)ncu;   // pixels
     // Which instance: us, two calls / workspace-free (convolution only).
+    if (sh.Hf == 3) {
+        // Stride 2: 224x224, padding 1, N=8 16 channels 13.0 / 13.7, here 11.3 / 12.2; 64 channels 15.7 / 16.3, 12.5 / 15.2; N=64 16 channels
+        // 74 / 75, 33 / 42; 64 channels 88 / 85, 50 / 57; 96 channels 198 / 180, 95 / 132.
+        if (sh.s == 2) {
+            if (blocks % 2) return launch_stem_t<3, 1, 1, 4>(P, implicit, st, plan);
+            return launch_stem_t<3, 2, 1, 4>(P, implicit, st, plan);
+        }
+        // At stride 1 the output stream is the bound, and with 64 channels the fp32 kernel, whose tiles are half as long, keeps it fuller (N=128
+        // 222x222 outputs 369, here 432; tiles of that length here 413, a group of 32 channels each 441).  With an odd number of blocks
+        // it runs groups of 32 channels too and is bound by their matrix work: N=128, 222x222 16 channels 278 / 330, here 167 / 194;
+        // 96 channels 940 / 1086, 787 / 729; N=16 96 channels 122 / 136, 80 / 95; N=128 64x64 32 channels 23.2 / 27.7, 22.4 / 27.0.  Below that
+        // number of pixels, or without 16-byte stores (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the faster.
+        const bool wide = P.howo % 4u == 0 && reinterpret_cast<uintptr_t>(out) % 16u == 0;
+        if (blocks % 2 == 0 || !wide || per_cu < 2048) return hipErrorNotSupported;
+        return launch_stem_t<3, 1, 1, 4, 4>(P, implicit, st, plan);
+    }
     if (sh.Hf == 7) {
         // Up to 64 channels and a tile or less per compute unit the fp32 kernel's shorter start is the faster (where it takes the layer:
         // three output rows per 64 pixels): 64 channels, N=1 224x224 10.9 / 11.7, here 11.3 / 13.2; N=2 16.6 / 17.5, here 13.4 / 15.8;

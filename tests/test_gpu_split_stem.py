@@ -11,22 +11,28 @@ from test_gpu_split import _assert_like_basic
 
 pytestmark = pytest.mark.gpu
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the instance: blocks of 32 channels, parts of K, blocks of 32 pixels per workgroup
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the instance: blocks of 32 channels, parts of K, runs of pixels per workgroup, blocks of 32
+# pixels per run
 SHAPES = [
-    ((9, 3, 85, 91, 17, 7, 7, 2, 3), (1, 2, 4)),      # odd widths, a last tile of a few pixels
-    ((21, 3, 32, 32, 32, 7, 7, 2, 0), (1, 2, 4)),     # 13 pixels a row: eleven rows to a tile
-    ((9, 3, 91, 85, 33, 7, 7, 2, 3), (2, 2, 2)),      # one channel past a block
-    ((1, 3, 33, 36, 130, 7, 7, 2, 1), (2, 2, 2)),     # three groups of channels, the last block of two
-    ((41, 3, 139, 144, 64, 7, 7, 2, 3), (2, 1, 4)),   # several tiles per workgroup
-    ((60, 3, 118, 113, 50, 7, 7, 2, 8), (2, 1, 4)),   # padding wider than the filter: windows of zeros
-    ((33, 3, 31, 64, 96, 7, 7, 2, 3), (3, 2, 2)),
-    ((1, 3, 7, 47, 70, 7, 7, 2, 0), (3, 2, 2)),       # one row, one tile
-    ((16, 3, 227, 225, 20, 11, 11, 4, 0), (1, 4, 2)),
-    ((300, 3, 11, 530, 31, 11, 11, 4, 0), (1, 4, 2)),  # one row per image: a tile may span two images
-    ((1, 3, 60, 230, 5, 11, 11, 4, 5), (2, 4, 1)),
-    ((55, 3, 39, 40, 64, 11, 11, 4, 5), (2, 4, 1)),   # eight pixels a row
-    ((9, 3, 130, 127, 96, 11, 11, 4, 2), (3, 4, 1)),
-    ((7, 3, 63, 67, 131, 11, 11, 4, 0), (3, 4, 1)),   # two groups of channels
+    ((9, 3, 85, 91, 17, 7, 7, 2, 3), (1, 2, 4, 1)),      # odd widths, a last tile of a few pixels
+    ((21, 3, 32, 32, 32, 7, 7, 2, 0), (1, 2, 4, 1)),     # 13 pixels a row: eleven rows to a tile
+    ((9, 3, 91, 85, 33, 7, 7, 2, 3), (2, 2, 2, 1)),      # one channel past a block
+    ((1, 3, 33, 36, 130, 7, 7, 2, 1), (2, 2, 2, 1)),     # three groups of channels, the last block of two
+    ((41, 3, 139, 144, 64, 7, 7, 2, 3), (2, 1, 4, 1)),   # several tiles per workgroup
+    ((60, 3, 118, 113, 50, 7, 7, 2, 8), (2, 1, 4, 1)),   # padding wider than the filter: windows of zeros
+    ((33, 3, 31, 64, 96, 7, 7, 2, 3), (3, 2, 2, 1)),
+    ((1, 3, 7, 47, 70, 7, 7, 2, 0), (3, 2, 2, 1)),       # one row, one tile
+    ((16, 3, 227, 225, 20, 11, 11, 4, 0), (1, 4, 2, 1)),
+    ((300, 3, 11, 530, 31, 11, 11, 4, 0), (1, 4, 2, 1)),  # one row per image: a tile may span two images
+    ((1, 3, 60, 230, 5, 11, 11, 4, 5), (2, 4, 1, 1)),
+    ((55, 3, 39, 40, 64, 11, 11, 4, 5), (2, 4, 1, 1)),   # eight pixels a row
+    ((9, 3, 130, 127, 96, 11, 11, 4, 2), (3, 4, 1, 1)),
+    ((7, 3, 63, 67, 131, 11, 11, 4, 0), (3, 4, 1, 1)),   # two groups of channels
+    ((5, 3, 61, 64, 30, 3, 3, 2, 1), (1, 1, 4, 1)),
+    ((3, 3, 47, 45, 65, 3, 3, 2, 0), (1, 1, 4, 1)),   # 22 pixels a row: seven rows to a tile
+    ((9, 3, 64, 59, 50, 3, 3, 2, 1), (2, 1, 4, 1)),
+    ((60, 3, 101, 102, 17, 3, 3, 1, 0), (1, 1, 4, 4)),   # 16-byte stores, 9900 pixels a plane
+    ((54, 3, 99, 100, 67, 3, 3, 1, 1), (1, 1, 4, 4)),
 ]
 
 
@@ -58,7 +64,7 @@ def _run(shape, I, F):
 def test_both_calls(shape, instance):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     for w in (False, True):
-        assert _plan(shape, w) == "conv_split_stem_kernel<%d, %d, %d, %d, %s>" % (Hf, *instance, "true" if w else "false")
+        assert _plan(shape, w) == "conv_split_stem_kernel<%d, %d, %d, %d, %d, %s>" % (Hf, *instance, "true" if w else "false")
     I, F = workloads.random_layer_inputs(9700 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
     got, fp32 = _run(shape, I, F)
@@ -69,7 +75,7 @@ def test_both_calls(shape, instance):
 
 
 @pytest.mark.parametrize("ei,ef", [(-118, 4), (4, -124), (-140, 20), (105, 0), (-120, 120), (60, 60)])
-@pytest.mark.parametrize("shape", [SHAPES[4][0], SHAPES[6][0], SHAPES[12][0]], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[4][0], SHAPES[6][0], SHAPES[12][0], SHAPES[17][0]], ids=lambda v: "x".join(map(str, v)))
 def test_no_operand_loses_bits(shape, ei, ef):
     """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
@@ -80,7 +86,7 @@ def test_no_operand_loses_bits(shape, ei, ef):
     assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0][0], SHAPES[4][0], SHAPES[8][0], SHAPES[12][0]], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[0][0], SHAPES[4][0], SHAPES[8][0], SHAPES[12][0], SHAPES[16][0], SHAPES[18][0]], ids=lambda v: "x".join(map(str, v)))
 def test_infinities_nan_and_the_ends_of_the_range(shape):
     """As in plain fp32 (the one-thread-per-output kernel), in both calls: also beside windows (the padded parts of a chunk hold zeros)."""
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
