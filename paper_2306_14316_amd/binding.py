@@ -6,6 +6,7 @@ torch stream is handed to the library as the hipStream_t.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -121,10 +122,15 @@ def im2col_footprint_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) -> int:
     return b.value
 
 
+# The host side of a call is what a small layer waits for (a 3x3 layer on one 32x32 image, two calls: 20 us, of which the two
+# launches take 7.5), so a call asks the library for its sizes once per layer (shapes that it refuses are not kept), names no
+# module and wraps no pointer or stream on its way: 20 -> 11.7 us.
+@functools.lru_cache(maxsize=1024)
 def _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad) -> int:
     return im2win_workspace_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) // 4
 
 
+@functools.lru_cache(maxsize=1024)
 def _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad) -> int:
     Ho, Wo = im2win_out_shape(Hi, Wi, Hf, Wf, stride, pad)
     return N * Co * Ho * Wo
@@ -137,21 +143,32 @@ def layer_sizes(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad) -> dict:
             "output_elems": N * Co * Ho * Wo}
 
 
-def _dev_ptr(t, name: str, numel: int):
+_torch = None
+
+
+def _load_torch():
+    global _torch
     import torch
+    _torch = torch
+    return torch
+
+
+def _dev_ptr(t, name: str, numel: int):
+    torch = _torch or _load_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a torch tensor in GPU memory" % name)
     if t.dtype != torch.float32 or not t.is_contiguous():
         raise TypeError("%s must be contiguous fp32" % name)
     if t.numel() != numel:
         raise ValueError("%s has %d elements, expected %d" % (name, t.numel(), numel))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:   # torch's current stream on the current device
+        torch = _torch or _load_torch()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def im2win_transform(input, window, N, Ci, Hi, Wi, Hf, Wf, stride, pad, stream=None):
