@@ -578,6 +578,8 @@ hipError_t launch_conv_implicit(const float *in, const float *flt, float *out, c
     if (fe != hipErrorNotSupported) return fe;
     fe = launch_conv_mfma_fast(P, sh, blocks, st, true, 4, plan);
     if (fe != hipErrorNotSupported) return fe;
+    fe = launch_conv_split_1x1(in, flt, out, sh, st, true, plan);
+    if (fe != hipErrorNotSupported) return fe;
     fe = launch_conv_mfma_1x1(in, flt, out, sh, st, true, plan);
     if (fe != hipErrorNotSupported) return fe;
     fe = launch_generic(P, sh, blocks, st, plan);
@@ -603,7 +605,9 @@ hipError_t launch_conv_mfma(const float *win, const float *flt, float *out, cons
         fe = launch_conv_mfma_fast(P, sh, blocks, st, false,
                                    variant == kVariantNarrowLoads ? 2 : (variant == kVariantScalarLoads ? 1 : 4), plan);
         if (fe != hipErrorNotSupported) return fe;
-        const hipError_t oe = launch_conv_mfma_1x1(win, flt, out, sh, st, false, plan);
+        hipError_t oe = launch_conv_split_1x1(win, flt, out, sh, st, false, plan);
+        if (oe != hipErrorNotSupported) return oe;
+        oe = launch_conv_mfma_1x1(win, flt, out, sh, st, false, plan);
         if (oe != hipErrorNotSupported) return oe;
         const hipError_t pe = launch_generic_pipe(P, sh, blocks, st, plan);
         if (pe != hipErrorNotSupported) return pe;

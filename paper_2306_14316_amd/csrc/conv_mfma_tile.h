@@ -110,6 +110,9 @@ hipError_t launch_conv_split(const MfmaParams &P, const Shape &sh, uint32_t bloc
 // conv_split_stem.hip: three-channel layers on the bf16 matrix cores.
 hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st,
                                   bool implicit, LaunchPlan *plan);
+// conv_split_1x1.hip: 1x1 layers on the bf16 matrix cores.
+hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st,
+                                 bool implicit, LaunchPlan *plan);
 hipError_t launch_conv_mfma_shallow(const float *win, const float *flt, float *out, const Shape &sh,
                                     hipStream_t st, bool implicit = false, LaunchPlan *plan = nullptr);
 hipError_t launch_conv_mfma_1x1(const float *src, const float *flt, float *out, const Shape &sh,

@@ -1,0 +1,317 @@
+// bf16-piece convolution (see conv_split.h for the pieces and their precision) of 1x1 layers: the GEMM
+// O[Co x pixels] = F[Co x Ci] * I[Ci x pixels], any stride, no padding.
+//
+// What bounds it: six MFMAs per fp32 product, and beside them the cutting of both operands -- a tile of 128 channels x 128 pixels
+// cuts 256 words per 16384 products, 6.5 vector instructions each, half of the time of its MFMAs.  So the cutting has to run beside
+// the MFMAs and a tile has to be large: tiles of 64 channels cut each pixel word Co/64 times, which took what the MFMAs save.
+// Eight waves, two per SIMD, all of which stage and multiply; half of them multiply first and stage then, the others the other way
+// round (see conv_split_stem.hip).  K blocks of 32 channels, two LDS stages, one barrier per block; a workgroup runs its tiles as one
+// sequence of K blocks, so the next tile's first block is on its way while a tile ends.
+//
+// Measured (convolution alone, us, fp32 matrix cores -> here): 256 -> 256 channels 28x28 N=64 60 -> 54, 512 -> 512 14x14 N=32 37 -> 26, N=128
+// 113 -> 96, 1024 -> 256 14x14 N=64 69 -> 46, 128 -> 129 30x33 N=64 78 -> 30 (generic kernel before).  A K block takes 1.4 us where its MFMAs take
+// 0.65: half of it is the wave's own chain of cutting, writing and reading.  Fetching two blocks ahead 60 on the first, tiles of 64 x 256 for
+// layers of up to 64 channels 16 against 13 (256 -> 64 56x56 N=8).  Relative 2-norm error against 64 bits 7e-8 (fp32 matrix cores 2e-7).
+//
+// LDS: [channel group of 8][piece][row or pixel][8 channels], one 16-byte read per operand and piece.  A thread fetches eight
+// consecutive filter words, and one word of eight channel planes per pixel, lanes on neighbouring pixels: strides and planes of any size
+// are only another offset per pixel.
+#include "conv_split.h"
+#include "runtime_cache.h"
+
+#include <algorithm>
+
+namespace im2win {
+
+struct Split1x1Params : SplitParams {
+    uint32_t npix, ntiles;
+    int nkb;                  // K blocks of 32 channels
+    uint32_t rowstep;         // words of the source from one output row to the next
+    FastDiv d_wo, d_howo;
+};
+
+constexpr uint32_t kNoStore1 = 0xffffff00u;   // no output descriptor here covers it
+
+// Tiles of 128 channels x 128 pixels; a wave owns 64 x 32.
+struct Tile1x1 {
+    static constexpr int WGM = 2, TM = 128, TN = 128;
+    // (+64: the four groups of a filter row, which neighbouring lanes write, start in other banks)
+    static constexpr uint32_t APL = 3 * TM * 16 + 64, BPL = 3 * TN * 16, BOFF = 4 * APL, STAGE = BOFF + 4 * BPL, PASS = 2 * STAGE;
+    static constexpr size_t LDS = PASS + 64;
+};
+
+template <bool IMP>
+__global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P)
+{
+    using T = Tile1x1;
+    constexpr int TM = T::TM, TN = T::TN;
+    extern __shared__ __align__(16) unsigned char smem[];
+    lds_byte *const L = (lds_byte *)smem;
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % T::WGM, wn = wave / T::WGM;
+    const bool late = (wave >> 2) & 1;
+    const uint32_t gx = gridDim.x;
+    uint32_t first = blockIdx.x, stop = P.ntiles;
+    float scale = kScale;
+
+    auto origin = [&](uint32_t t, int &m0, uint32_t &P0) __attribute__((always_inline)) {   // (the M tiles of a pixel tile are neighbours in one L2)
+        const uint32_t lb = xcd_swizzle(t, P.ntiles), tn = fdiv(lb, P.d_tm);
+        m0 = (int)(lb - tn * (uint32_t)P.tiles_m) * TM;
+        P0 = tn * TN;
+    };
+
+    // ---- staging.  Filter item: row tid/4, channels 8*(tid%4) ..; pixel item: pixel tid%128, group tid/128 of 8 channels
+    float wa[8], wb[8];
+    const int ar = tid >> 2, ag = tid & 3;
+    const int bp = tid % TN, bg = tid / TN;
+    uint32_t ft = 0, fvo = 0, bvo = 0;     // tile and offsets of the block being fetched
+    int fkb = 0;
+    __amdgpu_buffer_rsrc_t rf, rw;
+    auto desc = [](const float *base, size_t elems) __attribute__((always_inline)) {
+        const size_t left = elems * 4u;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, left < 0x7fffffffull ? left : 0x7fffffffull, 0x00020000);
+    };
+    auto aim = [&](uint32_t t) __attribute__((always_inline)) {
+        int m0;
+        uint32_t P0;
+        origin(t, m0, P0);
+        rf = desc(P.flt + (size_t)m0 * P.K, ((size_t)P.Co - (size_t)m0) * P.K);
+        fvo = m0 + ar < P.Co ? (uint32_t)(ar * P.K + ag * 8) * 4u : kNoWord;
+        const uint32_t img0 = fdiv(P0, P.d_howo);
+        const size_t base = (size_t)img0 * P.Ci * P.plane;
+        rw = desc(P.src + base, P.src_elems - base);
+        const uint32_t px = min(P0 + (uint32_t)bp, P.npix - 1u), img = fdiv(px, P.d_howo), pin = px - img * P.howo;
+        const uint32_t m = fdiv(pin, P.d_wo), n = pin - m * (uint32_t)P.Wo;
+        const uint32_t at = (img - img0) * (uint32_t)P.Ci * P.plane + m * P.rowstep + n * (uint32_t)P.s;
+        bvo = (at + (uint32_t)(bg * 8) * P.plane) * 4u;
+    };
+    auto fetch = [&]() __attribute__((always_inline)) {   // the block (ft, fkb); then the one after it, or the last again
+        const int c0 = fkb * 32;
+        const uint32_t vo = c0 + ag * 8 < P.Ci ? fvo : kNoWord;
+        const u32v4 a0 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u, 0), a1 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u + 16u, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const uint32_t w = e < 4 ? a0[e & 3] : a1[e & 3]; wa[e] = __builtin_bit_cast(float, w); }
+        const uint32_t bo = c0 + bg * 8 < P.Ci ? bvo : kNoWord;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wb[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, bo, (uint32_t)(c0 + e) * P.plane * 4u, 0));
+        if (++fkb == P.nkb) {
+            if (ft + gx < stop) { ft += gx; aim(ft); fkb = 0; }
+            else fkb = P.nkb - 1;
+        }
+    };
+    auto stage = [&](uint32_t at) __attribute__((always_inline)) {
+        bf16x8 c[3];
+        split8(wa, scale, c[0], c[1], c[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(lds_bf16x8 *)(L + at + (uint32_t)ag * T::APL + (uint32_t)(k * TM + ar) * 16u) = c[k];
+        split8(wb, scale, c[0], c[1], c[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(lds_bf16x8 *)(L + at + T::BOFF + (uint32_t)bg * T::BPL + (uint32_t)(k * TN + bp) * 16u) = c[k];
+    };
+
+    // ---- multiplication of one K block: two steps, the second's operands read during the first
+    floatx16 acc[2], acs[2];
+    auto multiply = [&](uint32_t at) __attribute__((always_inline)) {
+        struct Ops { bf16x8 a[2][3], b[3]; };
+        Ops o[2];
+        auto read = [&](int s, Ops &x) __attribute__((always_inline)) {
+            const uint32_t pa = at + (uint32_t)(2 * s + h) * T::APL + (uint32_t)(wm * 64 + l32) * 16u;
+            const uint32_t pb = at + T::BOFF + (uint32_t)(2 * s + h) * T::BPL + (uint32_t)(wn * 32 + l32) * 16u;
+#pragma unroll
+            for (int k = 2; k >= 0; --k) {
+                x.b[k] = *(const lds_bf16x8 *)(L + pb + k * TN * 16);
+#pragma unroll
+                for (int f = 0; f < 2; ++f) x.a[f][k] = *(const lds_bf16x8 *)(L + pa + (k * TM + f * 32) * 16);
+            }
+        };
+        read(0, o[0]);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (s == 0) read(1, o[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    floatx16 &c = i == 5 ? acc[f] : acs[f];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o[s].a[f][pa[i]], o[s].b[pb[i]], c, 0, 0, 0);
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[f][v] = 0.0f; acs[f][v] = 0.0f; }
+    };
+
+    uint32_t lo = 0xffffffffu, hi = 0;   // (uniform) first and last tile with an infinite or NaN output
+    auto store = [&](auto secondc, uint32_t t) __attribute__((always_inline)) {
+        int m0;
+        uint32_t P0;
+        origin(t, m0, P0);
+        m0 += wm * 64;
+        const uint32_t pix = P0 + (uint32_t)(wn * 32 + l32);
+        const bool live = pix < P.npix;
+        const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, P.npix - 1u), P.d_howo);
+        const uint32_t pin = min(pix, P.npix - 1u) - img * P.howo;
+        const size_t obase = ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo;
+        const size_t left = (P.out_elems - obase) * 4u;
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(P.out + obase, 0, left < kNoStore1 ? left : kNoStore1, 0x00020000);
+        const uint32_t howo4 = P.howo * 4u;
+        const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)(4 * h) * P.howo) * 4u : kNoStore1;
+        const int room = P.Co - m0 - 4 * h;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            float v[16], big = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                v[r] = (acc[f][r] + acs[f][r]) * (decltype(secondc)::value ? 1.0f / (kScale2 * kScale2) : 1.0f / (kScale * kScale));
+                big = __builtin_elementwise_maximum(big, __builtin_fabsf(v[r]));
+            }
+            if constexpr (decltype(secondc)::value) {
+                uint32_t small = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dj = 32 * f + 8 * (r >> 2) + (r & 3);
+                    if (!live || dj >= room) continue;
+                    float *const to = P.out + ((size_t)img * P.Co + (size_t)(m0 + 4 * h + dj)) * P.howo + pin;
+                    const float old = *to;
+                    if (finite(old)) continue;
+                    float val = v[r];
+                    if (settle(acc[f][r], old, val)) small |= 1u << r;
+                    else *to = val;
+                }
+                while (small) {
+                    const int r = __builtin_ctz(small);
+                    small &= small - 1;
+                    const int j = m0 + 4 * h + 32 * f + 8 * (r >> 2) + (r & 3);
+                    const int m = (int)fdiv(pin, P.d_wo), n = (int)pin - m * P.Wo;
+                    P.out[((size_t)img * P.Co + (size_t)j) * P.howo + pin] = dot_fp32<1, 1, IMP>(P, img, j, m, n);
+                }
+            } else {
+                if (__builtin_amdgcn_ballot_w64(live && !finite(big))) {
+                    // (the small products of an infinity are NaN: the sum of the h*h products stands for the output)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float x = acc[f][r];
+                        v[r] = finite(x) ? v[r] : x;
+                    }
+                    lo = min(lo, t);
+                    hi = t;
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dj = 32 * f + 8 * (r >> 2) + (r & 3);
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[r]), ro, dj < room ? voff : kNoStore1, (uint32_t)dj * howo4, 0);
+                }
+            }
+        }
+    };
+
+    // One pass over the tiles first, first + gx, ... below stop; LATE: the wave stages before it multiplies.  After the last block the
+    // last one is staged again.
+    auto tiles = [&](auto secondc, auto latec) __attribute__((always_inline)) {
+        uint32_t at = 0;
+        for (uint32_t t = first; t < stop; t += gx) {
+            clear();
+            for (int kb = 0; kb < P.nkb; ++kb) {
+                auto next = [&]() __attribute__((always_inline)) { stage(at ^ T::STAGE); fetch(); };
+                if constexpr (decltype(latec)::value) next();
+                multiply(at);
+                if constexpr (!decltype(latec)::value) next();
+                at ^= T::STAGE;
+                lds_barrier();
+            }
+            store(secondc, t);
+        }
+    };
+    auto pass = [&](auto secondc) __attribute__((always_inline)) {
+        ft = first;
+        fkb = 0;
+        aim(ft);
+        fetch();
+        stage(0);
+        fetch();
+        lds_barrier();
+        if constexpr (decltype(secondc)::value) tiles(secondc, std::false_type{});
+        else if (late) tiles(secondc, std::true_type{});
+        else tiles(secondc, std::false_type{});
+    };
+    static_assert(T::PASS % 16 == 0, "");
+    pass(std::false_type{});
+    // a second pass over the tiles, from the first to the last that has an infinite or NaN output (see conv_split.h)
+    if (lane == 0) *(lds_u32v2 *)(L + T::PASS + wave * 8) = u32v2{lo, hi};
+    lds_barrier();
+    uint32_t from = 0xffffffffu, to = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+        const u32v2 v = *(const lds_u32v2 *)(L + T::PASS + w * 8);
+        from = min(from, v[0]);
+        to = max(to, v[1]);
+    }
+    first = __builtin_amdgcn_readfirstlane(from);
+    if (first == 0xffffffffu) return;
+    stop = __builtin_amdgcn_readfirstlane(to) + 1u;
+    scale = kScale2;
+    pass(std::true_type{});
+}
+
+static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu, hipStream_t st, LaunchPlan *plan)
+{
+    using T = Tile1x1;
+    const unsigned long long imgs = std::min<unsigned long long>((unsigned long long)T::TN / P.howo + 2, (unsigned long long)P.N);
+    const unsigned long long larger = std::max((unsigned long long)P.Hi * P.Wi, (unsigned long long)P.Ho * P.rowlen);   // (both calls take the same kernel)
+    if (imgs * P.Ci * larger * 4ull >= (1ull << 31) || (unsigned long long)P.K * 4ull * T::TM >= (1ull << 31)) return hipErrorNotSupported;
+    if (((unsigned long long)P.Co * imgs + 128ull) * P.howo * 4ull >= kNoStore1) return hipErrorNotSupported;
+    P.tiles_m = (P.Co + T::TM - 1) / T::TM;
+    P.d_tm = make_fastdiv((uint32_t)P.tiles_m);
+    P.ntiles = ((P.npix + T::TN - 1) / T::TN) * (uint32_t)P.tiles_m;
+    const uint32_t grid = std::min(P.ntiles, (uint32_t)ncu);   // one workgroup per compute unit; it takes every grid-th tile
+    if (plan) {
+        plan_record(plan, dim3(grid), 512, T::LDS, "conv_split_1x1_kernel<%s>", tf(implicit));
+        return hipSuccess;
+    }
+    void (*kern)(Split1x1Params) = implicit ? &conv_split_1x1_kernel<true> : &conv_split_1x1_kernel<false>;
+    static KernelCache kc[2];
+    const hipError_t e = allow_dynamic_lds(kc[implicit], reinterpret_cast<const void *>(kern), T::LDS, dev);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), T::LDS, st, P);
+    return hipGetLastError();
+}
+
+// hipErrorNotSupported where the fp32 kernel (conv_mfma_1x1.hip) is the faster one or the layer is outside its conditions.
+hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st, bool implicit, LaunchPlan *plan)
+{
+    if (sh.Hf != 1 || sh.Wf != 1 || sh.p != 0 || sh.Ci % 8 != 0) return hipErrorNotSupported;
+    int dev = 0, ncu = 0;
+    hipError_t e = device_cus(&dev, &ncu);
+    if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
+    if (e != hipSuccess) return e;
+    Split1x1Params P = {};
+    P.src = src; P.flt = flt; P.out = out;
+    P.N = sh.N; P.Ci = sh.Ci; P.Ho = sh.Ho; P.Wo = sh.Wo; P.Co = sh.Co; P.s = sh.s; P.K = sh.K;
+    P.Hi = sh.Hi; P.Wi = sh.Wi; P.p = 0; P.rowlen = sh.rowlen;
+    P.plane = implicit ? (uint32_t)(sh.Hi * sh.Wi) : (uint32_t)((size_t)sh.Ho * sh.rowlen);
+    P.rowstep = implicit ? (uint32_t)sh.s * (uint32_t)sh.Wi : (uint32_t)sh.rowlen;
+    P.howo = (uint32_t)(sh.Ho * sh.Wo); P.npix = (uint32_t)sh.npix; P.nkb = (sh.Ci + 31) / 32;
+    P.src_elems = (size_t)sh.N * sh.Ci * P.plane; P.out_elems = (size_t)sh.npix * sh.Co;
+    P.d_wo = make_fastdiv((uint32_t)sh.Wo); P.d_howo = make_fastdiv(P.howo);
+    if (sh.s > 65536) return hipErrorNotSupported;
+    // Which is faster, in us: this kernel's rounds of tiles (a last round that leaves units idle runs at a higher clock: half of the loss is
+    // made up) at 1.6 for a K block, the fp32 kernel's 64 channel tiles at 115 TFLOP/s.  Measured, fp32 / here: 256 -> 256 28x28 N=64 59.5 / 52.5,
+    // 14x14 N=32 12.8 / 15.9, N=128 34 / 29; 512 -> 512 14x14 N=32 37 / 27, N=128 112 / 95, 56x56 N=64 807 / 645; 1024 -> 256 14x14 N=32 39 / 46,
+    // N=128 119 / 92; 256 -> 256 56x56 N=64 216 / 186; 64 -> 256 56x56 N=64 68 / 63; 256 -> 64 56x56 N=8 12.7 / 16.3.  (Channel counts that the
+    // fp32 1x1 kernel does not take run the generic one there, at 50 TFLOP/s.)
+    const double r = (double)((P.npix + 127) / 128) * ((sh.Co + 127) / 128) / ncu;
+    const double here = 2.0 + 0.5 * (r + std::max(1.0, (double)(long long)(r + 0.999))) * (P.nkb * 1.6 + 2.0);
+    const double fp32 = 3.0 + 2.0 * P.npix * ((sh.Co + 63) / 64 * 64.0) * sh.Ci / (sh.Co % 4 == 0 ? 115e6 : 50e6);
+    if (sh.Co <= 64 || here > 0.95 * fp32) return hipErrorNotSupported;
+    return launch_1x1_t(P, implicit, dev, ncu, st, plan);
+}
+
+}  // namespace im2win

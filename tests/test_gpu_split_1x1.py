@@ -1,0 +1,64 @@
+"""The bf16-piece kernel of 1x1 layers at ragged channel, pixel and plane counts through both calls, its error against the fp32 matrix
+cores, the range of its operands, infinities and NaN."""
+import pytest
+import torch
+
+import oracle
+import paper_2306_14316_amd as im2win
+from paper_2306_14316_amd import workloads
+from parity_util import assert_conv_close, conv_errors
+from test_gpu_split import _assert_like_basic
+from test_gpu_split_stem import _run
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (64, 256, 14, 15, 256, 1, 1, 1, 0),     # whole tiles of channels
+    (17, 520, 19, 21, 500, 1, 1, 1, 0),     # a last K block of one group, a last tile of 53 pixels
+    (300, 512, 7, 7, 130, 1, 1, 1, 0),      # two channels past a tile, planes of 49 pixels
+    (33, 512, 29, 28, 257, 1, 1, 2, 0),     # stride 2, one channel past a tile
+    (60, 504, 31, 40, 395, 1, 1, 3, 0),     # stride 3, 63 groups of channels
+    (7000, 256, 2, 2, 256, 1, 1, 1, 0),     # a tile spans 33 images
+    (64, 128, 30, 33, 129, 1, 1, 1, 0),     # several tiles per workgroup
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_both_calls(shape):
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    for w in (False, True):
+        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == "conv_split_1x1_kernel<%s>" % ("true" if w else "false")
+    I, F = workloads.random_layer_inputs(9950 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
+    O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
+    got, fp32 = _run(shape, I, F)
+    assert_conv_close(got, O_ref, B_ref)
+    l2, l2_32 = conv_errors(got, O_ref, B_ref)[1], conv_errors(fp32, O_ref, B_ref)[1]
+    print("relative L2 error: pieces %.2e, fp32 %.2e" % (l2, l2_32))
+    assert l2 <= l2_32
+
+
+@pytest.mark.parametrize("ei,ef", [(-118, 4), (4, -124), (-140, 20), (105, 0), (-120, 120), (60, 60)])
+def test_no_operand_loses_bits(ei, ef):
+    """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape = SHAPES[6]
+    I, F = workloads.random_layer_inputs(9960, N, Ci, Hi, Wi, Co, Hf, Wf)
+    I, F = torch.ldexp(I.double(), torch.tensor(ei)).float(), torch.ldexp(F.double(), torch.tensor(ef)).float()
+    O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
+    got, fp32 = _run(shape, I, F)
+    assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
+
+
+def test_infinities_nan_and_the_ends_of_the_range():
+    """As in plain fp32 (the one-thread-per-output kernel), in both calls."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape = SHAPES[6]
+    I, F = workloads.random_layer_inputs(9970, N, Ci, Hi, Wi, Co, Hf, Wf)
+    I.abs_()
+    I[0, 2, 10, 10], I[1, 1, 0, Wi - 1], I[2, 0, Hi - 1, 0] = float("inf"), float("-inf"), float("nan")
+    I[3, 127, 20, 20] = 3.4028e38            # rounds to infinity in bf16
+    I[4, 2, 5, 5], I[4, 9, 5, 5] = float("inf"), float("-inf")
+    I[5, 2, 21, 17] = torch.finfo(torch.float32).min
+    I[6, 1, 23, 30] = 2.0 ** 60
+    F[:, 2] *= 0.25
+    F[2, 2], F[3, 2], F[4, 1] = 0.0, 2.0 ** -140, 2.0 ** 50
+    ref = _assert_like_basic(shape, I, F)
+    assert torch.isnan(ref).any() and torch.isinf(ref).any()

@@ -98,3 +98,22 @@ def test_three_channel_layers():
         assert plans[0]["lds_bytes"] <= 160 * 1024 and (f == 3 or f * s in (14, 44, 88))
         seen.add((int(a[0].split("<")[1]), *(int(v) for v in a[1:5])))
     assert seen == tested, (seen ^ tested)
+
+
+def test_one_by_one_layers():
+    """The piece kernel of 1x1 layers: both calls take it or neither does, and it keeps to the layers it can index."""
+    rng, taken = random.Random(13), 0
+    for _ in range(20000):
+        Hi, s, p = int(2 ** rng.uniform(0, 8)), rng.choice([1, 1, 1, 2, 3]), rng.choice([0, 0, 0, 1])
+        Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(0, 8))
+        Ci, Co = rng.choice([8, 16, 60, 64, 250, 256, 520, 1024]), rng.choice([1, 64, 65, 128, 130, 256, 1000])
+        shape = (int(2 ** rng.uniform(0, 12)), Ci, Hi, Wi, Co, 1, 1, s, p)
+        if shape[0] * max(Ci, Co) * (Hi + 2 * p) * (Wi + 2 * p) >= 2 ** 31:
+            continue
+        plans = [im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w) for w in (False, True)]
+        split = [q["kernel"].startswith("conv_split_1x1") for q in plans]
+        assert split[0] == split[1], (shape, plans)
+        if split[0]:
+            taken += 1
+            assert p == 0 and Ci % 8 == 0 and Co > 64 and plans[0]["grid"] == plans[1]["grid"] and plans[0]["lds_bytes"] <= 160 * 1024
+    assert taken > 500
