@@ -8,10 +8,11 @@
 // round (see conv_split_stem.hip).  K blocks of 32 channels, two LDS stages, one barrier per block; a workgroup runs its tiles as one
 // sequence of K blocks, so the next tile's first block is on its way while a tile ends.
 //
-// Measured (convolution alone, us, fp32 matrix cores -> here): 256 -> 256 channels 28x28 N=64 60 -> 54, 512 -> 512 14x14 N=32 37 -> 26, N=128
-// 113 -> 96, 1024 -> 256 14x14 N=64 69 -> 46, 128 -> 129 30x33 N=64 78 -> 30 (generic kernel before).  A K block takes 1.4 us where its MFMAs take
-// 0.65: half of it is the wave's own chain of cutting, writing and reading.  Fetching two blocks ahead 60 on the first, tiles of 64 x 256 for
-// layers of up to 64 channels 16 against 13 (256 -> 64 56x56 N=8).  Relative 2-norm error against 64 bits 7e-8 (fp32 matrix cores 2e-7).
+// Measured (convolution alone, us, fp32 matrix cores -> tiles of 128 -> of 256 pixels): 256 -> 256 channels 28x28 N=64 60 -> 51 -> 45, 512 -> 512
+// 14x14 N=32 37 -> 25 -> 36, N=128 113 -> 95 -> 78, 56x56 N=64 853 -> 645 -> 563 (187 TFLOP/s); 1024 -> 256 14x14 N=64 69 -> 45 -> 64.  A lone tile
+// of 128 pixels takes 1.3 us for a K block whose MFMAs take 0.65: a wave's own chain of cutting, writing and reading; of 256 pixels 1.85 for
+// 1.3.  Fetching two blocks ahead gave nothing; tiles of 64 x 256 for layers of up to 64 channels 16 against 13 (256 -> 64 56x56 N=8).  Relative
+// 2-norm error against 64 bits 7e-8 (fp32 matrix cores 2e-7).
 //
 // LDS: [channel group of 8][piece][row or pixel][8 channels], one 16-byte read per operand and piece.  A thread fetches eight
 // consecutive filter words, and one word of eight channel planes per pixel, lanes on neighbouring pixels: strides and planes of any size
@@ -32,18 +33,19 @@ struct Split1x1Params : SplitParams {
 
 constexpr uint32_t kNoStore1 = 0xffffff00u;   // no output descriptor here covers it
 
-// Tiles of 128 channels x 128 pixels; a wave owns 64 x 32.
+// Tiles of 128 channels x 128*FN pixels; a wave owns 64 x 32*FN.
+template <int FN>
 struct Tile1x1 {
-    static constexpr int WGM = 2, TM = 128, TN = 128;
+    static constexpr int WGM = 2, TM = 128, TN = 128 * FN;
     // (+64: the four groups of a filter row, which neighbouring lanes write, start in other banks)
     static constexpr uint32_t APL = 3 * TM * 16 + 64, BPL = 3 * TN * 16, BOFF = 4 * APL, STAGE = BOFF + 4 * BPL, PASS = 2 * STAGE;
     static constexpr size_t LDS = PASS + 64;
 };
 
-template <bool IMP>
+template <int FN, bool IMP>
 __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P)
 {
-    using T = Tile1x1;
+    using T = Tile1x1<FN>;
     constexpr int TM = T::TM, TN = T::TN;
     extern __shared__ __align__(16) unsigned char smem[];
     lds_byte *const L = (lds_byte *)smem;
@@ -61,11 +63,11 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
         P0 = tn * TN;
     };
 
-    // ---- staging.  Filter item: row tid/4, channels 8*(tid%4) ..; pixel item: pixel tid%128, group tid/128 of 8 channels
-    float wa[8], wb[8];
+    // ---- staging.  Filter item: row tid/4, channels 8*(tid%4) ..; pixel items: pixel tid%TN, groups tid/TN + ... of 8 channels
+    float wa[8], wb[FN][8];
     const int ar = tid >> 2, ag = tid & 3;
     const int bp = tid % TN, bg = tid / TN;
-    uint32_t ft = 0, fvo = 0, bvo = 0;     // tile and offsets of the block being fetched
+    uint32_t ft = 0, fvo = 0, bvo[FN];     // tile and offsets of the block being fetched
     int fkb = 0;
     __amdgpu_buffer_rsrc_t rf, rw;
     auto desc = [](const float *base, size_t elems) __attribute__((always_inline)) {
@@ -84,7 +86,8 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
         const uint32_t px = min(P0 + (uint32_t)bp, P.npix - 1u), img = fdiv(px, P.d_howo), pin = px - img * P.howo;
         const uint32_t m = fdiv(pin, P.d_wo), n = pin - m * (uint32_t)P.Wo;
         const uint32_t at = (img - img0) * (uint32_t)P.Ci * P.plane + m * P.rowstep + n * (uint32_t)P.s;
-        bvo = (at + (uint32_t)(bg * 8) * P.plane) * 4u;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) bvo[j] = (at + (uint32_t)((bg + j * (4 / FN)) * 8) * P.plane) * 4u;
     };
     auto fetch = [&]() __attribute__((always_inline)) {   // the block (ft, fkb); then the one after it, or the last again
         const int c0 = fkb * 32;
@@ -92,9 +95,12 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
         const u32v4 a0 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u, 0), a1 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u + 16u, 0);
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const uint32_t w = e < 4 ? a0[e & 3] : a1[e & 3]; wa[e] = __builtin_bit_cast(float, w); }
-        const uint32_t bo = c0 + bg * 8 < P.Ci ? bvo : kNoWord;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) wb[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, bo, (uint32_t)(c0 + e) * P.plane * 4u, 0));
+        for (int j = 0; j < FN; ++j) {
+            const uint32_t bo = c0 + (bg + j * (4 / FN)) * 8 < P.Ci ? bvo[j] : kNoWord;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wb[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, bo, (uint32_t)(c0 + e) * P.plane * 4u, 0));
+        }
         if (++fkb == P.nkb) {
             if (ft + gx < stop) { ft += gx; aim(ft); fkb = 0; }
             else fkb = P.nkb - 1;
@@ -105,40 +111,52 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
         split8(wa, scale, c[0], c[1], c[2]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) *(lds_bf16x8 *)(L + at + (uint32_t)ag * T::APL + (uint32_t)(k * TM + ar) * 16u) = c[k];
-        split8(wb, scale, c[0], c[1], c[2]);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) *(lds_bf16x8 *)(L + at + T::BOFF + (uint32_t)bg * T::BPL + (uint32_t)(k * TN + bp) * 16u) = c[k];
+        for (int j = 0; j < FN; ++j) {
+            split8(wb[j], scale, c[0], c[1], c[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) *(lds_bf16x8 *)(L + at + T::BOFF + (uint32_t)(bg + j * (4 / FN)) * T::BPL + (uint32_t)(k * TN + bp) * 16u) = c[k];
+        }
     };
 
-    // ---- multiplication of one K block: two steps, the second's operands read during the first
-    floatx16 acc[2], acs[2];
+    // ---- multiplication of one K block: two steps.  The second's operands are read as the registers of each piece come free, the h pieces
+    // last, behind whose read the products of the m pieces run.  (A second set for the h pieces would spill.)
+    floatx16 acc[2][FN], acs[2][FN];
     auto multiply = [&](uint32_t at) __attribute__((always_inline)) {
-        struct Ops { bf16x8 a[2][3], b[3]; };
-        Ops o[2];
-        auto read = [&](int s, Ops &x) __attribute__((always_inline)) {
-            const uint32_t pa = at + (uint32_t)(2 * s + h) * T::APL + (uint32_t)(wm * 64 + l32) * 16u;
-            const uint32_t pb = at + T::BOFF + (uint32_t)(2 * s + h) * T::BPL + (uint32_t)(wn * 32 + l32) * 16u;
+        struct Piece { bf16x8 a[2], b[FN]; };
+        Piece ph, pm, pl;
+        const uint32_t pa = at + (uint32_t)h * T::APL + (uint32_t)(wm * 64 + l32) * 16u;
+        const uint32_t pb = at + T::BOFF + (uint32_t)h * T::BPL + (uint32_t)(wn * 32 * FN + l32) * 16u;
+        auto read = [&](int s, int k, Piece &x) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 2; k >= 0; --k) {
-                x.b[k] = *(const lds_bf16x8 *)(L + pb + k * TN * 16);
+            for (int f = 0; f < 2; ++f) x.a[f] = *(const lds_bf16x8 *)(L + pa + 2 * s * T::APL + (k * TM + f * 32) * 16);
 #pragma unroll
-                for (int f = 0; f < 2; ++f) x.a[f][k] = *(const lds_bf16x8 *)(L + pa + (k * TM + f * 32) * 16);
-            }
+            for (int n = 0; n < FN; ++n) x.b[n] = *(const lds_bf16x8 *)(L + pb + 2 * s * T::BPL + (k * TN + n * 32) * 16);
         };
-        read(0, o[0]);
+        auto mul = [&](floatx16 (&c)[2][FN], const Piece &x, const Piece &y) __attribute__((always_inline)) {
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+                for (int n = 0; n < FN; ++n) c[f][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[f], y.b[n], c[f][n], 0, 0, 0);
+        };
+        read(0, 1, pm); read(0, 0, ph); read(0, 2, pl);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             __builtin_amdgcn_sched_barrier(0);
-            if (s == 0) read(1, o[1]);
+            mul(acs, pm, pm);
+            mul(acs, pl, ph);
+            mul(acs, ph, pl);
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-#pragma unroll
-                for (int f = 0; f < 2; ++f) {
-                    floatx16 &c = i == 5 ? acc[f] : acs[f];
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o[s].a[f][pa[i]], o[s].b[pb[i]], c, 0, 0, 0);
-                }
+            if (s == 0) read(1, 2, pl);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(acs, pm, ph);
+            mul(acs, ph, pm);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s == 0) read(1, 1, pm);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(acc, ph, ph);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s == 0) read(1, 0, ph);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -146,16 +164,18 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[f][v] = 0.0f; acs[f][v] = 0.0f; }
+            for (int n = 0; n < FN; ++n)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { acc[f][n][v] = 0.0f; acs[f][n][v] = 0.0f; }
     };
 
     uint32_t lo = 0xffffffffu, hi = 0;   // (uniform) first and last tile with an infinite or NaN output
-    auto store = [&](auto secondc, uint32_t t) __attribute__((always_inline)) {
+    auto store = [&](auto secondc, uint32_t t, int nb) __attribute__((always_inline)) {   // (nb: the wave's block of 32 pixels)
         int m0;
         uint32_t P0;
         origin(t, m0, P0);
         m0 += wm * 64;
-        const uint32_t pix = P0 + (uint32_t)(wn * 32 + l32);
+        const uint32_t pix = P0 + (uint32_t)((wn * FN + nb) * 32 + l32);
         const bool live = pix < P.npix;
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, P.npix - 1u), P.d_howo);
         const uint32_t pin = min(pix, P.npix - 1u) - img * P.howo;
@@ -170,7 +190,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
             float v[16], big = 0.0f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                v[r] = (acc[f][r] + acs[f][r]) * (decltype(secondc)::value ? 1.0f / (kScale2 * kScale2) : 1.0f / (kScale * kScale));
+                v[r] = (acc[f][nb][r] + acs[f][nb][r]) * (decltype(secondc)::value ? 1.0f / (kScale2 * kScale2) : 1.0f / (kScale * kScale));
                 big = __builtin_elementwise_maximum(big, __builtin_fabsf(v[r]));
             }
             if constexpr (decltype(secondc)::value) {
@@ -183,7 +203,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
                     const float old = *to;
                     if (finite(old)) continue;
                     float val = v[r];
-                    if (settle(acc[f][r], old, val)) small |= 1u << r;
+                    if (settle(acc[f][nb][r], old, val)) small |= 1u << r;
                     else *to = val;
                 }
                 while (small) {
@@ -198,7 +218,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
                     // (the small products of an infinity are NaN: the sum of the h*h products stands for the output)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const float x = acc[f][r];
+                        const float x = acc[f][nb][r];
                         v[r] = finite(x) ? v[r] : x;
                     }
                     lo = min(lo, t);
@@ -227,7 +247,8 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
                 at ^= T::STAGE;
                 lds_barrier();
             }
-            store(secondc, t);
+#pragma unroll
+            for (int nb = 0; nb < FN; ++nb) store(secondc, t, nb);
         }
     };
     auto pass = [&](auto secondc) __attribute__((always_inline)) {
@@ -261,9 +282,10 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
     pass(std::true_type{});
 }
 
+template <int FN>
 static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu, hipStream_t st, LaunchPlan *plan)
 {
-    using T = Tile1x1;
+    using T = Tile1x1<FN>;
     const unsigned long long imgs = std::min<unsigned long long>((unsigned long long)T::TN / P.howo + 2, (unsigned long long)P.N);
     const unsigned long long larger = std::max((unsigned long long)P.Hi * P.Wi, (unsigned long long)P.Ho * P.rowlen);   // (both calls take the same kernel)
     if (imgs * P.Ci * larger * 4ull >= (1ull << 31) || (unsigned long long)P.K * 4ull * T::TM >= (1ull << 31)) return hipErrorNotSupported;
@@ -273,10 +295,10 @@ static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu
     P.ntiles = ((P.npix + T::TN - 1) / T::TN) * (uint32_t)P.tiles_m;
     const uint32_t grid = std::min(P.ntiles, (uint32_t)ncu);   // one workgroup per compute unit; it takes every grid-th tile
     if (plan) {
-        plan_record(plan, dim3(grid), 512, T::LDS, "conv_split_1x1_kernel<%s>", tf(implicit));
+        plan_record(plan, dim3(grid), 512, T::LDS, "conv_split_1x1_kernel<%d, %s>", FN, tf(implicit));
         return hipSuccess;
     }
-    void (*kern)(Split1x1Params) = implicit ? &conv_split_1x1_kernel<true> : &conv_split_1x1_kernel<false>;
+    void (*kern)(Split1x1Params) = implicit ? &conv_split_1x1_kernel<FN, true> : &conv_split_1x1_kernel<FN, false>;
     static KernelCache kc[2];
     const hipError_t e = allow_dynamic_lds(kc[implicit], reinterpret_cast<const void *>(kern), T::LDS, dev);
     if (e != hipSuccess) return e;
@@ -302,16 +324,24 @@ hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out,
     P.src_elems = (size_t)sh.N * sh.Ci * P.plane; P.out_elems = (size_t)sh.npix * sh.Co;
     P.d_wo = make_fastdiv((uint32_t)sh.Wo); P.d_howo = make_fastdiv(P.howo);
     if (sh.s > 65536) return hipErrorNotSupported;
-    // Which is faster, in us: this kernel's rounds of tiles (a last round that leaves units idle runs at a higher clock: half of the loss is
-    // made up) at 1.6 for a K block, the fp32 kernel's 64 channel tiles at 115 TFLOP/s.  Measured, fp32 / here: 256 -> 256 28x28 N=64 59.5 / 52.5,
-    // 14x14 N=32 12.8 / 15.9, N=128 34 / 29; 512 -> 512 14x14 N=32 37 / 27, N=128 112 / 95, 56x56 N=64 807 / 645; 1024 -> 256 14x14 N=32 39 / 46,
-    // N=128 119 / 92; 256 -> 256 56x56 N=64 216 / 186; 64 -> 256 56x56 N=64 68 / 63; 256 -> 64 56x56 N=8 12.7 / 16.3.  (Channel counts that the
-    // fp32 1x1 kernel does not take run the generic one there, at 50 TFLOP/s.)
-    const double r = (double)((P.npix + 127) / 128) * ((sh.Co + 127) / 128) / ncu;
-    const double here = 2.0 + 0.5 * (r + std::max(1.0, (double)(long long)(r + 0.999))) * (P.nkb * 1.6 + 2.0);
+    // Which is faster, in us: rounds of tiles (a last round that leaves units idle runs at a higher clock: half of the loss is made up) at 1.6 for a
+    // K block and 2 for a tile of 128 pixels, 2.55 and 6 of 256; the fp32 kernel's 64-channel tiles at 115 TFLOP/s.  Measured, fp32 / 128 / 256
+    // pixels: 256 -> 256 28x28 N=64 59.6 / 54-60 / 51.5, 14x14 N=32 12.8 / 15.9 / 22, N=128 34 / 28 / 27; 512 -> 512 14x14 N=32 37 / 26 / 39, N=64 62 /
+    // 48 / 43, N=128 112 / 94 / 82, 56x56 N=64 827 / 651 / 610; 1024 -> 256 14x14 N=32 39 / 46 / 69, N=128 118 / 89 / 76; 256 -> 256 56x56 N=64 218 / 184 /
+    // 186; 64 -> 256 56x56 N=64 68 / 63 / 78; 256 -> 64 56x56 N=8 12.7 / 16.3 / -.  (Channel counts that the fp32 1x1 kernel does not take run the
+    // generic one there, at 50 TFLOP/s.)
+    auto time = [&](int tn, double block, double tile) {
+        const double r = (double)((P.npix + tn - 1) / tn) * ((sh.Co + 127) / 128) / ncu;
+        return 2.0 + 0.5 * (r + (double)(long long)(r + 0.999)) * (P.nkb * block + tile);
+    };
+    const double t1 = time(128, 1.6, 2.0), t2 = time(256, 2.55, 6.0);
     const double fp32 = 3.0 + 2.0 * P.npix * ((sh.Co + 63) / 64 * 64.0) * sh.Ci / (sh.Co % 4 == 0 ? 115e6 : 50e6);
-    if (sh.Co <= 64 || here > 0.95 * fp32) return hipErrorNotSupported;
-    return launch_1x1_t(P, implicit, dev, ncu, st, plan);
+    if (sh.Co <= 64 || std::min(t1, t2) > 0.95 * fp32) return hipErrorNotSupported;
+    if (t2 < t1) {
+        e = launch_1x1_t<2>(P, implicit, dev, ncu, st, plan);
+        if (e != hipErrorNotSupported) return e;
+    }
+    return launch_1x1_t<1>(P, implicit, dev, ncu, st, plan);
 }
 
 }  // namespace im2win

@@ -12,22 +12,25 @@ from test_gpu_split_stem import _run
 
 pytestmark = pytest.mark.gpu
 
+# (shape, runs of 128 pixels per tile)
 SHAPES = [
-    (64, 256, 14, 15, 256, 1, 1, 1, 0),     # whole tiles of channels
-    (17, 520, 19, 21, 500, 1, 1, 1, 0),     # a last K block of one group, a last tile of 53 pixels
-    (300, 512, 7, 7, 130, 1, 1, 1, 0),      # two channels past a tile, planes of 49 pixels
-    (33, 512, 29, 28, 257, 1, 1, 2, 0),     # stride 2, one channel past a tile
-    (60, 504, 31, 40, 395, 1, 1, 3, 0),     # stride 3, 63 groups of channels
-    (7000, 256, 2, 2, 256, 1, 1, 1, 0),     # a tile spans 33 images
-    (64, 128, 30, 33, 129, 1, 1, 1, 0),     # several tiles per workgroup
+    ((64, 256, 14, 15, 256, 1, 1, 1, 0), 1),     # whole tiles of channels
+    ((17, 520, 19, 21, 500, 1, 1, 1, 0), 1),     # a last K block of one group, a last tile of 127 pixels
+    ((300, 512, 7, 7, 130, 1, 1, 1, 0), 1),      # two channels past a tile, planes of 49 pixels
+    ((33, 512, 29, 28, 257, 1, 1, 2, 0), 1),     # stride 2, one channel past a tile
+    ((9000, 256, 2, 2, 256, 1, 1, 1, 0), 1),     # a tile spans 32 images
+    ((60, 504, 31, 40, 395, 1, 1, 3, 0), 2),     # stride 3, 63 groups of channels
+    ((67, 384, 20, 19, 385, 1, 1, 1, 0), 2),     # one channel past a tile
+    ((21000, 256, 1, 1, 256, 1, 1, 1, 0), 2),    # a tile spans 256 images
+    ((64, 128, 30, 33, 129, 1, 1, 1, 0), 2),     # several tiles per workgroup
 ]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_both_calls(shape):
+@pytest.mark.parametrize("shape,runs", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_both_calls(shape, runs):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     for w in (False, True):
-        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == "conv_split_1x1_kernel<%s>" % ("true" if w else "false")
+        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == "conv_split_1x1_kernel<%d, %s>" % (runs, "true" if w else "false")
     I, F = workloads.random_layer_inputs(9950 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
     got, fp32 = _run(shape, I, F)
@@ -37,10 +40,11 @@ def test_both_calls(shape):
     assert l2 <= l2_32
 
 
+@pytest.mark.parametrize("shape", [SHAPES[2][0], SHAPES[8][0]], ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("ei,ef", [(-118, 4), (4, -124), (-140, 20), (105, 0), (-120, 120), (60, 60)])
-def test_no_operand_loses_bits(ei, ef):
+def test_no_operand_loses_bits(shape, ei, ef):
     """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
-    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape = SHAPES[6]
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     I, F = workloads.random_layer_inputs(9960, N, Ci, Hi, Wi, Co, Hf, Wf)
     I, F = torch.ldexp(I.double(), torch.tensor(ei)).float(), torch.ldexp(F.double(), torch.tensor(ef)).float()
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
@@ -48,9 +52,11 @@ def test_no_operand_loses_bits(ei, ef):
     assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
 
 
-def test_infinities_nan_and_the_ends_of_the_range():
+@pytest.mark.parametrize("shape", [(64, 256, 24, 31, 130, 1, 1, 1, 0), SHAPES[8][0]], ids=lambda s: "x".join(map(str, s)))
+def test_infinities_nan_and_the_ends_of_the_range(shape):
     """As in plain fp32 (the one-thread-per-output kernel), in both calls."""
-    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape = SHAPES[6]
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    assert im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"].startswith("conv_split_1x1_kernel<")
     I, F = workloads.random_layer_inputs(9970, N, Ci, Hi, Wi, Co, Hf, Wf)
     I.abs_()
     I[0, 2, 10, 10], I[1, 1, 0, Wi - 1], I[2, 0, Hi - 1, 0] = float("inf"), float("-inf"), float("nan")
