@@ -39,8 +39,8 @@ MEASURED_CONV_TRAFFIC_BYTES = {
     "cfg1_tiny_3x3": 209324,
     "cfg2_3x3_c64_56": 112791552,
     "cfg3_3x3_c256_14": 122461184,
-    "cfg4_7x7_s2_c3_224": 689076020,
-    "cfg5_11x11_s4_c3_227": 362789419}
+    "cfg4_7x7_s2_c3_224": 690790400,
+    "cfg5_11x11_s4_c3_227": 363622400}
 MEASURED_TRANSFORM_TRAFFIC_BYTES = {
     "cfg1_tiny_3x3": 63485,
     "cfg2_3x3_c64_56": 105594963,
