@@ -630,8 +630,9 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         // it runs groups of 32 channels too and is bound by their matrix work: N=128, 222x222 16 channels 278 / 330, here 167 / 194;
         // 96 channels 940 / 1086, 787 / 729; N=16 96 channels 122 / 136, 80 / 95; N=128 64x64 32 channels 23.2 / 27.7, 22.4 / 27.0.  Below that
         // number of pixels, or without 16-byte stores (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the faster.
-        const bool wide = P.howo % 4u == 0 && reinterpret_cast<uintptr_t>(out) % 16u == 0;
-        if (blocks % 2 == 0 || !wide || per_cu < 2048) return hipErrorNotSupported;
+        // (An output off 16-byte alignment takes the instance with 4-byte stores: the same sums in the same order.)
+        if (blocks % 2 == 0 || P.howo % 4u != 0 || per_cu < 2048) return hipErrorNotSupported;
+        if (reinterpret_cast<uintptr_t>(out) % 16u != 0) return launch_stem_t<3, 1, 1, 4>(P, implicit, st, plan);
         return launch_stem_t<3, 1, 1, 4, 4>(P, implicit, st, plan);
     }
     if (sh.Hf == 7) {

@@ -107,3 +107,19 @@ def test_infinities_nan_and_the_ends_of_the_range(shape):
     F[4, 1] = 2.0 ** 50                      # a sum past 2^96
     ref = _assert_like_basic(shape, I, F)
     assert torch.isnan(ref).any() and torch.isinf(ref).any()
+
+
+def test_an_output_off_16_byte_alignment():
+    """4-byte stores there, the same bits."""
+    shape = N, Ci, Hi, Wi, Co, Hf, Wf, s, p = SHAPES[17][0]
+    I, F = workloads.random_layer_inputs(9990, N, Ci, Hi, Wi, Co, Hf, Wf)
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    n = N * Co * Ho * Wo
+    buf = torch.full((2 * n + 9,), float("nan"), device="cuda")
+    outs = [buf[:n], buf[n + 4 - n % 4 + 1:][:n]]
+    assert outs[0].data_ptr() % 16 == 0 and outs[1].data_ptr() % 16 == 4
+    dW, dF = run_transform(I, Hf, Wf, s, p), F.cuda()
+    for o in outs:
+        im2win.conv2d_im2win_fwd(dW, dF, o, *shape)
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
