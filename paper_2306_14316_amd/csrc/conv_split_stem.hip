@@ -44,7 +44,7 @@ struct StemParams : SplitParams {
 };
 
 // HF x HF windows; R blocks of 32 rows, Q parts of K, PX runs of 32*B pixels: one wave each.
-// B = 4: a lane's four pixels are neighbours and their outputs leave in one store.
+// B = 4: a lane's four pixels are neighbours and their outputs leave in one store (of any 4-byte alignment).
 template <int HF_, int R_, int Q_, int PX_, int B_>
 struct Stem {
     static constexpr int HF = HF_, R = R_, Q = Q_, PX = PX_, B = B_;
@@ -629,10 +629,11 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         // 222x222 outputs 369, here 432; tiles of that length here 413, a group of 32 channels each 441).  With an odd number of blocks
         // it runs groups of 32 channels too and is bound by their matrix work: N=128, 222x222 16 channels 278 / 330, here 167 / 194;
         // 96 channels 940 / 1086, 787 / 729; N=16 96 channels 122 / 136, 80 / 95; N=128 64x64 32 channels 23.2 / 27.7, 22.4 / 27.0.  Below that
-        // number of pixels, or without 16-byte stores (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the faster.
-        // (An output off 16-byte alignment takes the instance with 4-byte stores: the same sums in the same order.)
+        // number of pixels, or where a lane's four pixels may lie in two planes (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the
+        // faster.  The alignment of the output chooses nothing: 16-byte stores need four bytes.  At 4 or 8 mod 16, fp32 kernel with 4-byte
+        // stores -> here: N=128 222x222 16 channels 214 / 248 -> 170 / 197, 96 channels 708 / 746 -> 806 / 738, N=16 96 channels 93 / 99 -> 84 / 99
+        // (4-byte stores here 234 / 232, 793 / 1020, 108 / 125).
         if (blocks % 2 == 0 || P.howo % 4u != 0 || per_cu < 2048) return hipErrorNotSupported;
-        if (reinterpret_cast<uintptr_t>(out) % 16u != 0) return launch_stem_t<3, 1, 1, 4>(P, implicit, st, plan);
         return launch_stem_t<3, 1, 1, 4, 4>(P, implicit, st, plan);
     }
     if (sh.Hf == 7) {

@@ -109,17 +109,26 @@ def test_infinities_nan_and_the_ends_of_the_range(shape):
     assert torch.isnan(ref).any() and torch.isinf(ref).any()
 
 
-def test_an_output_off_16_byte_alignment():
-    """4-byte stores there, the same bits."""
-    shape = N, Ci, Hi, Wi, Co, Hf, Wf, s, p = SHAPES[17][0]
-    I, F = workloads.random_layer_inputs(9990, N, Ci, Hi, Wi, Co, Hf, Wf)
+@pytest.mark.parametrize("shape", [SHAPES[17][0], SHAPES[18][0], (512, 3, 36, 36, 32, 3, 3, 1, 0), (300, 3, 42, 42, 16, 3, 3, 1, 1),
+                                   (150, 3, 64, 59, 67, 3, 3, 1, 1)], ids=lambda v: "x".join(map(str, v)))
+def test_an_output_off_16_byte_alignment(shape):
+    """The same kernel whatever the alignment, so the same bits: on images that the stem kernel takes and on narrower ones, where its tile
+    of 512 pixels has too many rows."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    assert _plan(shape).startswith("conv_split_stem_kernel<3, 1, 1, 4, 4" if Wo > 42 else "conv_mfma_shallow_kernel")
+    assert Ho * Wo % 4 == 0 and N * Ho * Wo >= 2048 * 256
+    I, F = workloads.random_layer_inputs(9990, N, Ci, Hi, Wi, Co, Hf, Wf)
     n = N * Co * Ho * Wo
-    buf = torch.full((2 * n + 9,), float("nan"), device="cuda")
-    outs = [buf[:n], buf[n + 4 - n % 4 + 1:][:n]]
-    assert outs[0].data_ptr() % 16 == 0 and outs[1].data_ptr() % 16 == 4
-    dW, dF = run_transform(I, Hf, Wf, s, p), F.cuda()
-    for o in outs:
-        im2win.conv2d_im2win_fwd(dW, dF, o, *shape)
-    torch.cuda.synchronize()
-    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+    dI, dW, dF = I.cuda(), run_transform(I, Hf, Wf, s, p), F.cuda()
+    buf = torch.full((3, n + 96), float("nan"), device="cuda")
+    outs = [buf[a, 32 + a:][:n] for a in range(3)]
+    assert (n + 96) % 4 == 0 and [o.data_ptr() % 16 for o in outs] == [0, 4, 8]
+    for call, source in ((im2win.conv2d_im2win_fwd, dW), (im2win.conv2d_im2win_implicit_fwd, dI)):
+        for o in outs:
+            call(source, dF, o, *shape)
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all()
+        for a, o in enumerate(outs):
+            assert torch.equal(outs[0].view(torch.int32), o.view(torch.int32)), a
+            assert torch.isnan(buf[a, :32 + a]).all() and torch.isnan(buf[a, 32 + a + n:]).all()   # nothing written outside
