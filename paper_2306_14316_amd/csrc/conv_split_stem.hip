@@ -575,7 +575,9 @@ static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, Lau
     const long long chunks = T::COLS ? cols + rows + 2 : (T::PAIRS ? cols / 2 + rows + 1 : (cols * HF) / 8 + rows + 1);   // (each row is rounded up; zeros; reads past the last)
     if (chunks > T::CAP) return hipErrorNotSupported;
     const unsigned long long imgs = std::min<unsigned long long>((unsigned long long)T::TN / P.howo + 2, (unsigned long long)P.N);
-    if (imgs * 3ull * P.plane * 4ull >= (1ull << 31)) return hipErrorNotSupported;
+    // (of the larger of both calls' sources, so that they take the same kernel and give the same bits)
+    const unsigned long long larger = std::max((unsigned long long)P.Hi * P.Wi, (unsigned long long)P.Ho * P.rowlen);
+    if (imgs * 3ull * larger * 4ull >= (1ull << 31)) return hipErrorNotSupported;
     if (((unsigned long long)P.Co * imgs + 64ull) * P.howo * 4ull >= kNoStore) return hipErrorNotSupported;
     constexpr uint32_t kPerCu = T::NW < 8 && 2 * T::LDS <= 160 * 1024 ? 2 : 1;
     P.ntiles = (P.npix + T::TN - 1) / T::TN;
@@ -604,9 +606,6 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     P.N = sh.N; P.Ci = sh.Ci; P.Ho = sh.Ho; P.Wo = sh.Wo; P.Co = sh.Co; P.s = sh.s; P.K = sh.K;
     P.Hi = sh.Hi; P.Wi = sh.Wi; P.p = sh.p; P.rowlen = sh.rowlen;
     P.plane = implicit ? (uint32_t)(sh.Hi * sh.Wi) : (uint32_t)((size_t)sh.Ho * sh.rowlen);
-    // (both calls ask for what either needs, so that they take the same kernel and give the same bits)
-    const unsigned long long larger = std::max((unsigned long long)sh.Hi * sh.Wi, (unsigned long long)sh.Ho * sh.rowlen);
-    if (larger * 12ull >= (1ull << 31) || (unsigned long long)sh.K * 4ull * 32ull >= (1ull << 31)) return hipErrorNotSupported;
     P.howo = (uint32_t)(sh.Ho * sh.Wo); P.npix = (uint32_t)sh.npix;
     P.src_elems = (size_t)sh.N * 3u * P.plane; P.out_elems = (size_t)sh.npix * sh.Co;
     const int cols = (sh.Wo - 1) * sh.s + sh.Wf;

@@ -100,6 +100,26 @@ def test_three_channel_layers():
     assert seen == tested, (seen ^ tested)
 
 
+def test_both_calls_of_large_layers():
+    """The im2win tensor is up to Hf times the input: where only one of them is within 32-bit offsets, both calls turn the layer away."""
+    rng, taken = random.Random(17), [0, 0]
+    shapes = [(4, 3, 7000, 7000, 96, 11, 11, 4, 0), (6, 3, 7120, 4184, 32, 7, 7, 2, 3), (2, 3, 6000, 6000, 16, 7, 7, 2, 0)]
+    while len(shapes) < 4000:
+        f, s = rng.choice([(3, 1), (3, 2), (7, 2), (11, 4), (1, 1), (1, 2)])
+        Hi, Wi, Ci = int(2 ** rng.uniform(9, 14)), int(2 ** rng.uniform(9, 14)), rng.choice([8, 64, 512]) if f == 1 else 3
+        shape = (rng.randint(1, 12), Ci, Hi, Wi, rng.choice([16, 65, 96, 128]), f, f, s, rng.randint(0, f // 2))
+        N, Ho, Wo = shape[0], (Hi + 2 * shape[8] - f) // s + 1, (Wi + 2 * shape[8] - f) // s + 1
+        if max(N * Ci * Ho * f * (Wi + 2 * shape[8]), N * Ci * Hi * Wi, N * shape[4] * Ho * Wo) < 2 ** 31:
+            shapes.append(shape)
+    for shape in shapes:
+        a, b = (im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] for w in (False, True))
+        assert a.startswith("conv_split") == b.startswith("conv_split"), (shape, a, b)
+        if a.startswith("conv_split"):
+            assert a.rsplit(", ", 1)[0] == b.rsplit(", ", 1)[0], (shape, a, b)
+        taken[a.startswith("conv_split")] += 1
+    assert min(taken) > 500, taken
+
+
 def test_one_by_one_layers():
     """The piece kernel of 1x1 layers: both calls take it or neither does, and it keeps to the layers it can index."""
     rng, taken = random.Random(13), 0
