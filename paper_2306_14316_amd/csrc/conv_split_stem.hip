@@ -637,9 +637,9 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     }
     if (sh.Hf == 7) {
         // Up to 64 channels and a tile or less per compute unit the fp32 kernel's shorter start is the faster (where it takes the layer:
-        // three output rows per 64 pixels): 64 channels, N=1 224x224 10.9 / 11.7, here 11.3 / 13.2; N=2 16.6 / 17.5, here 13.4 / 15.8;
+        // at most three output rows per 64 pixels): 64 channels, N=1 224x224 10.9 / 11.7, here 11.3 / 13.2; N=2 16.6 / 17.5, here 13.4 / 15.8;
         // 24 channels, N=1 11.2 / 10.5, 11.2 / 12.5; N=2 12.9 / 15.5, 11.4 / 12.6.
-        if (blocks <= 2 && per_cu < 64 && sh.Wo > 30) return hipErrorNotSupported;
+        if (blocks <= 2 && per_cu < 64 && sh.Wo > 31) return hipErrorNotSupported;
         if (blocks == 1) return launch_stem_t<7, 1, 2, 4>(P, implicit, st, plan);
         if (blocks == 3) return launch_stem_t<7, 3, 2, 2>(P, implicit, st, plan);
         // K in one wave or two: one cuts twice the filter words at its start, but nothing is exchanged.  64 channels, N=8 224x224
