@@ -1,5 +1,5 @@
 // bf16-piece convolution (see conv_split.h for the pieces and their precision) of layers with three input channels:
-// 7x7 at stride 2, 11x11 at strides that are multiples of four, 3x3.  K is 27 to 363, the pixels are many, and what
+// 7x7 at stride 2, 11x11 at stride 4, 3x3 at strides 1 and 2.  K is 27 to 363, the pixels are many, and what
 // the piece kernel of the deeper layers spends per tile on its filter stages, its start and its stores would cost more
 // than the MFMAs of such a tile.
 //
@@ -569,7 +569,7 @@ static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, Lau
     hipError_t e = device_cus(&dev, &ncu);
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
     if (e != hipSuccess) return e;
-    // chunks that a tile may need: P0 anywhere in a row, rows of Wo pixels
+    // chunks that a tile may need: P0 anywhere in a row, rows of Wo pixels (the strides here are below HF: most rows, most columns)
     const long long rows = std::min<long long>((T::TN + P.Wo - 2) / P.Wo + 1, T::TN);
     const long long cols = ((long long)T::TN - rows) * P.s + rows * HF;
     const long long chunks = T::COLS ? cols + rows + 2 : (T::PAIRS ? cols / 2 + rows + 1 : (cols * HF) / 8 + rows + 1);   // (each row is rounded up; zeros; reads past the last)
@@ -600,7 +600,7 @@ static hipError_t launch_stem_t(StemParams P, bool implicit, hipStream_t st, Lau
 hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st, bool implicit, LaunchPlan *plan)
 {
     if (sh.Ci != 3 || sh.Hf != sh.Wf) return hipErrorNotSupported;
-    if (!(sh.Hf == 3 && sh.s <= 2) && !(sh.Hf == 7 && sh.s == 2) && !(sh.Hf == 11 && sh.s % 4 == 0 && sh.s <= 64)) return hipErrorNotSupported;
+    if (!(sh.Hf == 3 && sh.s <= 2) && !(sh.Hf == 7 && sh.s == 2) && !(sh.Hf == 11 && sh.s == 4)) return hipErrorNotSupported;
     StemParams P = {};
     P.src = src; P.flt = flt; P.out = out;
     P.N = sh.N; P.Ci = sh.Ci; P.Ho = sh.Ho; P.Wo = sh.Wo; P.Co = sh.Co; P.s = sh.s; P.K = sh.K;

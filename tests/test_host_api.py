@@ -171,7 +171,7 @@ def test_launch_info_names_the_dispatch(lib):
     assert im2win.conv2d_im2win_fwd_launch_info(64, 252, 28, 28, 256, 1, 1, 1, 0)["kernel"] == "conv_mfma_pipe_kernel<1, 1>"
     assert im2win.conv2d_im2win_fwd_launch_info(4, 64, 28, 28, 64, 1, 7, 1, 0)["kernel"].startswith("conv_mfma_fast_kernel<1, 7, 8, 1, 4, 3, false,")
     assert im2win.conv2d_im2win_fwd_launch_info(4, 64, 28, 28, 64, 7, 1, 1, 3, workspace_free=True)["kernel"].startswith("conv_mfma_fast_kernel<7, 1, 8, 2, 4, 2, true,")
-    # three channels: the bf16-piece kernel at stride 2 (7x7) and at multiples of four (11x11), otherwise the fp32 matrix cores
+    # three channels: the bf16-piece kernel at stride 2 (7x7) and at stride 4 (11x11), otherwise the fp32 matrix cores
     assert im2win.conv2d_im2win_fwd_launch_info(128, 3, 227, 227, 96, 11, 11, 4, 0, workspace_free=True)["kernel"] == "conv_split_stem_kernel<11, 3, 4, 1, 1, true>"
     assert im2win.conv2d_im2win_fwd_launch_info(32, 3, 227, 227, 96, 11, 11, 2, 0)["kernel"] == "conv_mfma_shallow_kernel<11, 11, 3, 3, 2, 4, false, 1, false>"
     assert im2win.conv2d_im2win_fwd_launch_info(1, 3, 224, 224, 64, 7, 7, 2, 3)["kernel"] == "conv_mfma_shallow_kernel<7, 7, 3, 2, 1, 4, false, 1, false>"
