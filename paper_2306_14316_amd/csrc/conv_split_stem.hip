@@ -10,8 +10,8 @@
 //     an MFMA reads its pixel operand only;
 //   - a wave stages (cuts words into pieces and writes them to LDS) as well as multiplies.  Two or three waves share
 //     a SIMD; in each period half of them multiply first and stage then, the others the other way round, so that the
-//     vector ALU works for one while the matrix pipe works for the other.  Pixel stages are double-buffered: one
-//     barrier per tile;
+//     vector ALU works for one while the matrix pipe works for the other (3x3 with one block of channels: workgroups
+//     of four waves, one per SIMD, and two workgroups to a unit).  Pixel stages are double-buffered: one barrier per tile;
 //   - where K does not fit a wave's registers, Q waves share a 32x32 block: each takes its part of K and hands the
 //     others the sums of the channels that they store, through LDS, a period later.
 //
@@ -109,9 +109,10 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
     lds_byte *const L = (lds_byte *)smem;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (waves 4 apart share a SIMD: the parts of K of one block lie on different ones, and so do the halves of the order)
+    // (waves 4 apart share a SIMD: the parts of K of one block lie on different ones, and so do the halves of the order.
+    // Four waves: one to a SIMD, all in one order, and the waves of the unit's second workgroup beside them)
     const int ks = wave % Q, px = (wave / Q) % T::PX, rb = wave / (Q * T::PX);
-    const bool late = (wave >> 2) & 1;
+    const bool late = T::NW > 4 && ((wave >> 2) & 1);
     const int m0 = ((int)blockIdx.y * T::R + rb) * 32;   // the wave's first output channel
     const uint32_t gx = gridDim.x;
 
