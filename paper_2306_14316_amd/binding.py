@@ -124,23 +124,29 @@ def im2col_footprint_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) -> int:
 
 # The host side of a call is what a small layer waits for (a 3x3 layer on one 32x32 image, two calls: 20 us, of which the two
 # launches take 7.5), so a call asks the library for its sizes once per layer (shapes that it refuses are not kept), names no
-# module and wraps no pointer or stream on its way: 20 -> 11.7 us.
-@functools.lru_cache(maxsize=1024)
-def _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad) -> int:
-    return im2win_workspace_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) // 4
-
-
-@functools.lru_cache(maxsize=1024)
-def _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad) -> int:
+# module and wraps no pointer or stream on its way: 20 -> 12 us.
+# Kept for plain ints only: what else passes for one (a 0-dim tensor) would be told apart by identity though its value may change,
+# or equals an int without being accepted (a float).
+def _ask_elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad):
+    window = im2win_workspace_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) // 4
     Ho, Wo = im2win_out_shape(Hi, Wi, Hf, Wf, stride, pad)
-    return N * Co * Ho * Wo
+    return window, N * Co * Ho * Wo
+
+
+_kept_elems = functools.lru_cache(maxsize=1024)(_ask_elems)
+
+
+def _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad):
+    """Elements of the im2win tensor and of the output."""
+    ints = type(N) is type(Ci) is type(Hi) is type(Wi) is type(Co) is type(Hf) is type(Wf) is type(stride) is type(pad) is int
+    return (_kept_elems if ints else _ask_elems)(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
 
 
 def layer_sizes(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad) -> dict:
     """Ho, Wo and the element counts of the im2win tensor and the output, as the library derives them."""
     Ho, Wo = im2win_out_shape(Hi, Wi, Hf, Wf, stride, pad)
-    return {"Ho": Ho, "Wo": Wo, "window_elems": _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad),
-            "output_elems": N * Co * Ho * Wo}
+    window, output = _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
+    return {"Ho": Ho, "Wo": Wo, "window_elems": window, "output_elems": output}
 
 
 _torch = None
@@ -174,15 +180,16 @@ def _stream(stream):
 def im2win_transform(input, window, N, Ci, Hi, Wi, Hf, Wf, stride, pad, stream=None):
     """window <- im2win(input); both are device tensors owned by the caller."""
     a = _dev_ptr(input, "input", N * Ci * Hi * Wi)
-    w = _dev_ptr(window, "window", _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad))
+    w = _dev_ptr(window, "window", _elems(N, Ci, Hi, Wi, 1, Hf, Wf, stride, pad)[0])
     _check(load_library().im2win_transform(a, w, N, Ci, Hi, Wi, Hf, Wf, stride, pad, _stream(stream)),
            "im2win_transform")
 
 
 def _conv(fn_name, window, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, stream):
-    w = _dev_ptr(window, "window", _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad))
+    window_elems, output_elems = _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
+    w = _dev_ptr(window, "window", window_elems)
     f = _dev_ptr(filter, "filter", Co * Ci * Hf * Wf)
-    o = _dev_ptr(output, "output", _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad))
+    o = _dev_ptr(output, "output", output_elems)
     fn = getattr(load_library(), fn_name)
     _check(fn(w, f, o, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, _stream(stream)), fn_name)
 
@@ -205,9 +212,10 @@ VARIANT_VALU_MICROKERNEL, VARIANT_SCALAR_LOADS = 4, 5
 def conv2d_im2win_fwd_variant(window, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, variant,
                               stream=None):
     """output <- the convolution computed by one of the ablation variants (VARIANT_*)."""
-    w = _dev_ptr(window, "window", _window_elems(N, Ci, Hi, Wi, Hf, Wf, stride, pad))
+    window_elems, output_elems = _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
+    w = _dev_ptr(window, "window", window_elems)
     f = _dev_ptr(filter, "filter", Co * Ci * Hf * Wf)
-    o = _dev_ptr(output, "output", _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad))
+    o = _dev_ptr(output, "output", output_elems)
     _check(load_library().conv2d_im2win_fwd_variant(w, f, o, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad,
                                                      int(variant), _stream(stream)),
            "conv2d_im2win_fwd_variant")
@@ -217,7 +225,7 @@ def conv2d_im2win_implicit_fwd(input, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf,
     """output <- the im2win convolution straight from the NCHW input (no workspace)."""
     a = _dev_ptr(input, "input", N * Ci * Hi * Wi)
     f = _dev_ptr(filter, "filter", Co * Ci * Hf * Wf)
-    o = _dev_ptr(output, "output", _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad))
+    o = _dev_ptr(output, "output", _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)[1])
     _check(load_library().conv2d_im2win_implicit_fwd(a, f, o, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad,
                                                       _stream(stream)),
            "conv2d_im2win_implicit_fwd")
@@ -227,7 +235,7 @@ def conv2d_direct_fwd(input, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, 
     """output <- the direct convolution (baseline): one thread per output, no workspace."""
     a = _dev_ptr(input, "input", N * Ci * Hi * Wi)
     f = _dev_ptr(filter, "filter", Co * Ci * Hf * Wf)
-    o = _dev_ptr(output, "output", _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad))
+    o = _dev_ptr(output, "output", _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)[1])
     _check(load_library().conv2d_direct_fwd(a, f, o, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, _stream(stream)),
            "conv2d_direct_fwd")
 
@@ -244,7 +252,7 @@ def conv2d_im2col_fwd(col, filter, output, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pa
     """output <- GEMM of the im2col matrix with the filter matrix (baseline)."""
     c = _dev_ptr(col, "col", im2col_footprint_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) // 4)
     f = _dev_ptr(filter, "filter", Co * Ci * Hf * Wf)
-    o = _dev_ptr(output, "output", _out_elems(N, Co, Hi, Wi, Hf, Wf, stride, pad))
+    o = _dev_ptr(output, "output", _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)[1])
     _check(load_library().conv2d_im2col_fwd(c, f, o, N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad, _stream(stream)),
            "conv2d_im2col_fwd")
 

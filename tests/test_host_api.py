@@ -197,6 +197,21 @@ def test_launch_info_names_the_dispatch(lib):
     assert lib.im2win_transform_launch_info(1, 1, 4, 4, 2, 2, 1, 0, None) == -1
 
 
+def test_sizes_kept_from_earlier_calls_are_of_plain_ints_only(lib):
+    """A number that can change or that is no integer is asked about again on each call: a size kept for it would let a call past
+    the check of its buffers."""
+    import torch
+    n = torch.tensor(1)
+    first = im2win.layer_sizes(n, 3, 8, 8, 5, 3, 3, 1, 0)
+    n += 1
+    for N in (n, 2):
+        again = im2win.layer_sizes(N, 3, 8, 8, 5, 3, 3, 1, 0)
+        assert again["window_elems"] == 2 * first["window_elems"] and int(again["output_elems"]) == 2 * 5 * 6 * 6
+    for bad in (2.0, [2]):
+        with pytest.raises(ctypes.ArgumentError):
+            im2win.layer_sizes(bad, 3, 8, 8, 5, 3, 3, 1, 0)
+
+
 def test_probe_arguments_are_validated(lib):
     one = ctypes.c_void_p(16)
     fl = ctypes.c_double()
