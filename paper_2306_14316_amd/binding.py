@@ -149,12 +149,13 @@ def layer_sizes(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad) -> dict:
     return {"Ho": Ho, "Wo": Wo, "window_elems": window, "output_elems": output}
 
 
-_torch = None
+_torch = _raw_stream = None
 
 
 def _load_torch():
-    global _torch
+    global _torch, _raw_stream
     import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # (not public, so it may be missing)
     _torch = torch
     return torch
 
@@ -173,7 +174,7 @@ def _dev_ptr(t, name: str, numel: int):
 def _stream(stream):
     if stream is None:   # torch's current stream on the current device
         torch = _torch or _load_torch()
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 

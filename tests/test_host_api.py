@@ -212,6 +212,18 @@ def test_sizes_kept_from_earlier_calls_are_of_plain_ints_only(lib):
             im2win.layer_sizes(bad, 3, 8, 8, 5, 3, 3, 1, 0)
 
 
+def test_the_current_stream_needs_no_private_call(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=1234))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    for name in ("_torch", "_raw_stream"):   # as at the first call; put back behind the test
+        monkeypatch.setattr(binding, name, None, raising=False)
+    assert binding._stream(None) == 1234
+    assert binding._stream(SimpleNamespace(cuda_stream=77)) == 77
+
+
 def test_probe_arguments_are_validated(lib):
     one = ctypes.c_void_p(16)
     fl = ctypes.c_double()
