@@ -628,12 +628,16 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         // At stride 1 the output stream is the bound, and with 64 channels the fp32 kernel, whose tiles are half as long, keeps it fuller (N=128
         // 222x222 outputs 369, here 432; tiles of that length here 413, a group of 32 channels each 441).  With an odd number of blocks
         // it runs groups of 32 channels too and is bound by their matrix work: N=128, 222x222 16 channels 278 / 330, here 167 / 194;
-        // 96 channels 940 / 1086, 787 / 729; N=16 96 channels 122 / 136, 80 / 95; N=128 64x64 32 channels 23.2 / 27.7, 22.4 / 27.0.  Below that
-        // number of pixels, or where a lane's four pixels may lie in two planes (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the
-        // faster.  The alignment of the output chooses nothing: 16-byte stores need four bytes.  At 4 or 8 mod 16, fp32 kernel with 4-byte
+        // 96 channels 940 / 1086, 787 / 729; N=16 96 channels 122 / 136, 80 / 95.  Below 2048 pixels per unit, or where a lane's four pixels may
+        // lie in two planes (N=128 223x223 96 channels 714 / 755, here 959 / 867), it is the faster; with 32 channels, none of them missing, up to
+        // 3072, where it goes over to tiles of 256 pixels (N=201 54x54 24.8 / 29.3, here 28.3 / 31.5; N=109 74x74 25.2 / 30.2, 28.7 / 31.9; 3069
+        // pixels per unit 1.01 / 1.14 times as fast here, 3600 1.3; 16 channels, 2048 to 3072 1.1 to 1.4).  (Even counts from four blocks run
+        // groups of 32 there as well: N=128, 222x222 128 channels 1220 / 1361, here 1019 / 936; N=16 153 / 169, 99 / 119; but 836 / 966, 1043 / 902
+        // off alignment.  Not taken here.)
+        // The alignment of the output chooses nothing: 16-byte stores need four bytes.  At 4 or 8 mod 16, fp32 kernel with 4-byte
         // stores -> here: N=128 222x222 16 channels 214 / 248 -> 170 / 197, 96 channels 708 / 746 -> 806 / 738, N=16 96 channels 93 / 99 -> 84 / 99
         // (4-byte stores here 234 / 232, 793 / 1020, 108 / 125).
-        if (blocks % 2 == 0 || P.howo % 4u != 0 || per_cu < 2048) return hipErrorNotSupported;
+        if (blocks % 2 == 0 || P.howo % 4u != 0 || per_cu < (sh.Co == 32 ? 3072u : 2048u)) return hipErrorNotSupported;
         return launch_stem_t<3, 1, 1, 4, 4>(P, implicit, st, plan);
     }
     if (sh.Hf == 7) {

@@ -104,6 +104,21 @@ def test_three_channel_layers():
     assert seen == tested, (seen ^ tested)
 
 
+# (layer, the kernel its plan starts with): both sides of the lines between the kernels of three-channel layers, on 256 units
+LINES = [
+    ((201, 3, 54, 54, 32, 3, 3, 1, 1), "conv_mfma_shallow_kernel<3"),          # 2290 pixels per unit, no channel missing
+    ((300, 3, 54, 54, 32, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
+    ((201, 3, 54, 54, 31, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
+    ((201, 3, 54, 54, 96, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
+]
+
+
+@pytest.mark.parametrize("shape,kernel", LINES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_lines_between_the_kernels_of_three_channel_layers(shape, kernel):
+    for w in (False, True):
+        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"].startswith(kernel)
+
+
 def test_both_calls_of_large_layers():
     """The im2win tensor is up to Hf times the input: where only one of them is within 32-bit offsets, both calls turn the layer away."""
     rng, taken = random.Random(17), [0, 0]
