@@ -620,9 +620,18 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     // Which instance: us, two calls / workspace-free (convolution only).
     if (sh.Hf == 3) {
         // Stride 2: 224x224, padding 1, N=8 16 channels 13.0 / 13.7, here 11.3 / 12.2; 64 channels 15.7 / 16.3, 12.5 / 15.2; N=64 16 channels
-        // 74 / 75, 33 / 42; 64 channels 88 / 85, 50 / 57; 96 channels 198 / 180, 95 / 132.
+        // 74 / 75, 33 / 42; 64 channels 88 / 85, 50 / 57; 96 channels 198 / 180, 91 / 128.  Small layers (500 of all sizes): two calls gain 6 to
+        // 40 %; workspace-free, where a workgroup has one or two tiles, up to 7 % is lost (N=8 80x80 128 channels 10.7 / 11.3) and 12 % gained.
         if (sh.s == 2) {
-            if (blocks % 2) return launch_stem_t<3, 1, 1, 4>(P, implicit, st, plan);
+            // An odd count of blocks, three or more: single blocks stage each pixel once per block, pairs leave one block empty.  Pairs where a
+            // workgroup has few tiles (in pairs / single: 96 channels, N=1 313x313 9.1 / 10.8, 10.5 / 13.0; 160 channels, N=14 158x127 18.1 / 21.8,
+            // 19.7 / 24.6), but not where single ones have a unit each (N=8 51x51 96 channels 6.4 / 7.8, 5.8 / 7.4) or save a second round (N=18 66x66
+            // 9.1 / 10.9, 8.2 / 10.2); behind four rounds neither always wins (N=35 191x191 96 channels 40 / 49, 37 / 48; N=57 120x506 127 / 156, 141 / 166).
+            const uint32_t tiles = (P.npix + 127) / 128, units = (uint32_t)ncu;
+            auto rounds = [&](uint32_t slots, uint32_t groups) { const uint32_t gx = std::max(1u, slots / groups >= 8 ? slots / groups & ~7u : slots / groups); return (tiles + gx - 1) / gx; };
+            const uint32_t r1 = rounds(2 * units, (uint32_t)blocks), r2 = rounds(units, (uint32_t)(blocks + 1) / 2);
+            const bool single = blocks % 2 && (blocks == 1 || (unsigned long long)tiles * blocks <= units || (r1 == 1 && r2 > 1) || r1 > 4);
+            if (single) return launch_stem_t<3, 1, 1, 4>(P, implicit, st, plan);
             return launch_stem_t<3, 2, 1, 4>(P, implicit, st, plan);
         }
         // At stride 1 the output stream is the bound, and with 64 channels the fp32 kernel, whose tiles are half as long, keeps it fuller (N=128

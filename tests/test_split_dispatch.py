@@ -110,6 +110,12 @@ LINES = [
     ((300, 3, 54, 54, 32, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
     ((201, 3, 54, 54, 31, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
     ((201, 3, 54, 54, 96, 3, 3, 1, 1), "conv_split_stem_kernel<3, 1, 1, 4, 4"),
+    ((8, 3, 51, 51, 96, 3, 3, 2, 1), "conv_split_stem_kernel<3, 1, 1, 4, 1"),     # 43 tiles of three blocks
+    ((3, 3, 129, 129, 96, 3, 3, 2, 1), "conv_split_stem_kernel<3, 2, 1, 4, 1"),   # 100: pairs have a unit each
+    ((18, 3, 66, 66, 96, 3, 3, 2, 1), "conv_split_stem_kernel<3, 1, 1, 4, 1"),    # 154: single ones run in one round
+    ((1, 3, 313, 313, 160, 3, 3, 2, 0), "conv_split_stem_kernel<3, 2, 1, 4, 1"),
+    ((35, 3, 191, 191, 96, 3, 3, 2, 0), "conv_split_stem_kernel<3, 1, 1, 4, 1"),  # fifteen rounds
+    ((35, 3, 191, 191, 97, 3, 3, 2, 0), "conv_split_stem_kernel<3, 2, 1, 4, 1"),
 ]
 
 
