@@ -654,6 +654,7 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         // at most three output rows per 64 pixels): 64 channels, N=1 224x224 10.9 / 11.7, here 11.3 / 13.2; N=2 16.6 / 17.5, here 13.4 / 15.8;
         // 24 channels, N=1 11.2 / 10.5, 11.2 / 12.5; N=2 12.9 / 15.5, 11.4 / 12.6.
         if (blocks <= 2 && per_cu < 64 && sh.Wo > 31) return hipErrorNotSupported;
+        // Otherwise at any size (500 layers of all sizes: 1.08 to 2.9 times as fast in two calls, 1.02 to 2.9 workspace-free).
         if (blocks == 1) return launch_stem_t<7, 1, 2, 4>(P, implicit, st, plan);
         if (blocks == 3) return launch_stem_t<7, 3, 2, 2>(P, implicit, st, plan);
         // K in one wave or two: one cuts twice the filter words at its start, but nothing is exchanged.  64 channels, N=8 224x224
@@ -661,9 +662,13 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         if (per_cu < 768) return launch_stem_t<7, 2, 2, 2>(P, implicit, st, plan);
         return launch_stem_t<7, 2, 1, 4>(P, implicit, st, plan);
     }
-    if (blocks == 1 && per_cu >= 128) {
-        // 24 channels, N=8 227x227 15.1 / 25.8, with half of the tile empty (below) 16.3 / 20.4; N=32 160x160 20.6 / 31.3, 26.7 / 31.1;
-        // N=128 227x227 72 / 131, 132 / 155; fp32 kernel 18.0 / 21.9, 25.2 / 32.2, 100 / 136.  (Not for narrow images.)
+    // Two or more blocks: at any size (224 layers of all sizes: 1.37 to 3.2 times as fast as on the fp32 kernel in two calls, 1.19 to 2.6
+    // workspace-free).  One block: its own instance from four rounds of the other's tiles, whose one half is empty then; behind five
+    // with a full block, whose stores cost it more.
+    if (blocks == 1 && per_cu >= (sh.Co > 24 ? 161u : 128u)) {
+        // 24 channels, N=8 227x227 15.1 / 25.8, with half of the tile empty (below) 16.3 / 20.4; N=7 273x273 16.9 / 26.6, 17.7 / 24.4; N=16 255x255
+        // 21.0 / 31.2, 24.8 / 33.5; N=128 227x227 72 / 131, 132 / 155; fp32 kernel 18.0 / 21.9, 20.7 / 26.0, 25.0 / 31.9, 100 / 136.  8 channels, N=28
+        // 155x155 14.5 / 23.6, 16.5 / 23.3; fp32 17.8 / 23.2.  32 channels, N=9 261x261 19.8 / 28.8, 19.4 / 26.1; fp32 22.2 / 27.1.  (Not for narrow images.)
         const hipError_t e = launch_stem_t<11, 1, 4, 2>(P, implicit, st, plan);
         if (e != hipErrorNotSupported) return e;
     }

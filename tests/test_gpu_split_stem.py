@@ -23,7 +23,7 @@ SHAPES = [
     ((33, 3, 31, 64, 96, 7, 7, 2, 3), (3, 2, 2, 1)),
     ((1, 3, 7, 47, 70, 7, 7, 2, 0), (3, 2, 2, 1)),       # one row, one tile
     ((16, 3, 227, 225, 20, 11, 11, 4, 0), (1, 4, 2, 1)),
-    ((300, 3, 11, 530, 31, 11, 11, 4, 0), (1, 4, 2, 1)),  # one row per image: a tile may span two images
+    ((330, 3, 11, 530, 31, 11, 11, 4, 0), (1, 4, 2, 1)),  # one row per image: a tile may span two images
     ((1, 3, 60, 230, 5, 11, 11, 4, 5), (2, 4, 1, 1)),
     ((55, 3, 39, 40, 64, 11, 11, 4, 5), (2, 4, 1, 1)),   # eight pixels a row
     ((9, 3, 130, 127, 96, 11, 11, 4, 2), (3, 4, 1, 1)),

@@ -116,6 +116,9 @@ LINES = [
     ((1, 3, 313, 313, 160, 3, 3, 2, 0), "conv_split_stem_kernel<3, 2, 1, 4, 1"),
     ((35, 3, 191, 191, 96, 3, 3, 2, 0), "conv_split_stem_kernel<3, 1, 1, 4, 1"),  # fifteen rounds
     ((35, 3, 191, 191, 97, 3, 3, 2, 0), "conv_split_stem_kernel<3, 2, 1, 4, 1"),
+    ((9, 3, 261, 261, 32, 11, 11, 4, 5), "conv_split_stem_kernel<11, 2, 4, 1, 1"),   # five rounds
+    ((9, 3, 261, 261, 24, 11, 11, 4, 5), "conv_split_stem_kernel<11, 1, 4, 2, 1"),
+    ((22, 3, 191, 191, 32, 11, 11, 4, 0), "conv_split_stem_kernel<11, 1, 4, 2, 1"),
 ]
 
 
