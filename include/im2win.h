@@ -83,7 +83,7 @@ im2win_status im2win_transform(const float *input_dev, float *window_dev,
  * that is faster, on the bf16 matrix cores with every operand cut into three bf16
  * pieces that hold its 24 bits, whatever its magnitude, and fp32 accumulation (smaller
  * error; where a sum is infinite, NaN or passes 2^96 the tiles are computed a second
- * time, up to 2.5 times the time in all).  Of the words of the im2win tensor that repeat
+ * time, up to 2.6 times the time in all).  Of the words of the im2win tensor that repeat
  * an input word one is read, the same on every call: as im2win_transform writes them they
  * are equal.
  * Hi, Wi and pad are those given to im2win_transform, so that both calls derive

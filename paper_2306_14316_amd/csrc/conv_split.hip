@@ -49,7 +49,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     const unsigned long long larger = std::max((unsigned long long)sh.Hi * sh.Wi, (unsigned long long)sh.Ho * sh.rowlen);
     if ((unsigned long long)best_img * sh.Ci * larger * 4ull >= (1ull << 31)) return false;
     if ((unsigned long long)sh.K * 4ull * TM >= (1ull << 31)) return false;
-    if (((unsigned long long)sh.Co * best_img + 64ull) * (unsigned long long)sh.Ho * sh.Wo * 4ull >= (1ull << 32)) return false;
+    if (((unsigned long long)sh.Co * best_img + 64ull) * (unsigned long long)sh.Ho * sh.Wo * 4ull >= kNoStore) return false;
     const long long LF = (long long)(sh.Ho - 1) * sh.s + HF;
     if (LF > INT32_MAX / 2) return false;
     Q.src = P.win; Q.flt = P.flt; Q.out = P.out;

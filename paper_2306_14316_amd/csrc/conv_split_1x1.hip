@@ -31,8 +31,6 @@ struct Split1x1Params : SplitParams {
     FastDiv d_wo, d_howo;
 };
 
-constexpr uint32_t kNoStore1 = 0xffffff00u;   // no output descriptor here covers it
-
 // Tiles of 128 channels x 128*FN pixels; a wave owns 64 x 32*FN.
 template <int FN>
 struct Tile1x1 {
@@ -70,19 +68,15 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
     uint32_t ft = 0, fvo = 0, bvo[FN];     // tile and offsets of the block being fetched
     int fkb = 0;
     __amdgpu_buffer_rsrc_t rf, rw;
-    auto desc = [](const float *base, size_t elems) __attribute__((always_inline)) {
-        const size_t left = elems * 4u;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, left < 0x7fffffffull ? left : 0x7fffffffull, 0x00020000);
-    };
     auto aim = [&](uint32_t t) __attribute__((always_inline)) {
         int m0;
         uint32_t P0;
         origin(t, m0, P0);
-        rf = desc(P.flt + (size_t)m0 * P.K, ((size_t)P.Co - (size_t)m0) * P.K);
+        rf = operand_desc(P.flt + (size_t)m0 * P.K, ((size_t)P.Co - (size_t)m0) * P.K);
         fvo = m0 + ar < P.Co ? (uint32_t)(ar * P.K + ag * 8) * 4u : kNoWord;
         const uint32_t img0 = fdiv(P0, P.d_howo);
         const size_t base = (size_t)img0 * P.Ci * P.plane;
-        rw = desc(P.src + base, P.src_elems - base);
+        rw = operand_desc(P.src + base, P.src_elems - base);
         const uint32_t px = min(P0 + (uint32_t)bp, P.npix - 1u), img = fdiv(px, P.d_howo), pin = px - img * P.howo;
         const uint32_t m = fdiv(pin, P.d_wo), n = pin - m * (uint32_t)P.Wo;
         const uint32_t at = (img - img0) * (uint32_t)P.Ci * P.plane + m * P.rowstep + n * (uint32_t)P.s;
@@ -179,11 +173,9 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
         const bool live = pix < P.npix;
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, P.npix - 1u), P.d_howo);
         const uint32_t pin = min(pix, P.npix - 1u) - img * P.howo;
-        const size_t obase = ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo;
-        const size_t left = (P.out_elems - obase) * 4u;
-        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(P.out + obase, 0, left < kNoStore1 ? left : kNoStore1, 0x00020000);
+        const __amdgpu_buffer_rsrc_t ro = output_desc(P.out, P.out_elems, ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo);
         const uint32_t howo4 = P.howo * 4u;
-        const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)(4 * h) * P.howo) * 4u : kNoStore1;
+        const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)(4 * h) * P.howo) * 4u : kNoStore;
         const int room = P.Co - m0 - 4 * h;
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
@@ -194,25 +186,8 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
                 big = __builtin_elementwise_maximum(big, __builtin_fabsf(v[r]));
             }
             if constexpr (decltype(secondc)::value) {
-                uint32_t small = 0;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dj = 32 * f + 8 * (r >> 2) + (r & 3);
-                    if (!live || dj >= room) continue;
-                    float *const to = P.out + ((size_t)img * P.Co + (size_t)(m0 + 4 * h + dj)) * P.howo + pin;
-                    const float old = *to;
-                    if (finite(old)) continue;
-                    float val = v[r];
-                    if (settle(acc[f][nb][r], old, val)) small |= 1u << r;
-                    else *to = val;
-                }
-                while (small) {
-                    const int r = __builtin_ctz(small);
-                    small &= small - 1;
-                    const int j = m0 + 4 * h + 32 * f + 8 * (r >> 2) + (r & 3);
-                    const int m = (int)fdiv(pin, P.d_wo), n = (int)pin - m * P.Wo;
-                    P.out[((size_t)img * P.Co + (size_t)j) * P.howo + pin] = dot_fp32<1, 1, IMP>(P, img, j, m, n);
-                }
+                settle_outputs<1, 1, IMP, 16, 1>(P, ro, voff + (uint32_t)(32 * f) * howo4, live, room - 32 * f, img, m0 + 4 * h + 32 * f, pin,
+                                                 [&](int, int r, float &a) __attribute__((always_inline)) { a = acc[f][nb][r]; return v[r]; });
             } else {
                 if (__builtin_amdgcn_ballot_w64(live && !finite(big))) {
                     // (the small products of an infinity are NaN: the sum of the h*h products stands for the output)
@@ -227,7 +202,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int dj = 32 * f + 8 * (r >> 2) + (r & 3);
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[r]), ro, dj < room ? voff : kNoStore1, (uint32_t)dj * howo4, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[r]), ro, dj < room ? voff : kNoStore, (uint32_t)dj * howo4, 0);
                 }
             }
         }
@@ -289,7 +264,7 @@ static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu
     const unsigned long long imgs = std::min<unsigned long long>((unsigned long long)T::TN / P.howo + 2, (unsigned long long)P.N);
     const unsigned long long larger = std::max((unsigned long long)P.Hi * P.Wi, (unsigned long long)P.Ho * P.rowlen);   // (both calls take the same kernel)
     if (imgs * P.Ci * larger * 4ull >= (1ull << 31) || (unsigned long long)P.K * 4ull * T::TM >= (1ull << 31)) return hipErrorNotSupported;
-    if (((unsigned long long)P.Co * imgs + 128ull) * P.howo * 4ull >= kNoStore1) return hipErrorNotSupported;
+    if (((unsigned long long)P.Co * imgs + 128ull) * P.howo * 4ull >= kNoStore) return hipErrorNotSupported;
     P.tiles_m = (P.Co + T::TM - 1) / T::TM;
     P.d_tm = make_fastdiv((uint32_t)P.tiles_m);
     P.ntiles = ((P.npix + T::TN - 1) / T::TN) * (uint32_t)P.tiles_m;

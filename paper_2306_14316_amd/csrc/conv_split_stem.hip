@@ -87,9 +87,6 @@ __device__ __forceinline__ void stem_for(F &&f, std::integer_sequence<int, I...>
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-// A byte offset that no output descriptor of this kernel covers: their sizes are capped at it, and the launcher keeps real offsets below.
-constexpr uint32_t kNoStore = 0xffffff00u;
-
 // The largest magnitude of a wave's sums, NaN if there is one.
 template <class V>
 __device__ __forceinline__ float largest(const V &v)
@@ -247,8 +244,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         constexpr int q = decltype(qc)::value;
         const int row = m0 + l32;
         const size_t base = (size_t)min(m0, P.Co - 1) * P.K;   // (uniform)
-        const size_t left = ((size_t)P.Co * P.K - base) * 4u;
-        const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(P.flt + base), 0, left < 0x7fffffffull ? left : 0x7fffffffull, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rf = operand_desc(P.flt + base, (size_t)P.Co * P.K - base);
         stem_for([&](auto ic) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value, s = q * SPQ + i;
             float w[8];
@@ -364,42 +360,38 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
 
     // ---- the wave's share of a block's outputs: registers OWN*ks .. of the sums, all of them scaled
     uint32_t lo = 0xffffffffu, hi = 0;   // (uniform) first and last tile with an infinite or NaN output
-    const int j0 = (T::OWN == 16 ? 0 : ks * (T::OWN / 4) * 8) + 4 * h;   // the lane's first channel of the block
-    const int room = P.Co - m0 - j0;
+    // The lane's number again, worked out at each use: what depends on it alone would be kept through the loops, and a three-block workgroup
+    // (168 registers to a wave) then reloads filter words in them (11x11, N=128 227x227 96 channels 176 -> 187 us).  11x11 in eight waves has
+    // the registers (64 channels 132, so 137).
+    auto fresh_lane = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        if constexpr (Q < 4 || T::NW > 8) asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto first_channel = [&]() __attribute__((always_inline)) { return (T::OWN == 16 ? 0 : ks * (T::OWN / 4) * 8) + (fresh_lane() >> 5) * 4; };   // of the block
+    auto settled = [&](auto bc, const __amdgpu_buffer_rsrc_t &ro, uint32_t voff, bool live, int j0, uint32_t img, uint32_t pin, auto &&sum) __attribute__((always_inline)) {
+        settle_outputs<HF, HF, IMP, T::OWN, decltype(bc)::value>(P, ro, voff, live, P.Co - m0 - j0, img, m0 + j0, pin, [&](int b, int r, float &acc) __attribute__((always_inline)) {
+            acc = sum(b, r);
+            return acc * (1.0f / (kScale2 * kScale2));
+        });
+    };
     auto store = [&](auto secondc, auto fullc, uint32_t t, bool there, int blk, const auto &v) __attribute__((always_inline)) {
         const uint32_t P0 = t * T::TN, Pend = min(P0 + T::TN, P.npix) - 1u;
         const uint32_t pix = P0 + pixel(blk);
         const bool live = there && pix <= Pend;
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
         const uint32_t pin = min(pix, Pend) - img * P.howo;
+        const __amdgpu_buffer_rsrc_t ro = output_desc(P.out, P.out_elems, ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo);
+        const int j0 = first_channel(), room = P.Co - m0 - j0;
+        uint32_t at = (((img - img0) * (uint32_t)P.Co + (uint32_t)j0) * P.howo + pin) * 4u;
+        asm("" : "+v"(at));   // (computed by all lanes: no branch here either)
+        const uint32_t voff = live ? at : kNoStore;
         if constexpr (decltype(secondc)::value) {
-            uint32_t small = 0;
-#pragma unroll
-            for (int r = 0; r < T::OWN; ++r) {
-                const int dj = 8 * (r >> 2) + (r & 3);
-                if (!live || dj >= room) continue;
-                float *const to = P.out + ((size_t)img * P.Co + (size_t)(m0 + j0 + dj)) * P.howo + pin;
-                const float old = *to;
-                if (finite(old)) continue;
-                float val = v[r] * (1.0f / (kScale2 * kScale2));
-                if (settle(v[r], old, val)) small |= 1u << r;
-                else *to = val;
-            }
-            while (small) {
-                const int r = __builtin_ctz(small);
-                small &= small - 1;
-                const int j = m0 + j0 + 8 * (r >> 2) + (r & 3);
-                const int m = (int)fdiv(pin, P.d_wo), n = (int)pin - m * P.Wo;
-                P.out[((size_t)img * P.Co + (size_t)j) * P.howo + pin] = dot_fp32<HF, HF, IMP>(P, img, j, m, n);
-            }
+            settled(std::integral_constant<int, 1>{}, ro, voff, live, j0, img, pin, [&](int, int r) __attribute__((always_inline)) { return v[r]; });
         } else {
             // Every wave issues every store, the lanes that must not pass an offset that no descriptor covers: with their number fixed
             // the wait for the next tile's words counts past them instead of waiting for them.
-            const size_t obase = ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo;
-            const size_t left = (P.out_elems - obase) * 4u;
-            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(P.out + obase, 0, left < kNoStore ? left : kNoStore, 0x00020000);
             const uint32_t howo4 = P.howo * 4u;
-            const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)j0 * P.howo) * 4u : kNoStore;
             float o[T::OWN];
 #pragma unroll
             for (int r = 0; r < T::OWN; ++r) o[r] = v[r] * (1.0f / (kScale * kScale));
@@ -414,46 +406,47 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
     };
 
     // The same for the four neighbouring pixels of a lane, 16 bytes per channel (all inside the layer or all outside, in one plane).
-    auto store_wide = [&](auto fullc, uint32_t t, const floatx16 (&v)[T::B]) __attribute__((always_inline)) {
+    auto store_wide = [&](auto secondc, auto fullc, uint32_t t, const floatx16 (&v)[T::B]) __attribute__((always_inline)) {
         const uint32_t P0 = t * T::TN, Pend = min(P0 + T::TN, P.npix) - 1u;
         const uint32_t pix = P0 + pixel(0);
         const bool live = pix <= Pend;
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
         const uint32_t pin = min(pix, Pend) - img * P.howo;
-        const size_t obase = ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo;
-        const size_t left = (P.out_elems - obase) * 4u;
-        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(P.out + obase, 0, left < kNoStore ? left : kNoStore, 0x00020000);
-        const uint32_t howo4 = P.howo * 4u;
-        const uint32_t voff = live ? ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)j0 * P.howo) * 4u : kNoStore;
-        float odd = 0.0f;
+        const __amdgpu_buffer_rsrc_t ro = output_desc(P.out, P.out_elems, ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo);
+        const int j0 = first_channel(), room = P.Co - m0 - j0;
+        uint32_t at = (((img - img0) * (uint32_t)P.Co + (uint32_t)j0) * P.howo + pin) * 4u;
+        asm("" : "+v"(at));   // (computed by all lanes: no branch here either)
+        const uint32_t voff = live ? at : kNoStore;
+        if constexpr (decltype(secondc)::value) {
+            settled(std::integral_constant<int, T::B>{}, ro, voff, live, j0, img, pin, [&](int b, int r) __attribute__((always_inline)) { return v[b][r]; });
+        } else {
+            const uint32_t howo4 = P.howo * 4u;
+            float odd = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int dj = 8 * (r >> 2) + (r & 3);
-            u32v4 w;   // (element by element: a bit cast applied to a vector element reads element 0)
+            for (int r = 0; r < 16; ++r) {
+                const int dj = 8 * (r >> 2) + (r & 3);
+                u32v4 w;   // (element by element: a bit cast applied to a vector element reads element 0)
 #pragma unroll
-            for (int b = 0; b < T::B; ++b) {
-                const float o = v[b][r] * (1.0f / (kScale * kScale));
-                odd = __builtin_elementwise_maximum(odd, __builtin_fabsf(o));
-                w[b] = __builtin_bit_cast(uint32_t, o);
+                for (int b = 0; b < T::B; ++b) {
+                    const float o = v[b][r] * (1.0f / (kScale * kScale));
+                    odd = __builtin_elementwise_maximum(odd, __builtin_fabsf(o));
+                    w[b] = __builtin_bit_cast(uint32_t, o);
+                }
+                store_quad(w, ro, decltype(fullc)::value || dj < room ? voff : kNoStore, (uint32_t)dj * howo4);
             }
-            const uint32_t vo = decltype(fullc)::value || dj < room ? voff : kNoStore;
-            // (nothing is scheduled between the store and four idle cycles behind it: its data leave the register file over several cycles)
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_raw_buffer_store_b128(w, ro, vo, (uint32_t)dj * howo4, 0);
-            asm volatile("s_nop 3");
-            __builtin_amdgcn_sched_barrier(0);
+            if (__builtin_amdgcn_ballot_w64(live && !finite(odd))) { lo = min(lo, t); hi = t; }
         }
-        if (__builtin_amdgcn_ballot_w64(live && !finite(odd))) { lo = min(lo, t); hi = t; }
     };
 
     // Sums of the channels that other waves store go to LDS, [block][owner][source][quad][lane]; the wave's own stay.
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
     constexpr uint32_t QUADS = T::OWN / 4, SLOT = QUADS * 1024u;
-    const uint32_t block = 2u * T::STAGE + (uint32_t)(rb * T::PX + px) * (Q * (Q - 1)) * SLOT + (uint32_t)lane * 16u;
+    auto block_at = [&]() __attribute__((always_inline)) { return 2u * T::STAGE + (uint32_t)(rb * T::PX + px) * (Q * (Q - 1)) * SLOT + (uint32_t)fresh_lane() * 16u; };
     float own[T::OWN];
     auto hand_over = [&](auto qc, const floatx16 &sum, uint32_t red) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value;
+        const uint32_t block = block_at();
         stem_for([&](auto dc) __attribute__((always_inline)) {
             constexpr int d = decltype(dc)::value;
             if constexpr (d == q) {
@@ -470,6 +463,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         }, std::make_integer_sequence<int, Q>{});
     };
     auto finish = [&](auto secondc, auto fullc, uint32_t t, bool there, uint32_t red) __attribute__((always_inline)) {
+        const uint32_t block = block_at();
 #pragma unroll
         for (int s = 0; s < Q - 1; ++s)
 #pragma unroll
@@ -498,11 +492,11 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
                 const floatx16 sum = multiply(qc, t, 0, at);
                 finish(secondc, fullc, t == first ? t : t - gx, t != first, red ^ T::RED);
                 hand_over(qc, sum, red);
-            } else if constexpr (T::WIDE && !decltype(secondc)::value) {
+            } else if constexpr (T::WIDE) {
                 floatx16 sum[T::B];
 #pragma unroll
                 for (int b = 0; b < T::B; ++b) sum[b] = multiply(qc, t, b, at);
-                store_wide(fullc, t, sum);
+                store_wide(secondc, fullc, t, sum);
             } else {
 #pragma unroll
                 for (int b = 0; b < T::B; ++b) store(secondc, fullc, t, true, b, multiply(qc, t, b, at));

@@ -5,6 +5,7 @@ import torch
 
 import oracle
 import paper_2306_14316_amd as im2win
+from paper_2306_14316_amd import workloads
 
 # Acceptance bar for the fp32 convolution (fp32 multiply/accumulate on the
 # matrix cores, any summation order) against the fp64 oracle:
@@ -82,3 +83,44 @@ def check_layer(I, F, s, p, basic=False, twice=True):
         dO2 = run_conv(dW, F, N, Ci, Hi, Wi, s, p, basic=basic)
         assert torch.equal(dO.view(torch.int32), dO2.view(torch.int32))
     return res
+
+
+def _both_calls(shape, I, F):
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    dW, dI, dF = run_transform(I, Hf, Wf, s, p), I.cuda(), F.cuda()
+    outs = torch.full((2, N, Co, Ho, Wo), 7.0, device="cuda")
+    im2win.conv2d_im2win_fwd(dW, dF, outs[0], *shape)
+    im2win.conv2d_im2win_implicit_fwd(dI, dF, outs[1], *shape)
+    torch.cuda.synchronize()
+    return outs
+
+
+def check_second_pass(shape, seed):
+    """The second pass writes the outputs that the first left infinite or NaN, of all channels or of some, and no other.  Inputs times
+    2^100 take every sum of order one through it: the pieces, the products and their sums are the same, so the bits are."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    I, F = workloads.random_layer_inputs(seed, N, Ci, Hi, Wi, Co, Hf, Wf)
+    print("second pass", shape, im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"], flush=True)
+    plain = _both_calls(shape, I, F)
+    assert torch.isfinite(plain).all()
+    large = _both_calls(shape, torch.ldexp(I, torch.tensor(100)), F)
+    assert torch.equal(large, torch.ldexp(plain, torch.tensor(100, device="cuda")))
+    I2, F2 = I.clone(), F.clone()
+    I2[N // 2], F2[1::3, 0, 0, Wf - 1] = float("nan"), float("nan")   # one image, a third of the channels
+    some = _both_calls(shape, I2, F2)
+    want = plain.clone()
+    want[:, N // 2] = float("nan")
+    want[:, :, 1::3] = float("nan")
+    if p >= Hf:   # windows of padding only
+        want[:, N // 2] = torch.where(_touched(shape), want[:, N // 2], plain[:, N // 2])
+        want[:, N // 2, 1::3] = float("nan")
+    assert torch.equal(torch.isnan(some), torch.isnan(want))
+    assert torch.equal(some[~torch.isnan(want)].view(torch.int32), plain[~torch.isnan(want)].view(torch.int32))
+
+
+def _touched(shape):
+    """Outputs whose window meets the image."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    ones = torch.nn.functional.conv2d(torch.ones(1, 1, Hi, Wi), torch.ones(1, 1, Hf, Wf), stride=s, padding=p)
+    return (ones[0, 0] > 0).cuda()

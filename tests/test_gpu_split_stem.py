@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2306_14316_amd as im2win
 from paper_2306_14316_amd import workloads
-from parity_util import assert_conv_close, conv_errors, run_transform
+from parity_util import assert_conv_close, check_second_pass, conv_errors, run_transform
 from test_gpu_split import _assert_like_basic
 
 pytestmark = pytest.mark.gpu
@@ -107,6 +107,11 @@ def test_infinities_nan_and_the_ends_of_the_range(shape):
     F[4, 1] = 2.0 ** 50                      # a sum past 2^96
     ref = _assert_like_basic(shape, I, F)
     assert torch.isnan(ref).any() and torch.isinf(ref).any()
+
+
+@pytest.mark.parametrize("shape", [q[0] for q in SHAPES], ids=lambda v: "x".join(map(str, v)))
+def test_the_second_pass_writes_what_the_first_left(shape):
+    check_second_pass(shape, 9940)
 
 
 @pytest.mark.parametrize("shape", [SHAPES[17][0], SHAPES[18][0], (512, 3, 36, 36, 32, 3, 3, 1, 0), (300, 3, 42, 42, 16, 3, 3, 1, 1),
