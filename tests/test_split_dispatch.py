@@ -1,4 +1,4 @@
-"""Host side of the bf16-piece kernels (no GPU): the two calls of a layer always take the same instance, whatever the
+"""Host side of the bf16-piece kernels and of the fp32 kernel of three-channel layers (no GPU): the two calls of a layer always take the same instance, whatever the
 sizes, what the plan asks for fits the chip, and the GPU tests run every instance that the plan selects."""
 import random
 
@@ -6,6 +6,8 @@ import pytest
 
 import paper_2306_14316_amd as im2win
 from perf import cases
+from test_gpu_shallow import SHAPES as SHALLOW_SHAPES
+from test_gpu_shallow import instance_name
 from test_gpu_split import SHAPES
 from test_gpu_split_stem import SHAPES as STEM_SHAPES
 
@@ -126,6 +128,23 @@ LINES = [
 def test_lines_between_the_kernels_of_three_channel_layers(shape, kernel):
     for w in (False, True):
         assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"].startswith(kernel)
+
+
+def test_every_selected_fp32_instance_of_three_channel_layers_has_a_gpu_test():
+    tested = {instance_name(shape[5], instance, w) for shape, instance in SHALLOW_SHAPES for w in (False, True)}
+    rng, seen = random.Random(19), set()
+    for _ in range(30000):
+        f, s = rng.choice([(3, 1), (3, 2), (3, 3), (7, 1), (7, 2), (7, 3), (7, 8), (11, 1), (11, 2), (11, 3), (11, 4), (11, 8)])
+        Hi, p = int(2 ** rng.uniform(2, 10.5)), rng.randint(0, 6)
+        Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(2, 10.5))
+        shape = (int(2 ** rng.uniform(0, 9)), 3, Hi, Wi, rng.choice([1, 24, 32, 33, 64, 65, 96, 97, 128, 200]), f, f, s, p)
+        if Hi + 2 * p < f or Wi + 2 * p < f or shape[0] * max(shape[4], 3 * f) * (Hi + 2 * p) * (Wi + 2 * p) >= 2 ** 31:
+            continue
+        for w in (False, True):
+            name = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"]
+            if name.startswith("conv_mfma_shallow_kernel<"):
+                seen.add(name)
+    assert seen == tested, (sorted(seen ^ tested))
 
 
 def test_both_calls_of_large_layers():
