@@ -124,3 +124,30 @@ def _touched(shape):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     ones = torch.nn.functional.conv2d(torch.ones(1, 1, Hi, Wi), torch.ones(1, 1, Hf, Wf), stride=s, padding=p)
     return (ones[0, 0] > 0).cuda()
+
+
+def check_any_alignment(shape, seed):
+    """Buffers at every multiple of four bytes give the bits of aligned ones, and nothing is written outside the output."""
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
+    n = N * Co * Ho * Wo
+    I, F = workloads.random_layer_inputs(seed, N, Ci, Hi, Wi, Co, Hf, Wf)
+    dI, dF, dW = I.cuda(), F.cuda(), run_transform(I, Hf, Wf, s, p)
+
+    def shifted(t, words):
+        buf = torch.full((t.numel() + words + 1,), float("nan"), device="cuda")   # (NaN around: a word from outside would show)
+        buf[words:words + t.numel()] = t.flatten()
+        assert buf.data_ptr() % 16 == 0
+        return buf[words:words + t.numel()]
+
+    print("alignment", shape, im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"], flush=True)
+    for call, src in ((im2win.conv2d_im2win_fwd, dW), (im2win.conv2d_im2win_implicit_fwd, dI)):
+        want = None
+        for a, b, c in ((0, 0, 0), (1, 2, 3), (2, 3, 1), (3, 1, 2)):
+            out = torch.full((n + 68,), 7.0, device="cuda")
+            got = out[32 + c:32 + c + n]
+            call(shifted(src, a), shifted(dF, b), got, *shape)
+            torch.cuda.synchronize()
+            assert (out[:32 + c] == 7.0).all() and (out[32 + c + n:] == 7.0).all()
+            want = got.clone() if want is None else want
+            assert torch.isfinite(got).all() and torch.equal(got.view(torch.int32), want.view(torch.int32)), (a, b, c)

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2306_14316_amd as im2win
 from paper_2306_14316_amd import workloads
-from parity_util import assert_conv_close, check_second_pass, conv_errors, run_conv, run_transform
+from parity_util import assert_conv_close, check_any_alignment, check_second_pass, conv_errors, run_conv, run_transform
 
 pytestmark = pytest.mark.gpu
 
@@ -213,6 +213,11 @@ def _assert_like_basic(shape, I, F):
         a, b = o[fin].double(), ref[fin].double()
         assert bool(((a - b).abs() <= 1e-4 * b.abs().clamp(min=1.0)).all())   # (K = 288 sums of order one; 1e-4 of the sum of magnitudes)
     return ref
+
+
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)], ids=lambda v: "x".join(map(str, v)))
+def test_buffers_of_any_alignment(shape):
+    check_any_alignment(shape, 9315)
 
 
 @pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)], ids=lambda v: "x".join(map(str, v)))

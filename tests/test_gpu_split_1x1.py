@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2306_14316_amd as im2win
 from paper_2306_14316_amd import workloads
-from parity_util import assert_conv_close, check_second_pass, conv_errors
+from parity_util import assert_conv_close, check_any_alignment, check_second_pass, conv_errors
 from test_gpu_split import _assert_like_basic
 from test_gpu_split_stem import _run
 
@@ -50,6 +50,11 @@ def test_no_operand_loses_bits(shape, ei, ef):
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
     got, fp32 = _run(shape, I, F)
     assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
+
+
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (2, 3, 5, 8)], ids=lambda v: "x".join(map(str, v)))
+def test_buffers_of_any_alignment(shape):
+    check_any_alignment(shape, 9985)
 
 
 @pytest.mark.parametrize("shape", [SHAPES[1][0], SHAPES[2][0], SHAPES[5][0], SHAPES[8][0]], ids=lambda s: "x".join(map(str, s)))

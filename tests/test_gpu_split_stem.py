@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2306_14316_amd as im2win
 from paper_2306_14316_amd import workloads
-from parity_util import assert_conv_close, check_second_pass, conv_errors, run_transform
+from parity_util import assert_conv_close, check_any_alignment, check_second_pass, conv_errors, run_transform
 from test_gpu_split import _assert_like_basic
 
 pytestmark = pytest.mark.gpu
@@ -107,6 +107,11 @@ def test_infinities_nan_and_the_ends_of_the_range(shape):
     F[4, 1] = 2.0 ** 50                      # a sum past 2^96
     ref = _assert_like_basic(shape, I, F)
     assert torch.isnan(ref).any() and torch.isinf(ref).any()
+
+
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (0, 2, 4, 6, 8, 10, 12, 14, 16, 18)], ids=lambda v: "x".join(map(str, v)))
+def test_buffers_of_any_alignment(shape):
+    check_any_alignment(shape, 9945)
 
 
 @pytest.mark.parametrize("shape", [q[0] for q in SHAPES], ids=lambda v: "x".join(map(str, v)))
