@@ -8,8 +8,8 @@
 // round (see conv_split_stem.hip).  K blocks of 32 channels, two LDS stages, one barrier per block; a workgroup runs its tiles as one
 // sequence of K blocks, so the next tile's first block is on its way while a tile ends.
 //
-// Measured (convolution alone, us, fp32 matrix cores -> tiles of 128 -> of 256 pixels): 256 -> 256 channels 28x28 N=64 60 -> 51 -> 45, 512 -> 512
-// 14x14 N=32 37 -> 25 -> 36, N=128 113 -> 95 -> 78, 56x56 N=64 853 -> 645 -> 563 (187 TFLOP/s); 1024 -> 256 14x14 N=64 69 -> 45 -> 64.  A lone tile
+// Measured (convolution alone, us, fp32 matrix cores -> tiles of 128 -> of 256 pixels): 256 -> 256 channels 28x28 N=64 62 -> 51 -> 44, 512 -> 512
+// 14x14 N=32 37 -> 25 -> 35, N=128 112 -> 92 -> 75, 56x56 N=64 940 -> 627 -> 550 (191 TFLOP/s); 1024 -> 256 14x14 N=64 70 -> 44 -> 63.  A lone tile
 // of 128 pixels takes 1.3 us for a K block whose MFMAs take 0.65: a wave's own chain of cutting, writing and reading; of 256 pixels 1.85 for
 // 1.3.  Fetching two blocks ahead gave nothing; tiles of 64 x 256 for layers of up to 64 channels 16 against 13 (256 -> 64 56x56 N=8).  Relative
 // 2-norm error against 64 bits 7e-8 (fp32 matrix cores 2e-7).
@@ -300,11 +300,14 @@ hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out,
     P.d_wo = make_fastdiv((uint32_t)sh.Wo); P.d_howo = make_fastdiv(P.howo);
     if (sh.s > 65536) return hipErrorNotSupported;
     // Which is faster, in us: rounds of tiles (a last round that leaves units idle runs at a higher clock: half of the loss is made up) at 1.6 for a
-    // K block and 2 for a tile of 128 pixels, 2.55 and 6 of 256; the fp32 kernel's 64-channel tiles at 115 TFLOP/s.  Measured, fp32 / 128 / 256
-    // pixels: 256 -> 256 28x28 N=64 59.6 / 54-60 / 51.5, 14x14 N=32 12.8 / 15.9 / 22, N=128 34 / 28 / 27; 512 -> 512 14x14 N=32 37 / 26 / 39, N=64 62 /
-    // 48 / 43, N=128 112 / 94 / 82, 56x56 N=64 827 / 651 / 610; 1024 -> 256 14x14 N=32 39 / 46 / 69, N=128 118 / 89 / 76; 256 -> 256 56x56 N=64 218 / 184 /
-    // 186; 64 -> 256 56x56 N=64 68 / 63 / 78; 256 -> 64 56x56 N=8 12.7 / 16.3 / -.  (Channel counts that the fp32 1x1 kernel does not take run the
-    // generic one there, at 50 TFLOP/s.)
+    // K block and 2 for a tile of 128 pixels, 2.55 and 6 of 256; the fp32 kernel's 64-channel tiles at 115 TFLOP/s (channel counts that the fp32
+    // 1x1 kernel does not take run the generic one there, at 50).  Measured, fp32 / 128 / 256 pixels, the one that runs in brackets: 256 -> 256 28x28
+    // N=64 62 / 51 / [44], 14x14 N=32 [12.7] / 14.4 / 21, N=128 34 / 27 / [25]; 512 -> 512 14x14 N=32 37 / [25] / 35, N=64 64 / 45 / [39], N=128 112 / 92 /
+    // [75], 56x56 N=64 940 / 627 / [550]; 1024 -> 256 14x14 N=32 [40] / 42 / 61, N=64 70 / [44] / 63, N=128 122 / 85 / [70]; 256 -> 256 56x56 N=64 248 / 164 /
+    // [160]; 128 -> 129 30x33 N=64 79 / 29 / [27]; 256 -> 64 56x56 N=8 [12.5] / 14.7 / 21.  With short K loops the estimates of the pieces are too high
+    // (64 -> 256 56x56 N=64 68 / 75 for [70] / 59 / 58): such layers stay on the fp32 kernel where that is the slower one.  1000 layers that it takes,
+    // half of them strided: in two calls none is more than 3 % slower, workspace-free five strided ones 4 to 15 % (N=61 1408 -> 1024 88x31 stride 4,
+    // 364 / [421]; 238 against 283 in two calls).
     auto time = [&](int tn, double block, double tile) {
         const double r = (double)((P.npix + tn - 1) / tn) * ((sh.Co + 127) / 128) / ncu;
         return 2.0 + 0.5 * (r + (double)(long long)(r + 0.999)) * (P.nkb * block + tile);
