@@ -155,11 +155,12 @@ im2win_status conv2d_im2win_fwd_variant(const float *window_dev, const float *fi
  * input.  Each workgroup builds the im2win strips of its tile (Section 3.1, Eq. 2),
  * or the patch they come from, in LDS instead of reading an im2win tensor, so no
  * workspace and no transform call are needed; the MFMA loop and the result are those
- * of conv2d_im2win_fwd.  Any layer is accepted.  Layers the pipelined kernel takes
- * (3x3 filters with Ci a multiple of 8, 5x5 with Ci a multiple of 4, 7x7 with
- * Ci even, filter_dev 16-byte aligned) run at the speed of conv2d_im2win_fwd
- * alone; the others (three-channel stem layers among them) take the generic,
- * unpipelined kernel and are slower than the two-call path.
+ * of conv2d_im2win_fwd.  Any layer is accepted.  Layers with a kernel of their own (3x3
+ * filters with Ci a multiple of 8, 5x5 with Ci a multiple of 4, 7x7 with Ci even,
+ * filter_dev 16-byte aligned; 1x1 without padding, Ci a multiple of 8; three-channel 3x3,
+ * 7x7 and 11x11 stems; the bf16-piece filters) run at about the speed of
+ * conv2d_im2win_fwd alone; the others take the generic, unpipelined kernel and may be
+ * slower than the two-call path.
  *   input_dev   device, N*Ci*Hi*Wi floats, read only
  *   filter_dev  device, Co*Ci*Hf*Wf floats, [Co][Ci][Hf][Wf]
  *   output_dev  device, N*Co*Ho*Wo floats, fully overwritten
