@@ -6,7 +6,6 @@ torch stream is handed to the library as the hipStream_t.
 from __future__ import annotations
 
 import ctypes
-import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -125,27 +124,32 @@ def im2col_footprint_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) -> int:
 # The host side of a call is what a small layer waits for (a 3x3 layer on one 32x32 image, two calls: 20 us, of which the two
 # launches take 7.5), so a call asks the library for its sizes once per layer (shapes that it refuses are not kept), names no
 # module and wraps no pointer or stream on its way: 20 -> 12 us.
-# Kept for plain ints only: what else passes for one (a 0-dim tensor) would be told apart by identity though its value may change,
-# or equals an int without being accepted (a float).
+# Kept for plain ints only, and found by value: what else passes for one may change (a 0-dim tensor).
+_kept_elems = {}
+
+
 def _ask_elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad):
     window = im2win_workspace_bytes(N, Ci, Hi, Wi, Hf, Wf, stride, pad) // 4
     Ho, Wo = im2win_out_shape(Hi, Wi, Hf, Wf, stride, pad)
     return window, N * Co * Ho * Wo
 
 
-_kept_elems = functools.lru_cache(maxsize=1024)(_ask_elems)
-
-
-def _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad):
-    """Elements of the im2win tensor and of the output."""
-    ints = type(N) is type(Ci) is type(Hi) is type(Wi) is type(Co) is type(Hf) is type(Wf) is type(stride) is type(pad) is int
-    return (_kept_elems if ints else _ask_elems)(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
+def _elems(*dims):
+    """Elements of the im2win tensor and of the output, for N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad."""
+    elems = _kept_elems.get(dims)
+    if elems is None:
+        elems = _ask_elems(*dims)
+        if all(type(d) is int for d in dims):
+            if len(_kept_elems) >= 1024:
+                _kept_elems.clear()
+            _kept_elems[dims] = elems
+    return elems
 
 
 def layer_sizes(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad) -> dict:
     """Ho, Wo and the element counts of the im2win tensor and the output, as the library derives them."""
     Ho, Wo = im2win_out_shape(Hi, Wi, Hf, Wf, stride, pad)
-    window, output = _elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
+    window, output = _ask_elems(N, Ci, Hi, Wi, Co, Hf, Wf, stride, pad)
     return {"Ho": Ho, "Wo": Wo, "window_elems": window, "output_elems": output}
 
 

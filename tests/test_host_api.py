@@ -202,14 +202,19 @@ def test_sizes_kept_from_earlier_calls_are_of_plain_ints_only(lib):
     the check of its buffers."""
     import torch
     n = torch.tensor(1)
-    first = im2win.layer_sizes(n, 3, 8, 8, 5, 3, 3, 1, 0)
-    n += 1
-    for N in (n, 2):
-        again = im2win.layer_sizes(N, 3, 8, 8, 5, 3, 3, 1, 0)
-        assert again["window_elems"] == 2 * first["window_elems"] and int(again["output_elems"]) == 2 * 5 * 6 * 6
+    for elems in (binding._elems, lambda *d: (im2win.layer_sizes(*d)["window_elems"], im2win.layer_sizes(*d)["output_elems"])):
+        n.fill_(1)
+        first = elems(n, 3, 8, 8, 5, 3, 3, 1, 0)
+        n += 1
+        for N in (n, 2, n):
+            again = elems(N, 3, 8, 8, 5, 3, 3, 1, 0)
+            assert again[0] == 2 * first[0] and int(again[1]) == 2 * 5 * 6 * 6
     for bad in (2.0, [2]):
         with pytest.raises(ctypes.ArgumentError):
             im2win.layer_sizes(bad, 3, 8, 8, 5, 3, 3, 1, 0)
+    for N in range(1, 3000):   # bounded
+        binding._elems(N, 3, 8, 8, 5, 3, 3, 1, 0)
+    assert len(binding._kept_elems) <= 1024
 
 
 def test_the_current_stream_needs_no_private_call(monkeypatch):
