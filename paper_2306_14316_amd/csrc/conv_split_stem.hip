@@ -368,7 +368,12 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         if constexpr (Q < 4 || T::NW > 8) asm volatile("" : "+v"(l));
         return l;
     };
-    auto first_channel = [&]() __attribute__((always_inline)) { return (T::OWN == 16 ? 0 : ks * (T::OWN / 4) * 8) + (fresh_lane() >> 5) * 4; };   // of the block
+    auto first_channel = [&](int l) __attribute__((always_inline)) { return (T::OWN == 16 ? 0 : ks * (T::OWN / 4) * 8) + (l >> 5) * 4; };   // of the block
+    // (7x7 in two parts has registers for the comparisons with the channels left: N=128 224x224 80 channels 294, worked out again 302)
+    auto room_of = [&](int j0) __attribute__((always_inline)) {
+        if constexpr (Q == 2) return P.Co - m0 - first_channel(lane);
+        else return P.Co - m0 - j0;
+    };
     auto settled = [&](auto bc, const __amdgpu_buffer_rsrc_t &ro, uint32_t voff, bool live, int j0, uint32_t img, uint32_t pin, auto &&sum) __attribute__((always_inline)) {
         settle_outputs<HF, HF, IMP, T::OWN, decltype(bc)::value>(P, ro, voff, live, P.Co - m0 - j0, img, m0 + j0, pin, [&](int b, int r, float &acc) __attribute__((always_inline)) {
             acc = sum(b, r);
@@ -382,7 +387,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
         const uint32_t pin = min(pix, Pend) - img * P.howo;
         const __amdgpu_buffer_rsrc_t ro = output_desc(P.out, P.out_elems, ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo);
-        const int j0 = first_channel(), room = P.Co - m0 - j0;
+        const int j0 = first_channel(fresh_lane()), room = room_of(j0);
         uint32_t at = (((img - img0) * (uint32_t)P.Co + (uint32_t)j0) * P.howo + pin) * 4u;
         asm("" : "+v"(at));   // (computed by all lanes: no branch here either)
         const uint32_t voff = live ? at : kNoStore;
@@ -413,7 +418,7 @@ __device__ __forceinline__ void conv_stem_body(const StemParams &P, unsigned cha
         const uint32_t img0 = fdiv(P0, P.d_howo), img = fdiv(min(pix, Pend), P.d_howo);
         const uint32_t pin = min(pix, Pend) - img * P.howo;
         const __amdgpu_buffer_rsrc_t ro = output_desc(P.out, P.out_elems, ((size_t)img0 * P.Co + (size_t)min(m0, P.Co - 1)) * P.howo);
-        const int j0 = first_channel(), room = P.Co - m0 - j0;
+        const int j0 = first_channel(fresh_lane()), room = room_of(j0);
         uint32_t at = (((img - img0) * (uint32_t)P.Co + (uint32_t)j0) * P.howo + pin) * 4u;
         asm("" : "+v"(at));   // (computed by all lanes: no branch here either)
         const uint32_t voff = live ? at : kNoStore;
