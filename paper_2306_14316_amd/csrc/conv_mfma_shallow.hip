@@ -1,6 +1,7 @@
 // Filter-stationary MFMA im2win convolution for layers with few input channels
-// and a large window (the 7x7/stride-2 and 11x11/stride-4 stem layers, Table 2's
-// Conv1-Conv3/Conv7): K = Ci*Hf*Wf is small (27..363) while N = Ni*Ho*Wo is huge.
+// and a large window (three-channel 3x3, 7x7 and 11x11 layers; most 7x7 at stride 2,
+// 11x11 at stride 4 and some 3x3 ones have moved to conv_split_stem.hip): K = Ci*Hf*Wf
+// is small (27..363) while N = Ni*Ho*Wo is huge.
 //
 // Design (CDNA4's, not the paper's CUDA tiling):
 //   - persistent workgroups: the grid takes the 64-pixel tiles round by round, the

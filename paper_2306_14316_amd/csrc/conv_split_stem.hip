@@ -620,7 +620,7 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
     if (sh.Hf == 3) {
         // Stride 2: 224x224, padding 1, N=8 16 channels 13.0 / 13.7, here 11.3 / 12.2; 64 channels 15.7 / 16.3, 12.5 / 15.2; N=64 16 channels
         // 74 / 75, 33 / 42; 64 channels 88 / 85, 50 / 57; 96 channels 198 / 180, 91 / 128.  Small layers (500 of all sizes): two calls gain 6 to
-        // 40 %; workspace-free, where a workgroup has one or two tiles, up to 7 % is lost (N=8 80x80 128 channels 10.7 / 11.3) and 12 % gained.
+        // 40 %; workspace-free, where a workgroup has one or two tiles, up to 7 % is lost (N=77 8x138 124 channels 10.3 / 10.7, here 9.7 / 11.5) and 12 % gained.
         if (sh.s == 2) {
             // An odd count of blocks, three or more: single blocks stage each pixel once per block, pairs leave one block empty.  Pairs where a
             // workgroup has few tiles (in pairs / single: 96 channels, N=1 313x313 9.1 / 10.8, 10.5 / 13.0; 160 channels, N=14 158x127 18.1 / 21.8,
@@ -653,7 +653,7 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         // at most three output rows per 64 pixels): 64 channels, N=1 224x224 10.9 / 11.7, here 11.3 / 13.2; N=2 16.6 / 17.5, here 13.4 / 15.8;
         // 24 channels, N=1 11.2 / 10.5, 11.2 / 12.5; N=2 12.9 / 15.5, 11.4 / 12.6.
         if (blocks <= 2 && per_cu < 64 && sh.Wo > 31) return hipErrorNotSupported;
-        // Otherwise at any size (500 layers of all sizes: 1.08 to 2.9 times as fast in two calls, 1.02 to 2.9 workspace-free).
+        // Otherwise at any size (500 layers of all sizes: at least 1.08 times as fast in two calls, 1.02 workspace-free).
         if (blocks == 1) return launch_stem_t<7, 1, 2, 4>(P, implicit, st, plan);
         if (blocks == 3) return launch_stem_t<7, 3, 2, 2>(P, implicit, st, plan);
         // K in one wave or two: one cuts twice the filter words at its start, but nothing is exchanged.  64 channels, N=8 224x224
@@ -661,7 +661,7 @@ hipError_t launch_conv_split_stem(const float *src, const float *flt, float *out
         if (per_cu < 768) return launch_stem_t<7, 2, 2, 2>(P, implicit, st, plan);
         return launch_stem_t<7, 2, 1, 4>(P, implicit, st, plan);
     }
-    // Two or more blocks: at any size (224 layers of all sizes: 1.37 to 3.2 times as fast as on the fp32 kernel in two calls, 1.19 to 2.6
+    // Two or more blocks: at any size (331 layers of all sizes: at least 1.37 times as fast as on the fp32 kernels in two calls, 1.14
     // workspace-free).  One block: its own instance from four rounds of the other's tiles, whose one half is empty then; behind five
     // with a full block, whose stores cost it more.
     if (blocks == 1 && per_cu >= (sh.Co > 24 ? 161u : 128u)) {
