@@ -58,13 +58,14 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     Q.plane = (uint32_t)plane; Q.howo = P.howo; Q.src_elems = P.win_elems; Q.out_elems = P.out_elems;
     Q.tiles_m = (sh.Co + TM - 1) / TM;
     const uint32_t rows = (uint32_t)(sh.N * sh.Ho);
-    Q.tiles_s = (rows * (uint32_t)Q.w + TN - 1) / TN;
-    Q.nblocks = (Q.tiles_s * (uint32_t)(Q.nstrips - 1) + (rows * (uint32_t)Q.wl + TN - 1) / TN) * (uint32_t)Q.tiles_m;
+    const uint32_t tiles_s = (rows * (uint32_t)Q.w + TN - 1) / TN;
+    Q.tiles_l = (rows * (uint32_t)Q.wl + TN - 1) / TN;
+    Q.nblocks = (tiles_s * (uint32_t)(Q.nstrips - 1) + Q.tiles_l) * (uint32_t)Q.tiles_m;
     Q.LF = (int)LF; Q.npos = (int)best;
     Q.d_w = make_fastdiv((uint32_t)Q.w); Q.d_wl = make_fastdiv((uint32_t)Q.wl); Q.d_ho = make_fastdiv((uint32_t)sh.Ho);
     Q.rstep = rstep; Q.GF = (sh.Ho - 1 + rstep - 1) / rstep + 1;
     Q.d_rs = make_fastdiv((uint32_t)rstep); Q.d_gf = make_fastdiv((uint32_t)Q.GF); Q.d_pw = make_fastdiv((uint32_t)Q.PW); Q.d_lf = make_fastdiv((uint32_t)LF);
-    Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m); Q.d_ts = make_fastdiv(Q.tiles_s);
+    Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m); Q.d_ns = make_fastdiv((uint32_t)Q.nstrips); Q.d_ns1 = make_fastdiv((uint32_t)std::max(1, Q.nstrips - 1));
     *lds = 2 * (size_t)(2 * KC::KS) * split_a_plane(TM) + (size_t)KC::CG * (smax + 2) * 48 + kPassBytes;
     return true;
 }

@@ -82,6 +82,10 @@ SHAPES = [
     ((81, 8, 12, 100, 20, 7, 7, 1, 0), 3),
     ((48, 7, 39, 96, 33, 7, 7, 2, 4), 3),
     ((67, 18, 27, 81, 20, 7, 7, 2, 4), 3),
+    # strips of unequal width, the last with fewer tiles than the others (5, 7 and 3 strips; 43 tiles of 49, 12 of 15, 28 of 31)
+    ((38, 33, 22, 73, 65, 3, 3, 1, 1), 2),
+    ((11, 18, 23, 102, 65, 5, 5, 1, 2), 2),
+    ((22, 18, 49, 81, 65, 7, 7, 2, 3), 3),
 ]
 
 
