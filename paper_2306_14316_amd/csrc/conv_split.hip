@@ -13,7 +13,7 @@ template <int HF, int WF, int CFG>
 static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, bool implicit, size_t *lds)
 {
     using KC = SplitK<HF, WF, CFG>;
-    using T = SplitTile<KC::WIDE>;
+    using T = SplitTile<KC::SHAPE>;
     constexpr int TM = T::WGM * T::FM * 32, TN = T::WGN * T::FN * 32;
     constexpr int smax = split_positions<HF, WF, CFG>() - 2;
     // (Both calls ask for what either needs, so that they take the same kernel and give the same bits.)
@@ -40,7 +40,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
             imgs = std::max(imgs, I);
             items = std::max(items, KC::CG * std::max(rows * ((pw + 3) / 4), reads * ((pw * HF + 3) / 4)));
         }
-        if (need > smax || items > KC::JQ * 256 || (best >= 0 && need >= best)) continue;
+        if (need > smax || items > KC::JQ * KC::PW * 64 || (best >= 0 && need >= best)) continue;
         best = need; best_img = imgs;
         Q.w = w; Q.wl = wl; Q.nstrips = ns; Q.PW = (int)PW;
     }
@@ -71,7 +71,7 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
 }
 
 template <int HF, int WF, int CFG, bool IMP>
-__global__ __launch_bounds__(512, 2) void conv_split_kernel(SplitParams P)
+__global__ __launch_bounds__((split_threads<HF, WF, CFG>()), (split_threads<HF, WF, CFG>() / 256)) void conv_split_kernel(SplitParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     conv_split_body<HF, WF, CFG, IMP>(P, smem);
@@ -80,17 +80,46 @@ __global__ __launch_bounds__(512, 2) void conv_split_kernel(SplitParams P)
 template <int HF, int WF, int CFG, bool IMP>
 static hipError_t launch_split_t(const SplitParams &Q, size_t lds, int dev, int ncu, hipStream_t st, LaunchPlan *plan)
 {
+    constexpr int NT = split_threads<HF, WF, CFG>();
     const uint32_t grid = std::min(Q.nblocks, (uint32_t)ncu);   // one workgroup per compute unit; it takes every grid-th tile
     if (plan) {
-        plan_record(plan, dim3(grid), 512, lds, "conv_split_kernel<%d, %d, %d, %s>", HF, WF, CFG, IMP ? "true" : "false");
+        plan_record(plan, dim3(grid), NT, lds, "conv_split_kernel<%d, %d, %d, %s>", HF, WF, CFG, IMP ? "true" : "false");
         return hipSuccess;
     }
     void (*kern)(SplitParams) = &conv_split_kernel<HF, WF, CFG, IMP>;
     static KernelCache kc;
     const hipError_t e = allow_dynamic_lds(kc, reinterpret_cast<const void *>(kern), lds, dev);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, Q);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, Q);
     return hipGetLastError();
+}
+
+// What the layer takes on the fp32 matrix cores, in us: 64x64 tiles of the pipelined kernel, whose 3x3 and 5x5 instances cut leftover
+// tiles into halves or sixteenths and which runs over tile boundaries where K is short and the channels are whole tiles (10 % off, root
+// mean square, on 1440 layers).  Strips longer than its instances take (images of a few pixels a row, wide strides) leave the layer to the
+// generic kernels, at a quarter of the rate: 7x7 stride 2 20 -> 59 channels 55x55 N=27 105 us, pieces 27.  By sizes alone, so that both
+// calls take the same body.
+template <int HF, int WF>
+static double fp32_estimate(const MfmaParams &P, const Shape &sh, uint32_t blocks, int ncu)
+{
+    constexpr int CB = HF == 3 && WF == 3 ? 8 : HF == 5 ? 4 : HF == 7 && WF == 7 ? 2 : HF == 4 ? 4 : HF * WF == 7 ? 8 : 16;
+    constexpr int LONGEST = HF * WF == 3 ? 256 : HF == 7 && WF == 7 ? 1024 : HF == 5 || HF == 4 ? 768 : 512;
+    constexpr uint32_t RESIDENT = (HF == 3 && WF == 3) || (HF == 1 && WF == 7) ? 3 : 2;   // workgroups per compute unit
+    const double r = (double)blocks / ncu, up = (double)((blocks + ncu - 1) / ncu);
+    if (P.S > LONGEST) return 4.0 + std::max(0.5 * (r + up), 0.6) * (double)sh.K * 0.055;
+    const int nkb = (sh.Ci + CB - 1) / CB;
+    const bool whole = sh.Ci % CB == 0;
+    double rounds = 0.9 * up + 0.1 * std::max(r, up > 1.5 ? 0.0 : 0.84);
+    if (whole && nkb % 2 == 0 && nkb <= 12 && sh.Co % MB == 0 && blocks >= 3 * RESIDENT * (uint32_t)ncu) {
+        rounds = r;
+    } else if (whole && HF == WF && (HF == 3 || HF == 5)) {
+        const uint32_t left = blocks % (uint32_t)ncu;
+        const bool pieces = HF == 3 && sh.Ci % 16 == 0;
+        if (pieces && left <= (uint32_t)ncu / 8) rounds = (double)(blocks / ncu) + (left ? 0.42 : 0.0);
+        else if (left <= (uint32_t)ncu / 2) rounds = (double)(blocks / ncu) + (left ? 0.55 : 0.0);
+        else if (pieces && left <= (uint32_t)(ncu / 2 + ncu / 8)) rounds = (double)(blocks / ncu) + 0.65;
+    }
+    return 3.75 + rounds * ((double)(nkb * CB * HF * WF) * 0.0151 + 0.92);
 }
 
 // hipErrorNotSupported where no tile shape fits or the fp32 pipeline is the faster one.
@@ -101,43 +130,56 @@ static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t bl
     hipError_t e = device_cus(&dev, &ncu);
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
     if (e != hipSuccess) return e;
-    // Which is faster: estimates in ns, fitted to 3x3, 5x5, 7x7, 4x4, 1x7, 7x1, 1x3 and 3x1 layers of 16 to 512 channels
-    // (within about 15 %).  Measured, fp32 pipeline / this body in us: 3x3 64 channels 56x56 N=8 19 / 19-27, N=16 34 / 30,
-    // N=32 61 / 47; 3x3 256 channels 14x14 N=16 37 / 52, N=128 213 / 142; 5x5 96 -> 256 24x24 N=16 79 / 52; 7x1 128 channels
-    // 28x28 142 / 72; 1x3 128 channels 28x28 51 / 45; 4x4 stride 2 64 -> 128 64x64 130 / 91.  The fp32 pipeline: its 64x64
-    // tiles at 490 GFLOP/s per compute unit and 0.8 us each; the 3x3 instances cut leftover tiles up, so their rounds
-    // count in fractions, and the others' half.
-    auto rounds = [&](uint32_t tiles) {   // (a last round that leaves units idle runs at a higher clock: half of the loss is made up)
+    // Which is faster: estimates in us, fitted to 1600 layers of 3x3, 5x5, 7x7, 4x4, 1x7, 7x1, 1x3 and 3x1 filters with 4 to 512 channels, odd
+    // sizes and those of usual networks (7 % off, root mean square; the pick takes 1.007 times the best body's time on average, 1.3 at
+    // worst).  A body takes its start and end, and per round of tiles the tile's steps and its own start and stores.  Measured, fp32
+    // pipeline / wide / narrow / low: 3x3 64 channels 56x56 N=32 62 / 48 / 58 / 57; 3x3 256 channels 14x14 N=128 213 / 140 / 183 / 181;
+    // 3x3 512 channels 7x7 N=128 151 / 160 / 101 / 95; 3x3 100 -> 130 29x27 N=61 130 / 99 / 101 / 88; 5x5 96 -> 100 24x24 N=50
+    // - / 68 / 94 / 81; 7x7 stride 2 64 -> 20 134x134 N=16 - / 104 / 129 / 74.
+    // `mix`: how far a last round that leaves units idle counts in full (it runs at a higher clock).
+    auto rounds = [&](uint32_t tiles, double mix) {
         const double r = (double)tiles / ncu, up = (double)((tiles + ncu - 1) / ncu);
-        return 0.5 * (up + std::max(r, up > 1.5 ? 0.0 : 0.6));
+        return mix * up + (1.0 - mix) * std::max(r, up > 1.5 ? 0.0 : 0.6);
     };
-    const double ro = HF == 3 && WF == 3 ? std::max((double)blocks / ncu, 0.2) : std::max(0.5 * ((double)blocks / ncu + (blocks + ncu - 1) / ncu), 0.6);
-    const double old = ro * ((double)sh.K * 8192.0 / 490.0 + 800.0);
-    if (old < 12000.0) return hipErrorNotSupported;   // (nothing below starts and ends in less)
-    SplitParams Q[4];
-    size_t lds[4];
-    const bool ok[4] = {split_params<HF, WF, 0>(Q[0], P, sh, IMP, &lds[0]), split_params<HF, WF, 1>(Q[1], P, sh, IMP, &lds[1]),
-                        split_params<HF, WF, 2>(Q[2], P, sh, IMP, &lds[2]), split_params<HF, WF, 3>(Q[3], P, sh, IMP, &lds[3])};
+    const double old = fp32_estimate<HF, WF>(P, sh, blocks, ncu);
+    if (old < 9.0) return hipErrorNotSupported;   // (nothing below starts and ends in less)
+    SplitParams Q[5];
+    size_t lds[5];
     int pick = -1;
-    double least = 0.95 * old;
-    auto consider = [&](int i, bool wide, int CG) {
-        if (!ok[i]) return;
-        const double steps = (double)((sh.Ci + 8 * CG - 1) / (8 * CG)) * ((CG * HF * WF + 1) / 2);
-        const double t = 4000.0 + rounds(Q[i].nblocks) * (wide ? steps * 517.0 + 6000.0 : steps * 350.0 + 3500.0);
-        if (t < least) { least = t; pick = i; }
+    double least = 0.93 * old;
+    auto consider = [&](auto cfg) {
+        constexpr int CFG = decltype(cfg)::value;
+        using KC = SplitK<HF, WF, CFG>;
+        if (!split_params<HF, WF, CFG>(Q[CFG], P, sh, IMP, &lds[CFG])) return;
+        const double steps = (double)((sh.Ci + 8 * KC::CG - 1) / (8 * KC::CG)) * ((KC::CG * HF * WF + 1) / 2);
+        constexpr bool SHORT = HF * WF == 3 || (HF == 4 && WF == 4);   // short K blocks, more patch to a step
+        const double t = KC::SHAPE == kWide     ? 5.3 + rounds(Q[CFG].nblocks, 0.65) * (SHORT ? 1.15 : 1.0) * (steps * 0.475 + 4.25)
+                         : KC::SHAPE == kNarrow ? 4.55 + rounds(Q[CFG].nblocks, 0.75) * (SHORT ? 1.16 : 1.0) * (steps * 0.3035 + 2.3)
+                                                : 5.05 + rounds(Q[CFG].nblocks, 0.65) * (SHORT ? 1.3 : HF * WF >= 25 ? 0.94 : 1.0) * (steps * 0.31 + 2.2);
+        if (t < least) { least = t; pick = CFG; }
     };
-    constexpr bool LONG = SplitK<HF, WF, 0>::CG < 4;   // (1x3 and 3x1: 0 is 3 with one item per thread, for tiles of a few pixels)
-    if (LONG) consider(0, SplitK<HF, WF, 0>::WIDE, SplitK<HF, WF, 0>::CG);
-    consider(1, SplitK<HF, WF, 1>::WIDE, SplitK<HF, WF, 1>::CG);
-    consider(2, SplitK<HF, WF, 2>::WIDE, SplitK<HF, WF, 2>::CG);
-    consider(3, SplitK<HF, WF, 3>::WIDE, SplitK<HF, WF, 3>::CG);
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using C2 = std::integral_constant<int, 2>;
+    using C3 = std::integral_constant<int, 3>;
+    using C4 = std::integral_constant<int, 4>;
+    constexpr bool LONG = HF * WF != 3;                             // (1x3 and 3x1: 0 would be 3 with one item per thread)
+    constexpr bool EIGHT = HF == WF && (HF == 3 || HF == 5);       // (the others hold 8 channels in every configuration, or need not)
+    if constexpr (LONG) consider(C0{});
+    consider(C1{});
+    if constexpr (EIGHT) consider(C2{});
+    consider(C3{});
+    consider(C4{});
     switch (pick) {
         case 0:
             if constexpr (LONG) return launch_split_t<HF, WF, 0, IMP>(Q[0], lds[0], dev, ncu, st, plan);
-            else return hipErrorNotSupported;
+            return hipErrorNotSupported;
         case 1: return launch_split_t<HF, WF, 1, IMP>(Q[1], lds[1], dev, ncu, st, plan);
-        case 2: return launch_split_t<HF, WF, 2, IMP>(Q[2], lds[2], dev, ncu, st, plan);
+        case 2:
+            if constexpr (EIGHT) return launch_split_t<HF, WF, 2, IMP>(Q[2], lds[2], dev, ncu, st, plan);
+            return hipErrorNotSupported;
         case 3: return launch_split_t<HF, WF, 3, IMP>(Q[3], lds[3], dev, ncu, st, plan);
+        case 4: return launch_split_t<HF, WF, 4, IMP>(Q[4], lds[4], dev, ncu, st, plan);
         default: return hipErrorNotSupported;
     }
 }

@@ -269,7 +269,8 @@ ASYMMETRIC_SHAPES = [
     ((1, 17, 30, 14, 72, 3, 1, 2, 1), False),    # 3x1 stride 2: strips longer than the instance's
     ((1, 17, 30, 14, 72, 1, 3, 2, 1), True),     # 1x3 stride 2, 17 channels
     ((2, 12, 14, 30, 40, 1, 3, 1, 1), False),    # 1x3 with fewer channels than a K block
-    ((48, 16, 56, 56, 64, 1, 7, 1, 3), True),    # 1x7: several tiles per workgroup
+    ((48, 16, 56, 56, 64, 1, 7, 1, 3), False),    # 1x7: the bf16-piece kernel
+    ((92, 16, 36, 156, 64, 1, 7, 2, 3), True),   # 1x7 stride 2: several tiles per workgroup
     ((32, 32, 56, 56, 64, 3, 1, 1, 1), True),    # 3x1: several tiles per workgroup
     ((2, 8, 20, 20, 40, 4, 4, 2, 1), True),      # 4x4 stride 2: a tile spans seven rows
     ((2, 64, 64, 64, 64, 4, 4, 2, 1), True),     # 4x4 stride 2, sixteen K blocks, two rows per tile

@@ -16,77 +16,118 @@ def _split(shape, workspace_free=False):
     return im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)["kernel"].startswith("conv_split_kernel<")
 
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the configuration (0 / 1: long filter stages, 64 x 256 / 64 x 128 tiles; 2 and 3: larger
-# patches): every instance at channel counts off its K block and tile, with padding, on short images (a tile spans several)
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the configuration (0 / 1 / 4: long filter stages, tiles of 64 x 256 / 64 x 128 / 32 x 256; 2 and 3:
+# 64 x 256 with larger patches): every instance at channel counts off its K block and tile, with padding, on short images (a tile spans several)
 # and at the strides it takes
 SHAPES = [
-    ((54, 404, 61, 6, 100, 1, 3, 1, 0), 2),
+    ((54, 404, 61, 6, 100, 1, 3, 1, 0), 1),
     ((26, 283, 23, 16, 20, 1, 3, 1, 4), 1),
     ((99, 298, 7, 31, 20, 1, 3, 1, 0), 1),
     ((22, 100, 50, 59, 128, 1, 3, 1, 0), 3),
-    ((68, 131, 8, 116, 20, 1, 3, 1, 0), 3),
+    ((68, 131, 8, 116, 20, 1, 3, 1, 0), 4),
     ((17, 100, 44, 39, 33, 1, 7, 1, 3), 0),
-    ((78, 63, 6, 89, 20, 1, 7, 1, 0), 0),
-    ((6, 128, 57, 51, 32, 1, 7, 1, 1), 1),
-    ((66, 232, 9, 38, 20, 1, 7, 1, 0), 1),
-    ((14, 128, 41, 60, 65, 1, 7, 2, 1), 2),   # a stride wider than the filter is high: rows between the windows
-    ((114, 126, 7, 70, 20, 1, 7, 2, 1), 2),
-    ((49, 109, 94, 6, 20, 1, 7, 1, 4), 3),
+    ((78, 63, 6, 89, 20, 1, 7, 1, 0), 4),
+    ((6, 128, 57, 51, 32, 1, 7, 1, 1), 4),
+    ((66, 232, 9, 38, 20, 1, 7, 1, 0), 4),
+    ((14, 128, 41, 60, 65, 1, 7, 2, 1), 1),   # a stride wider than the filter is high: rows between the windows
+    ((114, 126, 7, 70, 20, 1, 7, 2, 1), 1),
+    ((49, 109, 94, 6, 20, 1, 7, 1, 4), 4),
     ((83, 506, 7, 26, 20, 3, 1, 1, 2), 1),
     ((113, 252, 10, 7, 20, 3, 1, 1, 3), 1),
-    ((41, 282, 9, 52, 33, 3, 1, 1, 1), 2),
-    ((52, 303, 19, 6, 20, 3, 1, 1, 4), 2),
+    ((41, 282, 9, 52, 33, 3, 1, 1, 1), 1),
+    ((52, 303, 19, 6, 20, 3, 1, 1, 4), 1),
     ((13, 128, 52, 28, 65, 3, 1, 1, 2), 3),
-    ((106, 93, 10, 65, 20, 3, 1, 1, 0), 3),
+    ((106, 93, 10, 65, 20, 3, 1, 1, 0), 4),
     ((16, 32, 43, 50, 65, 3, 3, 1, 0), 0),   # one channel past a tile, two K blocks
     ((17, 100, 56, 38, 33, 3, 3, 1, 2), 0),   # a last K block of 4 channels, padding
-    ((22, 100, 44, 11, 65, 3, 3, 1, 3), 1),   # padding as wide as the filter: windows of zeros
-    ((23, 128, 53, 21, 32, 3, 3, 1, 1), 1),
+    ((22, 100, 44, 11, 65, 3, 3, 1, 3), 4),   # padding as wide as the filter: windows of zeros
+    ((23, 128, 53, 21, 32, 3, 3, 1, 1), 4),
     ((22, 40, 16, 58, 65, 3, 3, 1, 3), 2),   # 8 channels at a time: an odd tap against zero pixels
     ((42, 40, 8, 119, 65, 3, 3, 1, 0), 2),
-    ((24, 128, 21, 48, 65, 3, 3, 1, 0), 3),
-    ((80, 44, 9, 76, 20, 3, 3, 1, 1), 3),
+    ((24, 128, 21, 48, 65, 3, 3, 1, 0), 4),
+    ((80, 44, 9, 76, 20, 3, 3, 1, 1), 4),
     ((23, 16, 46, 38, 33, 4, 4, 1, 4), 0),
-    ((38, 38, 12, 124, 20, 4, 4, 1, 0), 0),
+    ((38, 38, 12, 124, 20, 4, 4, 1, 0), 4),
     ((11, 47, 32, 62, 20, 4, 4, 1, 2), 1),
     ((19, 64, 59, 51, 33, 4, 4, 2, 4), 1),
     ((65, 60, 14, 105, 20, 4, 4, 2, 0), 1),
-    ((107, 48, 9, 44, 65, 4, 4, 2, 2), 2),
-    ((64, 63, 56, 51, 20, 4, 4, 3, 2), 2),
-    ((119, 75, 15, 68, 20, 4, 4, 3, 4), 2),
-    ((24, 32, 48, 50, 65, 4, 4, 2, 4), 3),
+    ((107, 48, 9, 44, 65, 4, 4, 2, 2), 1),
+    ((64, 63, 56, 51, 20, 4, 4, 3, 2), 1),
+    ((119, 75, 15, 68, 20, 4, 4, 3, 4), 1),
+    ((24, 32, 48, 50, 65, 4, 4, 2, 4), 4),
     ((65, 24, 14, 113, 65, 4, 4, 2, 2), 3),
-    ((1, 46, 98, 114, 130, 5, 5, 1, 4), 0),
-    ((11, 32, 46, 32, 32, 5, 5, 1, 3), 1),
-    ((54, 45, 9, 41, 33, 5, 5, 1, 2), 1),
-    ((11, 40, 60, 36, 65, 5, 5, 1, 0), 2),
+    ((1, 46, 98, 114, 130, 5, 5, 1, 4), 4),
+    ((11, 32, 46, 32, 32, 5, 5, 1, 3), 4),
+    ((54, 45, 9, 41, 33, 5, 5, 1, 2), 4),
+    ((11, 40, 60, 36, 65, 5, 5, 1, 0), 4),
     ((21, 8, 59, 57, 65, 5, 5, 1, 4), 2),   # one K block per tile
-    ((21, 16, 47, 38, 32, 5, 5, 1, 3), 3),
-    ((65, 16, 7, 70, 20, 5, 5, 1, 3), 3),
-    ((17, 42, 42, 78, 20, 7, 1, 1, 2), 0),
+    ((21, 16, 47, 38, 32, 5, 5, 1, 3), 4),
+    ((65, 16, 7, 70, 20, 5, 5, 1, 3), 4),
+    ((17, 42, 42, 78, 20, 7, 1, 1, 2), 4),
     ((19, 64, 31, 49, 33, 7, 1, 1, 4), 0),
-    ((2, 139, 102, 80, 20, 7, 1, 1, 3), 1),
-    ((26, 120, 9, 78, 20, 7, 1, 1, 3), 1),
-    ((31, 144, 5, 51, 65, 7, 1, 1, 3), 2),
-    ((21, 128, 60, 49, 32, 7, 1, 2, 2), 2),
-    ((49, 107, 86, 23, 20, 7, 1, 2, 1), 2),
-    ((10, 42, 75, 58, 20, 7, 1, 1, 4), 3),
-    ((94, 43, 8, 66, 20, 7, 1, 1, 3), 3),
-    ((19, 8, 55, 49, 32, 7, 7, 1, 1), 0),
-    ((83, 14, 11, 60, 65, 7, 7, 1, 2), 0),
-    ((20, 40, 52, 8, 65, 7, 7, 1, 3), 1),
-    ((91, 16, 5, 53, 20, 7, 7, 1, 3), 1),
-    ((21, 40, 55, 26, 65, 7, 7, 2, 4), 2),   # stride 2
-    ((24, 16, 42, 43, 65, 7, 7, 2, 2), 2),
-    ((58, 34, 87, 52, 20, 7, 7, 3, 1), 2),
-    ((81, 8, 12, 100, 20, 7, 7, 1, 0), 3),
+    ((2, 139, 102, 80, 20, 7, 1, 1, 3), 4),
+    ((26, 120, 9, 78, 20, 7, 1, 1, 3), 4),
+    ((31, 144, 5, 51, 65, 7, 1, 1, 3), 1),
+    ((21, 128, 60, 49, 32, 7, 1, 2, 2), 1),
+    ((49, 107, 86, 23, 20, 7, 1, 2, 1), 1),
+    ((10, 42, 75, 58, 20, 7, 1, 1, 4), 4),
+    ((94, 43, 8, 66, 20, 7, 1, 1, 3), 4),
+    ((19, 8, 55, 49, 32, 7, 7, 1, 1), 4),
+    ((83, 14, 11, 60, 65, 7, 7, 1, 2), 4),
+    ((20, 40, 52, 8, 65, 7, 7, 1, 3), 4),
+    ((91, 16, 5, 53, 20, 7, 7, 1, 3), 4),
+    ((21, 40, 55, 26, 65, 7, 7, 2, 4), 1),   # stride 2
+    ((24, 16, 42, 43, 65, 7, 7, 2, 2), 1),
+    ((58, 34, 87, 52, 20, 7, 7, 3, 1), 1),
+    ((81, 8, 12, 100, 20, 7, 7, 1, 0), 4),
     ((48, 7, 39, 96, 33, 7, 7, 2, 4), 3),
     ((67, 18, 27, 81, 20, 7, 7, 2, 4), 3),
     # strips of unequal width, the last with fewer tiles than the others (5, 7 and 3 strips; 43 tiles of 49, 12 of 15, 28 of 31)
-    ((38, 33, 22, 73, 65, 3, 3, 1, 1), 2),
+    ((38, 33, 22, 73, 65, 3, 3, 1, 1), 4),
     ((11, 18, 23, 102, 65, 5, 5, 1, 2), 2),
     ((22, 18, 49, 81, 65, 7, 7, 2, 3), 3),
+    ((1, 9, 105, 121, 200, 5, 5, 1, 2), 0),
+    ((1, 13, 97, 69, 300, 5, 5, 1, 2), 0),
+    ((62, 120, 41, 21, 64, 1, 3, 1, 4), 1),
+    ((65, 113, 12, 20, 33, 1, 3, 1, 1), 1),
+    ((69, 128, 5, 90, 64, 1, 3, 1, 1), 3),
+    ((15, 65, 70, 31, 65, 1, 7, 1, 0), 0),
+    ((45, 68, 10, 36, 100, 1, 7, 1, 0), 1),
+    ((39, 15, 50, 6, 130, 1, 7, 1, 4), 3),
+    ((33, 35, 60, 14, 200, 1, 7, 1, 0), 3),
+    ((2, 124, 5, 9, 100, 3, 1, 3, 0), 1),
+    ((49, 239, 42, 13, 33, 3, 1, 1, 1), 1),
+    ((37, 99, 26, 117, 33, 3, 1, 1, 2), 3),
+    ((14, 184, 45, 46, 130, 3, 1, 1, 0), 3),
+    ((40, 47, 42, 18, 64, 3, 3, 1, 0), 1),
+    ((7, 78, 24, 30, 300, 3, 3, 1, 2), 1),
+    ((6, 31, 8, 5, 65, 3, 3, 3, 1), 1),
+    ((50, 10, 8, 50, 200, 3, 3, 1, 0), 3),
+    ((43, 14, 16, 103, 64, 3, 3, 1, 0), 3),
+    ((36, 65, 44, 12, 130, 3, 3, 1, 2), 4),
+    ((2, 60, 6, 12, 20, 3, 3, 3, 0), 1),
+    ((23, 30, 54, 18, 130, 4, 4, 1, 0), 0),
+    ((51, 21, 19, 112, 200, 4, 4, 2, 2), 3),
+    ((8, 24, 5, 39, 64, 4, 4, 3, 0), 1),
+    ((9, 81, 60, 8, 100, 5, 5, 2, 4), 1),
+    ((1, 15, 25, 6, 300, 5, 5, 3, 3), 4),
+    ((9, 18, 41, 92, 33, 5, 5, 1, 4), 2),
+    ((31, 11, 30, 31, 65, 5, 5, 1, 1), 3),
+    ((43, 42, 27, 32, 33, 5, 5, 1, 2), 3),
+    ((1, 30, 12, 9, 64, 5, 5, 2, 1), 4),
+    ((26, 37, 39, 100, 64, 7, 1, 1, 2), 0),
+    ((83, 47, 27, 26, 33, 7, 1, 1, 0), 3),
+    ((9, 57, 47, 59, 65, 7, 1, 1, 1), 3),
+    ((13, 7, 38, 64, 33, 7, 7, 1, 4), 0),
+    ((83, 12, 12, 32, 65, 7, 7, 1, 2), 0),
+    ((8, 95, 9, 57, 200, 7, 7, 2, 0), 3),
+    ((54, 15, 37, 22, 200, 7, 7, 2, 1), 3),
+    ((2, 8, 47, 11, 20, 7, 7, 3, 0), 4),
+    ((1, 114, 17, 22, 200, 7, 7, 2, 3), 4),
 ]
+
+
+OTHER_SHAPES = [(7, 78, 24, 30, 300, 3, 3, 1, 2), (43, 14, 16, 103, 64, 3, 3, 1, 0), (83, 47, 27, 26, 33, 7, 1, 1, 0)]   # narrow tiles, larger patches
 
 
 @pytest.mark.parametrize("shape,cfg", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
@@ -219,12 +260,12 @@ def _assert_like_basic(shape, I, F):
     return ref
 
 
-@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)] + OTHER_SHAPES, ids=lambda v: "x".join(map(str, v)))
 def test_buffers_of_any_alignment(shape):
     check_any_alignment(shape, 9315)
 
 
-@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (9, 18, 20, 22, 24, 29)] + OTHER_SHAPES, ids=lambda v: "x".join(map(str, v)))
 def test_the_second_pass_writes_what_the_first_left(shape):
     check_second_pass(shape, 9310)
 
