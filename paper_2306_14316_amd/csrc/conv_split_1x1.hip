@@ -8,6 +8,8 @@
 // round (see conv_split_stem.hip).  K blocks of 32 channels, two LDS stages, one barrier per block; a workgroup runs its tiles as one
 // sequence of K blocks, so the next tile's first block is on its way while a tile ends.
 //
+// A channel count that is no multiple of eight leaves the last group's missing words zero (RAG: a select per word).
+//
 // Measured (convolution alone, us, fp32 matrix cores -> tiles of 128 -> of 256 pixels): 256 -> 256 channels 28x28 N=64 62 -> 51 -> 44, 512 -> 512
 // 14x14 N=32 37 -> 25 -> 35, N=128 112 -> 92 -> 75, 56x56 N=64 940 -> 627 -> 550 (191 TFLOP/s); 1024 -> 256 14x14 N=64 70 -> 44 -> 63.  A lone tile
 // of 128 pixels takes 1.3 us for a K block whose MFMAs take 0.65: a wave's own chain of cutting, writing and reading; of 256 pixels 1.85 for
@@ -40,7 +42,8 @@ struct Tile1x1 {
     static constexpr size_t LDS = PASS + 64;
 };
 
-template <int FN, bool IMP>
+// RAG: Ci is no multiple of eight.
+template <int FN, bool RAG, bool IMP>
 __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P)
 {
     using T = Tile1x1<FN>;
@@ -85,15 +88,20 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
     };
     auto fetch = [&]() __attribute__((always_inline)) {   // the block (ft, fkb); then the one after it, or the last again
         const int c0 = fkb * 32;
-        const uint32_t vo = c0 + ag * 8 < P.Ci ? fvo : kNoWord;
+        const int room = P.Ci - c0;
+        const uint32_t vo = ag * 8 < room ? fvo : kNoWord;
         const u32v4 a0 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u, 0), a1 = __builtin_amdgcn_raw_buffer_load_b128(rf, vo, (uint32_t)c0 * 4u + 16u, 0);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { const uint32_t w = e < 4 ? a0[e & 3] : a1[e & 3]; wa[e] = __builtin_bit_cast(float, w); }
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t w = e < 4 ? a0[e & 3] : a1[e & 3];
+            wa[e] = __builtin_bit_cast(float, !RAG || ag * 8 + e < room ? w : 0u);   // (the words behind a row's last are the next row's)
+        }
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            const uint32_t bo = c0 + (bg + j * (4 / FN)) * 8 < P.Ci ? bvo[j] : kNoWord;
+            const int c = (bg + j * (4 / FN)) * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) wb[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, bo, (uint32_t)(c0 + e) * P.plane * 4u, 0));
+            for (int e = 0; e < 8; ++e)
+                wb[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, c + (RAG ? e : 0) < room ? bvo[j] : kNoWord, (uint32_t)(c0 + e) * P.plane * 4u, 0));
         }
         if (++fkb == P.nkb) {
             if (ft + gx < stop) { ft += gx; aim(ft); fkb = 0; }
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(512, 2) void conv_split_1x1_kernel(Split1x1Params P
     pass(std::true_type{});
 }
 
-template <int FN>
+template <int FN, bool RAG>
 static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu, hipStream_t st, LaunchPlan *plan)
 {
     using T = Tile1x1<FN>;
@@ -270,10 +278,10 @@ static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu
     P.ntiles = ((P.npix + T::TN - 1) / T::TN) * (uint32_t)P.tiles_m;
     const uint32_t grid = std::min(P.ntiles, (uint32_t)ncu);   // one workgroup per compute unit; it takes every grid-th tile
     if (plan) {
-        plan_record(plan, dim3(grid), 512, T::LDS, "conv_split_1x1_kernel<%d, %s>", FN, tf(implicit));
+        plan_record(plan, dim3(grid), 512, T::LDS, "conv_split_1x1_kernel<%d, %s, %s>", FN, tf(RAG), tf(implicit));
         return hipSuccess;
     }
-    void (*kern)(Split1x1Params) = implicit ? &conv_split_1x1_kernel<FN, true> : &conv_split_1x1_kernel<FN, false>;
+    void (*kern)(Split1x1Params) = implicit ? &conv_split_1x1_kernel<FN, RAG, true> : &conv_split_1x1_kernel<FN, RAG, false>;
     static KernelCache kc[2];
     const hipError_t e = allow_dynamic_lds(kc[implicit], reinterpret_cast<const void *>(kern), T::LDS, dev);
     if (e != hipSuccess) return e;
@@ -284,7 +292,7 @@ static hipError_t launch_1x1_t(Split1x1Params P, bool implicit, int dev, int ncu
 // hipErrorNotSupported where the fp32 kernel (conv_mfma_1x1.hip) is the faster one or the layer is outside its conditions.
 hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out, const Shape &sh, hipStream_t st, bool implicit, LaunchPlan *plan)
 {
-    if (sh.Hf != 1 || sh.Wf != 1 || sh.p != 0 || sh.Ci % 8 != 0) return hipErrorNotSupported;
+    if (sh.Hf != 1 || sh.Wf != 1 || sh.p != 0) return hipErrorNotSupported;
     int dev = 0, ncu = 0;
     hipError_t e = device_cus(&dev, &ncu);
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
@@ -299,27 +307,32 @@ hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out,
     P.src_elems = (size_t)sh.N * sh.Ci * P.plane; P.out_elems = (size_t)sh.npix * sh.Co;
     P.d_wo = make_fastdiv((uint32_t)sh.Wo); P.d_howo = make_fastdiv(P.howo);
     if (sh.s > 65536) return hipErrorNotSupported;
-    // Which is faster, in us: rounds of tiles (a last round that leaves units idle runs at a higher clock: half of the loss is made up) at 1.6 for a
-    // K block and 2 for a tile of 128 pixels, 2.55 and 6 of 256; the fp32 kernel's 64-channel tiles at 115 TFLOP/s (channel counts that the fp32
-    // 1x1 kernel does not take run the generic one there, at 50).  Measured, fp32 / 128 / 256 pixels, the one that runs in brackets: 256 -> 256 28x28
-    // N=64 62 / 51 / [44], 14x14 N=32 [12.7] / 14.4 / 21, N=128 34 / 27 / [25]; 512 -> 512 14x14 N=32 37 / [25] / 35, N=64 64 / 45 / [39], N=128 112 / 92 /
-    // [75], 56x56 N=64 940 / 627 / [550]; 1024 -> 256 14x14 N=32 [40] / 42 / 61, N=64 70 / [44] / 63, N=128 122 / 85 / [70]; 256 -> 256 56x56 N=64 248 / 164 /
-    // [160]; 128 -> 129 30x33 N=64 79 / 29 / [27]; 256 -> 64 56x56 N=8 [12.5] / 14.7 / 21.  With short K loops the estimates of the pieces are too high
-    // (64 -> 256 56x56 N=64 68 / 75 for [70] / 59 / 58): such layers stay on the fp32 kernel where that is the slower one.  1000 layers that it takes,
-    // half of them strided: in two calls none is more than 3 % slower, workspace-free five strided ones 4 to 15 % (N=61 1408 -> 1024 88x31 stride 4,
-    // 364 / [421]; 238 against 283 in two calls).
-    auto time = [&](int tn, double block, double tile) {
-        const double r = (double)((P.npix + tn - 1) / tn) * ((sh.Co + 127) / 128) / ncu;
-        return 2.0 + 0.5 * (r + (double)(long long)(r + 0.999)) * (P.nkb * block + tile);
+    // Which is faster, in us: fitted to 1300 layers, the pieces' tiles of 128 and 256 pixels 6 and 8 % off (root mean square), the fp32 kernel's 13 %
+    // (the pick takes 1.002 times the best one's time on average).  `mix`: how far a last round that leaves units idle counts in full.  Layers that
+    // the fp32 1x1 kernel does not take (Ci no multiple of 8, Co none of 4) ran the generic kernels, which take up to eight times as long:
+    // in us, generic two calls / workspace-free / pieces: 43 -> 100 channels 28x28 N=29 28 / 27 / 8.6, 285 -> 94 8x5 N=58 20 / 126 / 16, 870 -> 102
+    // 16x16 stride 2 N=8 59 / 391 / 40, 226 -> 19 44x44 N=6 16 / 93 / 15; up to four channels they are as fast.  Measured, fp32 / 128 / 256 pixels, the
+    // one that runs in brackets: 256 -> 256 28x28 N=64 62 / 51 / [44], 14x14 N=32 [12.7] / 14.4 / 21, N=128 34 / 27 / [25]; 512 -> 512 14x14 N=32
+    // 37 / [25] / 35, N=64 64 / 45 / [39], N=128 112 / 92 / [75], 56x56 N=64 940 / 627 / [550]; 1024 -> 256 14x14 N=64 70 / [44] / 63, N=128 122 / 85 / [70].
+    auto rounds = [&](double r, double mix) {
+        const double up = (double)(long long)(r + 0.9999);
+        return mix * up + (1.0 - mix) * std::max(r, up > 1.5 ? 0.0 : 0.6);
     };
-    const double t1 = time(128, 1.6, 2.0), t2 = time(256, 2.55, 6.0);
-    const double fp32 = 3.0 + 2.0 * P.npix * ((sh.Co + 63) / 64 * 64.0) * sh.Ci / (sh.Co % 4 == 0 ? 115e6 : 50e6);
-    if (sh.Co <= 64 || std::min(t1, t2) > 0.95 * fp32) return hipErrorNotSupported;
+    auto tiles = [&](int tm, int tn) { return (double)((P.npix + tn - 1) / tn) * ((sh.Co + tm - 1) / tm) / ncu; };
+    const bool ragged = sh.Ci % 8 != 0, fp32 = !ragged && sh.Co % 4 == 0;
+    const double t1 = 3.15 + rounds(tiles(128, 128), 0.45) * (P.nkb * (ragged ? 1.58 : 1.47) + 2.2);
+    const double t2 = 3.65 + rounds(tiles(128, 256), 0.45) * (P.nkb * (ragged ? 2.49 : 2.33) + (ragged ? 5.65 : 5.1));
+    if (fp32) {
+        const double r = tiles(64, 64), up = (double)(long long)(r + 0.9999);
+        if (std::min(t1, t2) > 0.9 * (3.56 + (0.25 * up + 0.75 * std::max(r, up > 1.5 ? 0.0 : 1.0)) * (sh.Ci * 0.0213 + 0.28))) return hipErrorNotSupported;
+    } else if (sh.Ci <= 4) {
+        return hipErrorNotSupported;
+    }
     if (t2 < t1) {
-        e = launch_1x1_t<2>(P, implicit, dev, ncu, st, plan);
+        e = sh.Ci % 8 ? launch_1x1_t<2, true>(P, implicit, dev, ncu, st, plan) : launch_1x1_t<2, false>(P, implicit, dev, ncu, st, plan);
         if (e != hipErrorNotSupported) return e;
     }
-    return launch_1x1_t<1>(P, implicit, dev, ncu, st, plan);
+    return sh.Ci % 8 ? launch_1x1_t<1, true>(P, implicit, dev, ncu, st, plan) : launch_1x1_t<1, false>(P, implicit, dev, ncu, st, plan);
 }
 
 }  // namespace im2win

@@ -23,6 +23,12 @@ SHAPES = [
     ((67, 384, 20, 19, 385, 1, 1, 1, 0), 2),     # one channel past a tile
     ((21000, 256, 1, 1, 256, 1, 1, 1, 0), 2),    # a tile spans 256 images
     ((64, 128, 30, 33, 129, 1, 1, 1, 0), 2),     # several tiles per workgroup
+    ((29, 43, 28, 30, 100, 1, 1, 1, 0), 1),      # channels that are no multiple of eight: 11 in the last K block, one tile of 128 channels
+    ((3, 5, 16, 15, 20, 1, 1, 1, 0), 1),         # five channels
+    ((58, 33, 9, 5, 94, 1, 1, 2, 0), 1),         # one channel in the last K block, stride 2
+    ((40, 127, 57, 55, 200, 1, 1, 2, 0), 2),     # 31 of 32 in the last K block, stride 2
+    ((64, 77, 40, 41, 33, 1, 1, 1, 0), 2),
+    ((31, 72, 20, 21, 66, 1, 1, 1, 0), 1),       # output channels that are no multiple of four
 ]
 
 
@@ -30,7 +36,7 @@ SHAPES = [
 def test_both_calls(shape, runs):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     for w in (False, True):
-        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == "conv_split_1x1_kernel<%d, %s>" % (runs, "true" if w else "false")
+        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == "conv_split_1x1_kernel<%d, %s, %s>" % (runs, *("true" if q else "false" for q in (Ci % 8, w)))
     I, F = workloads.random_layer_inputs(9950 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
     got, fp32 = _run(shape, I, F)
@@ -40,7 +46,7 @@ def test_both_calls(shape, runs):
     assert l2 <= l2_32
 
 
-@pytest.mark.parametrize("shape", [SHAPES[2][0], SHAPES[8][0]], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [SHAPES[2][0], SHAPES[8][0], SHAPES[9][0], SHAPES[12][0]], ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("ei,ef", [(-118, 4), (4, -124), (-140, 20), (105, 0), (-120, 120), (60, 60)])
 def test_no_operand_loses_bits(shape, ei, ef):
     """The 24 bits of an operand hold whatever its magnitude: against 64 bits no further off than the fp32 kernel."""
@@ -52,12 +58,12 @@ def test_no_operand_loses_bits(shape, ei, ef):
     assert conv_errors(got, O_ref, B_ref)[1] <= 1.1 * conv_errors(fp32, O_ref, B_ref)[1]
 
 
-@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (2, 3, 5, 8)], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[i][0] for i in (2, 3, 5, 8, 9, 12)], ids=lambda v: "x".join(map(str, v)))
 def test_buffers_of_any_alignment(shape):
     check_any_alignment(shape, 9985)
 
 
-@pytest.mark.parametrize("shape", [SHAPES[1][0], SHAPES[2][0], SHAPES[5][0], SHAPES[8][0]], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [SHAPES[1][0], SHAPES[2][0], SHAPES[5][0], SHAPES[8][0], SHAPES[9][0], SHAPES[12][0]], ids=lambda s: "x".join(map(str, s)))
 def test_the_second_pass_writes_what_the_first_left(shape):
     check_second_pass(shape, 9980)
 

@@ -182,5 +182,5 @@ def test_one_by_one_layers():
         assert split[0] == split[1], (shape, plans)
         if split[0]:
             taken += 1
-            assert p == 0 and Ci % 8 == 0 and Co > 64 and plans[0]["grid"] == plans[1]["grid"] and plans[0]["lds_bytes"] <= 160 * 1024
+            assert p == 0 and Ci > 4 and plans[0]["grid"] == plans[1]["grid"] and plans[0]["lds_bytes"] <= 160 * 1024
     assert taken > 500
