@@ -203,35 +203,39 @@ __device__ __forceinline__ void tail_piece(const MfmaParams &P, uint32_t lt, int
 // RAG: Ci is not a multiple of CB.  The last K block then holds Ci % CB real channels; the words
 // of the missing ones -- strip words and filter columns, whatever the loads brought in from the
 // neighbouring channel planes and filter rows -- are replaced by +0.0 when that block is written
-// to LDS, so the MFMA loop itself is unchanged.  (Whole tiles only: not combined with PER, TAIL, HALF.)
-template <int HF, int WF, int CB, int JX, int CW, int OCC, bool IMP, bool PER, bool TAIL, bool HALF = false, bool RAG = false>
-__global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
+// to LDS, so the MFMA loop itself is unchanged.  (Whole tiles and halves: not combined with PER, TAIL.)
+// QUART: every workgroup takes a tile of 32 channels x 32 pixels, staged and pipelined like a half tile, and its four waves a quarter of
+// the channel pairs of every K block each; the four partial sums meet in LDS.  For layers that would leave most of the compute units idle.
+template <int HF, int WF, int CB, int JX, int CW, bool IMP, bool PER, bool TAIL, bool HALF, bool RAG, bool QUART>
+__device__ __forceinline__ void conv_mfma_fast_body(const MfmaParams &P)
 {
+    constexpr int MT = QUART ? 32 : MB, NT = QUART ? 32 : NB;   // channels and pixels of a tile
     constexpr int KHW = HF * WF;
     constexpr int KB = CB * KHW;            // K elements per block
     constexpr int CPR = KB / CW;            // chunks per filter row per block
-    constexpr int NFC = MB * CPR;           // chunks per filter tile
+    constexpr int NFC = MT * CPR;           // chunks per filter tile
     constexpr int JF = (NFC + 255) / 256;   // chunks per thread
     constexpr int PF = KB | 1;              // odd LDS pitch of a filter row
     constexpr int SS = 256 * JX;            // LDS floats per channel strip (compile-time stride)
-    constexpr int SF_FLOATS = (MB * PF + 3) & ~3;
+    constexpr int SF_FLOATS = (MT * PF + 3) & ~3;
     constexpr int STAGE = SF_FLOATS + CB * SS;   // floats per LDS stage
-    constexpr int R = HALF ? pick_ring_half((CB / 2) * KHW) : pick_ring((CB / 2) * KHW);
+    constexpr int R = QUART ? 3 : HALF ? pick_ring_half((CB / 2) * KHW) : pick_ring((CB / 2) * KHW);
     static_assert(R > 0, "no ring length divides the MFMAs per block");
     static_assert(CW == 4 || CW == 2 || CW == 1, "chunks are 16, 8 or 4 bytes");
     static_assert(KB % CW == 0, "K block must be a whole number of chunks");
     static_assert(CB % 2 == 0, "pair steps need an even channel count");
-    static_assert(!RAG || (!PER && !TAIL && !HALF), "a ragged last K block comes with whole tiles only");
+    static_assert(!RAG || (!PER && !TAIL), "a ragged last K block comes with whole tiles and halves only");
 
-    // two LDS stages, each [filter tile MB x PF][CB strips of SS floats]
+    // two LDS stages, each [filter tile MT x PF][CB strips of SS floats]
     extern __shared__ __align__(16) unsigned char smem[];
     float *lds = reinterpret_cast<float *>(smem);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
+    const int wm = QUART ? 0 : wave & 1, wn = wave >> 1;
     const int h = lane >> 5, l32 = lane & 31;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);   // the same, known to be wave-uniform
     const int wm_u = wave_u & 1, wn_u = wave_u >> 1;
+    static_assert(!QUART || (HALF && !PER && !TAIL && CB % 8 == 0 && KHW % 3 == 0), "quarter tiles: two channels of every K block to a wave");
     static_assert(!HALF || (!PER && (CB / 2) % 2 == 0),
                   "half tiles: the channel pairs of a K block split evenly between two waves");
     // half-tile workgroups: which tile, which half; waves 0/1 take the first half of the channel
@@ -245,11 +249,12 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         if (bid >= P.tail_at && bid < P.tail_at + npb) bid = end_main + (bid - P.tail_at);
         else if (bid >= P.tail_at + npb) bid -= npb;
     }
-    const bool hmode = HALF && bid >= P.nmain && bid < P.nmain + 2u * P.nhalf;   // workgroup-uniform
-    const uint32_t vb_first = hmode ? P.nmain + ((bid - P.nmain) >> 1) : bid;
-    const int hpix = hmode ? (int)((bid - P.nmain) & 1u) * 32 : 0;   // first pixel of the half, within the tile
+    const bool hmode = QUART || (HALF && bid >= P.nmain && bid < P.nmain + 2u * P.nhalf);   // workgroup-uniform
+    const uint32_t vb_first = !QUART && hmode ? P.nmain + ((bid - P.nmain) >> 1) : bid;
+    const int hpix = !QUART && hmode ? (int)((bid - P.nmain) & 1u) * 32 : 0;   // first pixel of the half, within the tile
     const int wn_g = hmode ? 0 : wn;             // pixel block of the wave within the (half) tile
-    const int hk = hmode ? (wave >> 1) : 0, hk_u = hmode ? (wave_u >> 1) : 0;
+    constexpr int PARTS = QUART ? 4 : 2;          // waves that share a block of outputs (half and quarter tiles)
+    const int hk = QUART ? wave : hmode ? (wave >> 1) : 0, hk_u = hmode ? (wave_u >> 1) : 0;
 
     if constexpr (TAIL) if (bid >= P.nmain + 2u * P.nhalf) {
         // Piece q of leftover tile t.  Workgroup b runs on XCD b % 8 and the pieces start at a
@@ -300,13 +305,13 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
     auto tile_geometry = [&](uint32_t vb, uint32_t &P0, uint32_t &Pend, int &m0, const lds_float *&bp,
                              uint32_t (&soffb)[JX], int (&loffI)[JX], uint32_t &zero,
                              __amdgpu_buffer_rsrc_t &rf, __amdgpu_buffer_rsrc_t &rw) __attribute__((always_inline)) {
-        const uint32_t lb = (TAIL || HALF) ? (vb < P.nmain ? xcd_swizzle(vb, P.nmain) : vb) : xcd_swizzle(vb, ntiles);
+        const uint32_t lb = (TAIL || HALF) && !QUART ? (vb < P.nmain ? xcd_swizzle(vb, P.nmain) : vb) : xcd_swizzle(vb, ntiles);
         const uint32_t tile_n = fdiv(lb, P.d_tm);
         const uint32_t tile_m = lb - tile_n * (uint32_t)P.tiles_m;
-        m0 = (int)tile_m * MB;
-        P0 = tile_n * NB;
-        Pend = min(P0 + NB - 1, P.npix - 1);
-        if (HALF && hmode) {   // the half's own 32 pixels (the caller has checked that it has any)
+        m0 = (int)tile_m * MT;
+        P0 = tile_n * NT;
+        Pend = min(P0 + NT - 1, P.npix - 1);
+        if (HALF && !QUART && hmode) {   // the half's own 32 pixels (the caller has checked that it has any)
             P0 += (uint32_t)hpix;
             Pend = min(P0 + 31u, Pend);
         }
@@ -369,9 +374,9 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         const int nl = (int)(Pl - ql * (uint32_t)P.Wo);
         const int rhol = (int)(ql - q0);
         const int b_base = rhol == 0 ? (nl - nlo0) * sHf : len0 + (rhol - 1) * P.fullseg + nl * sHf;
-        bp = (const lds_float *)lds + SF_FLOATS + b_base + h * SS + hk * ((CB / 2) * SS);
+        bp = (const lds_float *)lds + SF_FLOATS + b_base + h * SS + hk * ((CB / PARTS) * SS);
     };
-    if (HALF && hmode) {   // a ragged last tile may have no pixel in its second half (whole workgroup)
+    if (HALF && !QUART && hmode) {   // a ragged last tile may have no pixel in its second half (whole workgroup)
         const uint32_t tn = fdiv(vb_first, P.d_tm);
         if (tn * NB + (uint32_t)hpix >= P.npix) return;
     }
@@ -401,7 +406,7 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
     }
 
     // ---- filter staging coordinates of this thread's chunks ----
-    // The tile is MB rows x CPR chunks of CW floats.  Chunk columns are dealt out
+    // The tile is MT rows x CPR chunks of CW floats.  Chunk columns are dealt out
     // so that each dword LDS write of a half-wave is conflict-free with the odd
     // row pitch: a half-wave covers CW consecutive rows x 32/CW chunk columns
     // (128 contiguous bytes per row in global memory); the CPR % (32/CW) leftover
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
     // Rows past Co feed accumulators that are never stored; they reload row 0.
     constexpr int COLS = 32 / CW;              // chunk columns per half-wave
     constexpr int CG = CPR / COLS;             // full column groups
-    constexpr int NMAIN = MB * CG * COLS;      // chunks in full groups
+    constexpr int NMAIN = MT * CG * COLS;      // chunks in full groups
     uint32_t goffb[JF];
     int loff[JF];
 #pragma unroll
@@ -422,8 +427,8 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
             cc = COLS * (g % (CG > 0 ? CG : 1)) + (w % COLS);
         } else {
             const int r = f - NMAIN;
-            row = r % MB;
-            cc = CG * COLS + r / MB;
+            row = r % MT;
+            cc = CG * COLS + r / MT;
         }
         const int e = cc * CW;
         const bool live = (f < NFC) && (m0 + row < P.Co);
@@ -445,7 +450,7 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         }
     }
 
-    const lds_float *ap0 = (const lds_float *)lds + (wm * 32 + l32) * PF + h * KHW + hk * ((CB / 2) * KHW);
+    const lds_float *ap0 = (const lds_float *)lds + (wm * 32 + l32) * PF + h * KHW + hk * ((CB / PARTS) * KHW);
     float *wI0 = lds + SF_FLOATS + tid;
 
     floatx16 acc;
@@ -499,7 +504,7 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
     constexpr int NFW = HPC * JF;         // filter store slots
     constexpr int NIW = CB * JX;          // strip stores / loads
     constexpr int NIWS = (NIW + 1) / 2;   // slots that store strip words (two each)
-    static_assert(NM > R && NSLOT - NFW - NIWS > 0, "K block too short for the pipeline");
+    static_assert(QUART || (NM > R && NSLOT - NFW - NIWS > 0), "K block too short for the pipeline");
     constexpr int LPS = (NIW + (NSLOT - NFW - NIWS) - 1) / (NSLOT - NFW - NIWS);   // strip loads per slot
     constexpr int NILS = (NIW + LPS - 1) / LPS;                                      // slots that load strip words
     static_assert(NFW + NIWS + NILS <= NSLOT, "staging work must fit before the barrier");
@@ -606,9 +611,9 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
 #pragma unroll
     for (int i = 0; i < R; ++i) lds_op(0, i, bp_c);
 
-    // ---- half tile: the same pipeline with half of the MFMA steps per K block ----
+    // ---- half or quarter tile: the same pipeline with half or a quarter of the MFMA steps per K block ----
     if constexpr (HALF) if (hmode) {
-        constexpr int NMH = NM / 2;          // this wave's MFMAs per block: its half of the channel pairs
+        constexpr int NMH = NM / PARTS;      // this wave's MFMAs per block: its half or quarter of the channel pairs
         constexpr int NSLOTH = NMH - R;      // MFMAs before the barrier
         constexpr int NITEM = NFW + NIWS + NIW;              // staging items: filter half-stores, strip stores (two each), strip loads
         constexpr int IPS = (NITEM + NSLOTH - 1) / NSLOTH;   // items per slot
@@ -616,6 +621,7 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         auto block_half = [&](int kb2, auto stc, auto has1c, auto has2c) __attribute__((always_inline)) {
             constexpr int ST = decltype(stc)::value;
             constexpr bool HAS1 = decltype(has1c)::value, HAS2 = decltype(has2c)::value;
+            constexpr bool LAST = RAG && HAS1 && !HAS2;
 #pragma unroll
             for (int i = 0; i < NMH; ++i) {
                 if (HAS1 && i == NSLOTH) __syncthreads();
@@ -626,13 +632,13 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
 #pragma unroll
                     for (int it = i * IPS; it < (i + 1) * IPS && it < NITEM; ++it) {
                         if (it < NFW) {                       // filter chunk it/HPC: store a half, then reload it
-                            if (HAS1) store_f(ST ^ 1, it / HPC, it % HPC);
+                            if (HAS1) store_f(ST ^ 1, it / HPC, it % HPC, LAST);
                             if (HAS2 && (it % HPC == HPC - 1)) load_f(kb2, it / HPC, rf_c);
                         } else if (it < NFW + NIWS) {         // strip words of the next block: two stores
                             if (HAS1) {
                                 const int w = 2 * (it - NFW);
-                                store_i(ST ^ 1, ST ^ 1, w / JX, w % JX, loffI_c, zero_c);
-                                if (w + 1 < NIW) store_i(ST ^ 1, ST ^ 1, (w + 1) / JX, (w + 1) % JX, loffI_c, zero_c);
+                                store_i(ST ^ 1, ST ^ 1, w / JX, w % JX, loffI_c, zero_c, LAST);
+                                if (w + 1 < NIW) store_i(ST ^ 1, ST ^ 1, (w + 1) / JX, (w + 1) % JX, loffI_c, zero_c, LAST);
                             }
                         } else {                              // strip words of the block after that
                             const int w = it - NFW - NIWS;
@@ -659,6 +665,27 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         } else {
             block_half(0, I0{}, F{}, F{});
         }
+        if constexpr (QUART) {
+            // the four partial sums: wave w adds and stores the channels 8w ... 8w+7 of the 32 (its lanes' registers 4w ... 4w+3)
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lds[(v * 4 + wave_u) * 64 + lane] = acc[v];
+            __syncthreads();
+            const float *part = lds + wave_u * (4 * 4 * 64) + lane;
+            const int jw = m0 + 8 * wave_u;
+            if (jw >= P.Co) return;
+            const uint32_t img0 = fdiv(P0_c, P.d_howo), Pm = P0_c + (uint32_t)l32;
+            const __amdgpu_buffer_rsrc_t ro = desc(P.out + ((size_t)img0 * P.Co + (size_t)jw) * P.howo, P.out_elems - ((size_t)img0 * P.Co + (size_t)jw) * P.howo);
+            const uint32_t img = fdiv(min(Pm, Pend_c), P.d_howo), pin = min(Pm, Pend_c) - img * P.howo;
+            const uint32_t voff = ((img - img0) * (uint32_t)P.Co * P.howo + pin + (uint32_t)(4 * h) * P.howo) * 4u;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float sum = (part[v * 256] + part[v * 256 + 64]) + (part[v * 256 + 128] + part[v * 256 + 192]);
+                if (Pm <= Pend_c && v < P.Co - jw - 4 * h)
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sum), ro, voff, (uint32_t)v * P.howo * 4u, 0);
+            }
+            return;
+        }
         // the two partial sums of a block of outputs: waves 2/3 hand theirs to waves 0/1 through
         // LDS (every wave has taken its last operands before the stages are overwritten)
         __syncthreads();
@@ -674,6 +701,8 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
         }
         return;
     }
+
+    if constexpr (QUART) return;
 
     // ---- tiles of this workgroup ----
     // The host gives a workgroup more than one tile only when nkb is even (every tile then
@@ -715,6 +744,39 @@ __global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
     }
 }
 
+template <int HF, int WF, int CB, int JX, int CW, int OCC, bool IMP, bool PER, bool TAIL, bool HALF = false, bool RAG = false>
+__global__ __launch_bounds__(256, OCC) void conv_mfma_fast_kernel(MfmaParams P)
+{
+    conv_mfma_fast_body<HF, WF, CB, JX, CW, IMP, PER, TAIL, HALF, RAG, false>(P);
+}
+
+template <int HF, int WF, int CB, int JX, bool IMP, bool RAG>
+__global__ __launch_bounds__(256, 2) void conv_mfma_quarter_kernel(MfmaParams P)
+{
+    conv_mfma_fast_body<HF, WF, CB, JX, 4, IMP, false, false, true, RAG, true>(P);
+}
+
+// Layers of few tiles, as quarter tiles.
+template <int HF, int WF, int CB, int JX, bool IMP, bool RAG>
+static hipError_t launch_quarter_t(MfmaParams Q, int dev, hipStream_t st, LaunchPlan *plan)
+{
+    constexpr size_t lds = 2u * 4u * (size_t)(((32 * ((CB * HF * WF) | 1) + 3) & ~3) + CB * 256 * JX);
+    static_assert(lds >= 16 * 4 * 64 * 4, "the partial sums fit the stages");
+    Q.tiles_m = (Q.Co + 31) / 32;
+    Q.d_tm = make_fastdiv((uint32_t)Q.tiles_m);
+    Q.nblocks = ((Q.npix + 31) / 32) * (uint32_t)Q.tiles_m;
+    if (plan) {
+        plan_record(plan, dim3(Q.nblocks), 256, lds, "conv_mfma_quarter_kernel<%d, %d, %d, %d, %s, %s>", HF, WF, CB, JX, tf(IMP), tf(RAG));
+        return hipSuccess;
+    }
+    void (*kern)(MfmaParams) = &conv_mfma_quarter_kernel<HF, WF, CB, JX, IMP, RAG>;
+    static KernelCache kc;
+    const hipError_t e = allow_dynamic_lds(kc, reinterpret_cast<const void *>(kern), lds, dev);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(Q.nblocks), dim3(256), lds, st, Q);
+    return hipGetLastError();
+}
+
 template <int HF, int WF, int CB, int JX, int CW, int OCC>
 static hipError_t launch_fast_i(const MfmaParams &P, uint32_t blocks, hipStream_t st, bool implicit, LaunchPlan *plan);
 
@@ -724,23 +786,44 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     constexpr int KB = CB * HF * WF;
     constexpr int PF = KB | 1;
     constexpr size_t lds = 2u * 4u * (size_t)(((MB * PF + 3) & ~3) + CB * 256 * JX);
+    constexpr bool PIECEABLE = HF == 3 && WF == 3 && CB == 8;
+    constexpr bool HALFABLE = PIECEABLE || (HF == 5 && WF == 5 && CB == 4);   // (the 5x5 instance: halves only)
+    // Instances with halves: two workgroups per compute unit, as the half tile's loop has half of the MFMAs to carry the same staging and
+    // holds more of it at once (three, at 168 registers each, spilled 27 to 147 of them).
+    constexpr int OCCH = HALFABLE && OCC > 2 ? 2 : OCC;
+    int dev = 0, ncu = 0;
+    hipError_t e = device_cus(&dev, &ncu);
+    if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
+    if (e != hipSuccess) return e;
+    const uint32_t left = ncu >= 8 && ncu % 8 == 0 ? blocks % (uint32_t)ncu : 0u, eighth = (uint32_t)ncu / 8, halfcu = (uint32_t)ncu / 2;
+    if constexpr (PIECEABLE && CW == 4) {
+        // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths, as far as those have.  Convolution alone, us, two
+        // calls / workspace-free, halves or sixteenths / quarters: 64 -> 64 channels 56x56 (196 quarters) 8.0 / 8.5 / 6.1 / 6.6; 344 -> 29 13x12 N=27
+        // 29.3 / 32.7 / 18.2 / 21.4; 128 -> 128 28x28 (26 tiles) 9.7 / 12.0 / 8.9 / 9.9; 128 -> 256 14x14 (16 tiles) 6.5 / 8.2 / 8.9 / 10.1; 64 -> 64 28x28
+        // N=16 (392 quarters) 11.8 / 12.5 / 13.6 / 14.7.
+        const uint32_t quarters = ((P.npix + 31) / 32) * (uint32_t)((P.Co + 31) / 32);
+        if (quarters <= (uint32_t)ncu && !(P.Ci % 16 == 0 && 16 * blocks <= (uint32_t)ncu))
+            return P.Ci % CB != 0 ? launch_quarter_t<HF, WF, CB, JX, IMP, true>(P, dev, st, plan) : launch_quarter_t<HF, WF, CB, JX, IMP, false>(P, dev, st, plan);
+    }
     if (P.Ci % CB != 0) {
-        // ragged last K block: whole tiles, one per workgroup (only the 16-byte filter-fetch instances exist)
+        // ragged last K block: whole tiles, one per workgroup, and leftover tiles as halves (below; only the 16-byte filter-fetch
+        // instances exist)
         if constexpr (CW == ((HF == 7 && WF == 7) ? 2 : 4)) {
             MfmaParams Q = P;
-            Q.nblocks = blocks; Q.nmain = blocks; Q.nhalf = 0; Q.tail_at = blocks;
+            Q.nblocks = blocks; Q.nhalf = HALFABLE && left <= halfcu ? left : 0u; Q.nmain = blocks - Q.nhalf;
+            const uint32_t grid = Q.nmain + 2 * Q.nhalf;
+            Q.tail_at = grid;
+            const int which = Q.nhalf ? 1 : 0;
             void (*kern)(MfmaParams) = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, false, false, true>;
+            if (which) kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCH, IMP, false, false, HALFABLE, true>;
             if (plan) {
-                plan_record(plan, dim3(blocks), 256, lds, "conv_mfma_fast_kernel<%d, %d, %d, %d, %d, %d, %s, false, false, false, true>",
-                            HF, WF, CB, JX, CW, OCC, tf(IMP));
+                plan_record(plan, dim3(grid), 256, lds, "conv_mfma_fast_kernel<%d, %d, %d, %d, %d, %d, %s, false, false, %s, true>",
+                            HF, WF, CB, JX, CW, which ? OCCH : OCC, tf(IMP), tf(which != 0));
                 return hipSuccess;
             }
-            static KernelCache kcr;
-            int dev = 0;
-            hipError_t e = hipGetDevice(&dev);
-            if (e != hipSuccess) return e;
-            if ((e = allow_dynamic_lds(kcr, reinterpret_cast<const void *>(kern), lds, dev)) != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, Q);
+            static KernelCache kcr[2];
+            if ((e = allow_dynamic_lds(kcr[which], reinterpret_cast<const void *>(kern), lds, dev)) != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, Q);
             return hipGetLastError();
         } else {
             return hipErrorNotSupported;
@@ -756,10 +839,6 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     Q.nblocks = blocks;
     Q.nmain = blocks;
     uint32_t grid = blocks;
-    int dev = 0, ncu = 0;
-    hipError_t e = device_cus(&dev, &ncu);
-    if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
-    if (e != hipSuccess) return e;
     if ((Q.Ci / CB) % 2 == 0 && Q.Ci / CB <= 12 && Q.Co % MB == 0) {
         const uint32_t resident = ((uint32_t)ncu * OCC) & ~7u;
         if (resident >= 8 && blocks >= 3 * resident) grid = resident;
@@ -776,11 +855,8 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     //     into sixteenths, which read their operands without sharing them through LDS: four
     //     times the traffic of a whole tile, but one cold load latency long (measured against
     //     the halves on 64- and 256-channel layers, they win up to 32-44 leftover tiles of 256).
-    constexpr bool PIECEABLE = HF == 3 && WF == 3 && CB == 8;
-    constexpr bool HALFABLE = PIECEABLE || (HF == 5 && WF == 5 && CB == 4);   // (the 5x5 instance: halves only)
     uint32_t nhalf = 0, npiece = 0;
-    if (HALFABLE && grid == blocks && ncu >= 8 && ncu % 8 == 0) {   // (a layer with fewer tiles than compute units is all leftover)
-        const uint32_t left = blocks % (uint32_t)ncu, eighth = (uint32_t)ncu / 8, halfcu = (uint32_t)ncu / 2;
+    if (HALFABLE && grid == blocks) {   // (a layer with fewer tiles than compute units is all leftover)
         const bool pieces_ok = PIECEABLE && Q.Ci % 16 == 0;
         if (pieces_ok && left <= eighth) npiece = left;
         else if (left <= halfcu) nhalf = left;
@@ -794,12 +870,12 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     int which = 0;   // which of this launcher's five kernel instances
     if (grid < blocks) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, true, false>; which = 1; }
     if (npiece && !nhalf) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, PIECEABLE>; which = 2; }
-    if (nhalf && !npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, false, HALFABLE>; which = 3; }
-    if (nhalf && npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, PIECEABLE, HALFABLE>; which = 4; }
+    if (nhalf && !npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCH, IMP, false, false, HALFABLE>; which = 3; }
+    if (nhalf && npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCH, IMP, false, PIECEABLE, HALFABLE>; which = 4; }
     if (plan) {
         const bool per = which == 1, tail = (which == 2 || which == 4) && PIECEABLE, half = (which == 3 || which == 4) && HALFABLE;
         plan_record(plan, dim3(grid), 256, lds, "conv_mfma_fast_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, false>",
-                    HF, WF, CB, JX, CW, OCC, tf(IMP), tf(per), tf(tail), tf(half));
+                    HF, WF, CB, JX, CW, half ? OCCH : OCC, tf(IMP), tf(per), tf(tail), tf(half));
         return hipSuccess;
     }
     static KernelCache kc[5];

@@ -108,18 +108,19 @@ static double fp32_estimate(const MfmaParams &P, const Shape &sh, uint32_t block
     const double r = (double)blocks / ncu, up = (double)((blocks + ncu - 1) / ncu);
     if (P.S > LONGEST) return 4.0 + std::max(0.5 * (r + up), 0.6) * (double)sh.K * 0.055;
     const int nkb = (sh.Ci + CB - 1) / CB;
-    const bool whole = sh.Ci % CB == 0;
+    const bool whole = sh.Ci % CB == 0, pieces = HF == 3 && WF == 3 && sh.Ci % 16 == 0;
+    const double k = (double)(nkb * CB * HF * WF);
+    if (HF == 3 && WF == 3 && (uint32_t)((sh.npix + 31) / 32) * (uint32_t)((sh.Co + 31) / 32) <= (uint32_t)ncu) return 3.4 + k * 0.0048;   // quarter tiles
     double rounds = 0.9 * up + 0.1 * std::max(r, up > 1.5 ? 0.0 : 0.84);
     if (whole && nkb % 2 == 0 && nkb <= 12 && sh.Co % MB == 0 && blocks >= 3 * RESIDENT * (uint32_t)ncu) {
         rounds = r;
-    } else if (whole && HF == WF && (HF == 3 || HF == 5)) {
+    } else if (HF == WF && (HF == 3 || HF == 5)) {
         const uint32_t left = blocks % (uint32_t)ncu;
-        const bool pieces = HF == 3 && sh.Ci % 16 == 0;
         if (pieces && left <= (uint32_t)ncu / 8) rounds = (double)(blocks / ncu) + (left ? 0.42 : 0.0);
         else if (left <= (uint32_t)ncu / 2) rounds = (double)(blocks / ncu) + (left ? 0.55 : 0.0);
         else if (pieces && left <= (uint32_t)(ncu / 2 + ncu / 8)) rounds = (double)(blocks / ncu) + 0.65;
     }
-    return 3.75 + rounds * ((double)(nkb * CB * HF * WF) * 0.0151 + 0.92);
+    return 3.75 + rounds * (k * 0.0151 + 0.92);
 }
 
 // hipErrorNotSupported where no tile shape fits or the fp32 pipeline is the faster one.

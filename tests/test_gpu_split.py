@@ -111,7 +111,7 @@ SHAPES = [
     ((8, 24, 5, 39, 64, 4, 4, 3, 0), 1),
     ((9, 81, 60, 8, 100, 5, 5, 2, 4), 1),
     ((1, 15, 25, 6, 300, 5, 5, 3, 3), 4),
-    ((9, 18, 41, 92, 33, 5, 5, 1, 4), 2),
+    ((11, 18, 41, 92, 33, 5, 5, 1, 4), 2),
     ((31, 11, 30, 31, 65, 5, 5, 1, 1), 3),
     ((43, 42, 27, 32, 33, 5, 5, 1, 2), 3),
     ((1, 30, 12, 9, 64, 5, 5, 2, 1), 4),

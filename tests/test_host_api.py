@@ -159,8 +159,9 @@ def test_launch_info_names_the_dispatch(lib):
     assert im2win.conv2d_im2win_fwd_launch_info(*L.dims, workspace_free=True)["kernel"] == "conv_split_kernel<3, 3, 0, true>"
     assert im2win.conv2d_im2win_fwd_launch_info(128, 60, 56, 56, 64, 3, 3, 1, 1)["kernel"] == "conv_split_kernel<3, 3, 0, false>"
     # a channel count off the K block still takes the pipelined kernel (its ragged instance)
-    assert im2win.conv2d_im2win_fwd_launch_info(3, 13, 12, 12, 96, 3, 3, 1, 0)["kernel"] == \
+    assert im2win.conv2d_im2win_fwd_launch_info(4, 13, 60, 60, 96, 3, 3, 1, 0)["kernel"] == \
         "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, false, true>"
+    assert im2win.conv2d_im2win_fwd_launch_info(3, 13, 12, 12, 96, 3, 3, 1, 0)["kernel"] == "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"   # few tiles
     assert im2win.conv2d_im2win_fwd_launch_info(8, 7, 56, 56, 64, 3, 3, 1, 1)["kernel"] == "conv_mfma_kernel<9, false>"
     # 1x1 layers: their own kernel; 1x7 / 7x1 / 1x3 / 3x1: instances of the pipelined kernel; other asymmetric filters:
     # the pipelined generic kernel, its single-stage form when two stages do not fit LDS
