@@ -202,7 +202,7 @@ __device__ __forceinline__ void tail_piece(const MfmaParams &P, uint32_t lt, int
 // TAIL: a workgroup takes one sixteenth of its tile (tail_piece above).
 // RAG: Ci is not a multiple of CB.  The last K block then holds Ci % CB real channels; the words
 // of the missing ones -- strip words and filter columns, whatever the loads brought in from the
-// neighbouring channel planes and filter rows -- are replaced by +0.0 when that block is written
+// last channel's plane and neighbouring filter rows -- are replaced by +0.0 when that block is written
 // to LDS, so the MFMA loop itself is unchanged.  (Whole tiles and halves: not combined with PER, TAIL.)
 // QUART: every workgroup takes a tile of 32 channels x 32 pixels, staged and pipelined like a half tile, and its four waves a quarter of
 // the channel pairs of every K block each; the four partial sums meet in LDS.  For layers that would leave most of the compute units idle.
@@ -391,8 +391,9 @@ __device__ __forceinline__ void conv_mfma_fast_body(const MfmaParams &P)
     float ir[2][CB * JX];
     const uint32_t plane_bytes = (IMP ? P.in_plane : P.chan_stride) * 4u;
     auto load_i = [&](int kb, int set, int c, int j, const __amdgpu_buffer_rsrc_t &rw, const uint32_t (&soffb)[JX]) __attribute__((always_inline)) {
+        const int chan = RAG ? min(kb * CB + c, P.Ci - 1) : kb * CB + c;   // (a missing channel: the last one again, so that no load leaves the tensor)
         ir[set][c * JX + j] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(rw, soffb[j], (uint32_t)(kb * CB + c) * plane_bytes, 0));
+            float, __builtin_amdgcn_raw_buffer_load_b32(rw, soffb[j], (uint32_t)chan * plane_bytes, 0));
     };
     // The strip words of the first tile's first two K blocks are requested here, before the
     // filter staging coordinates are worked out: they have the longest way to come.
@@ -600,9 +601,9 @@ __device__ __forceinline__ void conv_mfma_fast_body(const MfmaParams &P)
 #pragma unroll
     for (int j = 0; j < JF; ++j)
 #pragma unroll
-        for (int hh = 0; hh < HPC; ++hh) store_f(0, j, hh);
+        for (int hh = 0; hh < HPC; ++hh) store_f(0, j, hh, QUART && nkb == 1);
 #pragma unroll
-    for (int w = 0; w < NIW; ++w) store_i(0, 0, w / JX, w % JX, loffI_c, zero_c);
+    for (int w = 0; w < NIW; ++w) store_i(0, 0, w / JX, w % JX, loffI_c, zero_c, QUART && nkb == 1);   // (quarter tiles: also less than a K block)
     if (nkb > 1) {
 #pragma unroll
         for (int j = 0; j < JF; ++j) load_f(1, j, rf_c);
@@ -928,6 +929,19 @@ hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks,
     const hipError_t e = launch_conv_split(P, sh, blocks, st, implicit, plan);
     if (e != hipErrorNotSupported) return e;
     if (!in_reach) return hipErrorNotSupported;
+    // Fewer channels than a K block: quarter tiles where each has a unit, at the price of MFMAs on zeros; the generic kernels where there are
+    // more.  Convolution alone, us, generic / here (4 is what a launch takes): 3 -> 16 channels 30x30 6.5 / 4.2, 5 -> 20 30x30 stride 2 8.2 / 4.0, 7 -> 40
+    // 56x56 8.0 / 4.1, 6 -> 64 28x28 N=4 8.3 / 4.0.
+    if (sh.Hf == 3 && sh.Wf == 3 && sh.Ci < 8 && al16 && P.S <= 512) {
+        int dev = 0, ncu = 0;
+        hipError_t de = device_cus(&dev, &ncu);
+        if (de != hipSuccess && plan) { de = hipSuccess; ncu = 256; }
+        if (de != hipSuccess) return de;
+        if (((P.npix + 31) / 32) * (uint32_t)((P.Co + 31) / 32) <= (uint32_t)ncu) {
+            if (P.S <= 256) return implicit ? launch_quarter_t<3, 3, 8, 1, true, true>(P, dev, st, plan) : launch_quarter_t<3, 3, 8, 1, false, true>(P, dev, st, plan);
+            return implicit ? launch_quarter_t<3, 3, 8, 2, true, true>(P, dev, st, plan) : launch_quarter_t<3, 3, 8, 2, false, true>(P, dev, st, plan);
+        }
+    }
     // (Ci need not be a multiple of the K block: the last block is then zero-filled)
     if (sh.Hf == 3 && sh.Wf == 3 && sh.Ci >= 8 && al16) {
         if (P.S <= 256) return launch_fast_i<3, 3, 8, 1, 4, 3>(P, blocks, st, implicit, plan);

@@ -21,6 +21,9 @@ SHAPES = [
     ((1, 12, 7, 180, 20, 3, 3, 2, 0), "conv_mfma_quarter_kernel<3, 3, 8, 2, false, true>"),
     ((1, 48, 3, 3, 5, 3, 3, 1, 3), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, true, false, false>"),   # one tile: sixteenths
     ((1, 33, 3, 3, 5, 3, 3, 1, 3), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"),       # padding as wide as the filter: windows of zeros
+    ((1, 3, 32, 32, 16, 3, 3, 1, 0), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"),     # less than a K block
+    ((2, 1, 28, 27, 33, 3, 3, 1, 1), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"),
+    ((1, 7, 31, 30, 20, 3, 3, 2, 1), "conv_mfma_quarter_kernel<3, 3, 8, 2, false, true>"),
     ((2, 100, 45, 45, 120, 3, 3, 1, 1), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 2, false, false, false, true, true>"),
     ((3, 13, 50, 47, 120, 3, 3, 2, 1), "conv_mfma_quarter_kernel<3, 3, 8, 2, false, true>"),
     ((5, 20, 63, 44, 70, 3, 3, 2, 1), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, false, true, true>"),
@@ -55,7 +58,7 @@ def test_both_calls(shape, kernel):
     assert torch.equal(outs[0].view(torch.int32), outs[2].view(torch.int32))   # same strips, same order
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0][0], SHAPES[3][0]], ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("shape", [SHAPES[0][0], SHAPES[3][0], (2, 3, 20, 21, 16, 3, 3, 1, 0)], ids=lambda v: "x".join(map(str, v)))
 def test_words_beyond_the_channels_are_not_used(shape):
     """The planes and filter rows behind the last channel's are the next image's and the next output channel's: with NaN there, an image or a
     channel of ordinary data stays ordinary, and only its neighbours are NaN."""

@@ -127,7 +127,7 @@ def test_binding_rejects_host_tensors(lib):
 def test_launch_info_names_the_dispatch(lib):
     """The planning calls run the library's own dispatch and launch nothing (no GPU needed: the
     grid is then planned for 256 compute units)."""
-    want = {1: "conv_mfma_kernel<9, false>", 2: "conv_split_kernel<3, 3, 0, false>", 3: "conv_split_kernel<3, 3, 0, false>",
+    want = {1: "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>", 2: "conv_split_kernel<3, 3, 0, false>", 3: "conv_split_kernel<3, 3, 0, false>",
             4: "conv_split_stem_kernel<7, 2, 1, 4, 1, false>", 5: "conv_split_stem_kernel<11, 3, 4, 1, 1, false>"}
     for idx, prefix in want.items():
         L = workloads.layer(idx)
