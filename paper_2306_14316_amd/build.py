@@ -1,14 +1,16 @@
-"""Build the gfx950 library in-tree: hipcc -> paper_2306_14316_amd/libim2win.so."""
+"""Build the gfx950 library in-tree: hipcc -> paper_2306_14316_amd/libim2win.so, and gcc -> paper_2306_14316_amd/_native.so."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libim2win.so")
+NATIVE = os.path.join(HERE, "_native.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ("api.hip", "transform.hip", "conv_basic.hip", "conv_mfma.hip", "conv_mfma_fast.hip", "conv_split.hip",
            "conv_split_stem.hip", "conv_split_1x1.hip", "conv_mfma_shallow.hip", "conv_mfma_1x1.hip", "baselines.hip", "probes.hip")
@@ -36,9 +38,18 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_native() -> None:
+    """The binding's short path (host code, a CPython module)."""
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "native_call.c"), "-o", tmp], check=True)
+    os.replace(tmp, NATIVE)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source for gfx950 and link the shared library (always rebuilds)."""
+    """Compile every source for gfx950 and link the shared library (always rebuilds); the binding's module with it."""
     os.makedirs(OBJDIR, exist_ok=True)
+    _build_native()
     with ThreadPoolExecutor(max_workers=4) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()

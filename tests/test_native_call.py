@@ -1,0 +1,65 @@
+"""The binding's calls in C: what they take is what the general path takes, with the same results; everything else is left to that path."""
+from types import SimpleNamespace
+
+import pytest
+import torch
+
+import paper_2306_14316_amd as im2win
+from paper_2306_14316_amd import binding
+
+LAYER = (2, 3, 9, 8, 5, 3, 3, 1, 1)
+
+
+def _args(device):
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = LAYER
+    sz = im2win.layer_sizes(*LAYER)
+    g = torch.Generator().manual_seed(7)
+    x, f = torch.randn((N, Ci, Hi, Wi), generator=g), torch.randn((Co, Ci, Hf, Wf), generator=g)
+    return x.to(device), f.to(device), torch.zeros(sz["window_elems"], device=device), torch.zeros((N, Co, sz["Ho"], sz["Wo"]), device=device)
+
+
+def test_what_is_not_plain_is_left_to_the_general_path():
+    transform, conv = binding._load_native()
+    x, f, w, o = _args("cpu")
+    d = LAYER[:4] + LAYER[5:]
+    assert transform(x, w, *d, None) is None                        # not on the GPU
+    assert conv(0, w, f, o, *LAYER, None) is None and conv(1, x, f, o, *LAYER, None) is None
+    assert transform(None, w, *d, None) is None and transform(x, w, *d[:-1]) is None and conv() is None
+    assert conv(1, x, f, o, *LAYER[:-1], 1.0, None) is None and conv(1, x, f, o, *LAYER[:-1], 2 ** 40, None) is None
+    with pytest.raises(TypeError):
+        im2win.conv2d_im2win_implicit_fwd(x, f, o, *LAYER)
+    assert conv(1, x, f, o, *LAYER[:7], 0, 1, None) is None         # stride 0
+
+
+@pytest.mark.gpu
+def test_same_results_and_refusals_as_the_general_path(monkeypatch):
+    x, f, w, o = _args("cuda")
+    d = LAYER[:4] + LAYER[5:]
+    transform, conv = binding._load_native()
+    assert transform(x, w, *d, None) == 0 and conv(0, w, f, o, *LAYER, None) == 0   # these go through
+    torch.cuda.synchronize()
+
+    def both():
+        out, win = torch.full_like(o, float("nan")), torch.full_like(w, float("nan"))
+        out2, side = torch.full_like(o, float("nan")), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):                               # the current stream
+            im2win.im2win_transform(x, win, *d)
+        torch.cuda.current_stream().wait_stream(side)
+        im2win.conv2d_im2win_fwd(win, f, out, *LAYER)
+        torch.cuda.synchronize()
+        im2win.conv2d_im2win_implicit_fwd(x, torch.nn.Parameter(f), out2, *LAYER, stream=side)   # a given one
+        torch.cuda.synchronize()
+        refused = []
+        for bad in ((x[:, :, ::2], f, o), (x.double(), f, o), (x, f[:4], o), (x, f, o[:1]), (x.cpu(), f, o), (x, f, SimpleNamespace())):
+            with pytest.raises((TypeError, ValueError)) as e:
+                im2win.conv2d_im2win_implicit_fwd(*bad, *LAYER)
+            refused.append((e.type, str(e.value)))
+        return out, out2, win, refused
+
+    got = both()
+    monkeypatch.setattr(binding, "_call_transform", lambda *a: None)
+    monkeypatch.setattr(binding, "_call_conv", lambda *a: None)
+    want = both()
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(got[:3], want[:3])) and got[3] == want[3]
+    assert torch.isfinite(got[0]).all() and torch.isfinite(got[1]).all()
