@@ -36,17 +36,17 @@ PEAK_HBM_GBS = 8000.0             # MI355X HBM3E
 # gives the commands; tests/test_host_api.py holds the two to each other.  Layers that were not
 # measured report null.
 MEASURED_CONV_TRAFFIC_BYTES = {
-    "cfg1_tiny_3x3": 209336,
-    "cfg2_3x3_c64_56": 112869627,
-    "cfg3_3x3_c256_14": 122700562,
-    "cfg4_7x7_s2_c3_224": 690636739,
-    "cfg5_11x11_s4_c3_227": 365292661}
+    "cfg1_tiny_3x3": 233459,
+    "cfg2_3x3_c64_56": 65774873,
+    "cfg3_3x3_c256_14": 122695463,
+    "cfg4_7x7_s2_c3_224": 690592941,
+    "cfg5_11x11_s4_c3_227": 365294070}
 MEASURED_TRANSFORM_TRAFFIC_BYTES = {
-    "cfg1_tiny_3x3": 63485,
-    "cfg2_3x3_c64_56": 105597908,
-    "cfg3_3x3_c256_14": 113849456,
-    "cfg4_7x7_s2_c3_224": 362314479,
-    "cfg5_11x11_s4_c3_227": 298572217}
+    "cfg1_tiny_3x3": 63490,
+    "cfg2_3x3_c64_56": 105604460,
+    "cfg3_3x3_c256_14": 113849087,
+    "cfg4_7x7_s2_c3_224": 362291063,
+    "cfg5_11x11_s4_c3_227": 298590394}
 
 
 def parse_args():
