@@ -45,6 +45,15 @@ constexpr int pick_ring_half(int nm)
     return 0;
 }
 
+// Quarter tiles: a quarter of that count, at least half of it before the barrier.
+constexpr int pick_ring_quarter(int nm)
+{
+    const int cand[] = {8, 7, 5, 6, 4, 3};
+    for (int r : cand)
+        if (nm % 4 == 0 && (nm / 4) % r == 0 && 2 * r <= nm / 4) return r;
+    return 0;
+}
+
 // ---- leftover tiles: sixteen 16x16 pieces per tile ------------------------------------------
 // A workgroup alone on a compute unit already keeps all four matrix pipes busy, so when fewer
 // tiles than compute units are left after the last full round of the grid they take a whole
@@ -219,7 +228,7 @@ __device__ __forceinline__ void conv_mfma_fast_body(const MfmaParams &P)
     constexpr int SS = 256 * JX;            // LDS floats per channel strip (compile-time stride)
     constexpr int SF_FLOATS = (MT * PF + 3) & ~3;
     constexpr int STAGE = SF_FLOATS + CB * SS;   // floats per LDS stage
-    constexpr int R = QUART ? 3 : HALF ? pick_ring_half((CB / 2) * KHW) : pick_ring((CB / 2) * KHW);
+    constexpr int R = QUART ? pick_ring_quarter((CB / 2) * KHW) : HALF ? pick_ring_half((CB / 2) * KHW) : pick_ring((CB / 2) * KHW);
     static_assert(R > 0, "no ring length divides the MFMAs per block");
     static_assert(CW == 4 || CW == 2 || CW == 1, "chunks are 16, 8 or 4 bytes");
     static_assert(KB % CW == 0, "K block must be a whole number of chunks");
@@ -235,7 +244,7 @@ __device__ __forceinline__ void conv_mfma_fast_body(const MfmaParams &P)
     const int h = lane >> 5, l32 = lane & 31;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);   // the same, known to be wave-uniform
     const int wm_u = wave_u & 1, wn_u = wave_u >> 1;
-    static_assert(!QUART || (HALF && !PER && !TAIL && CB % 8 == 0 && KHW % 3 == 0), "quarter tiles: two channels of every K block to a wave");
+    static_assert(!QUART || (HALF && !PER && !TAIL && CB % 8 == 0), "quarter tiles: two channels of every K block to a wave");
     static_assert(!HALF || (!PER && (CB / 2) % 2 == 0),
                   "half tiles: the channel pairs of a K block split evenly between two waves");
     // half-tile workgroups: which tile, which half; waves 0/1 take the first half of the channel
@@ -797,14 +806,15 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
     if (e != hipSuccess) return e;
     const uint32_t left = ncu >= 8 && ncu % 8 == 0 ? blocks % (uint32_t)ncu : 0u, eighth = (uint32_t)ncu / 8, halfcu = (uint32_t)ncu / 2;
-    if constexpr (PIECEABLE && CW == 4) {
-        // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths, as far as those have.  Convolution alone, us, two
+    if constexpr (HF == WF && HF >= 3 && HF <= 5 && CW == 4 && (HF < 5 || JX > 1)) {   // (K blocks of eight channels; two stages of 7x7 filters and strips pass 160 KB)
+        // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths, as far as those have (or two of them one,
+        // where they are a group or two of channels long: 32 -> 130 14x11 stride 2 N=12, 21 tiles, 4.4 / 4.5 against 5.5 / 5.6).  Convolution alone, us, two
         // calls / workspace-free, halves or sixteenths / quarters: 64 -> 64 channels 56x56 (196 quarters) 8.0 / 8.5 / 6.1 / 6.6; 344 -> 29 13x12 N=27
         // 29.3 / 32.7 / 18.2 / 21.4; 128 -> 128 28x28 (26 tiles) 9.7 / 12.0 / 8.9 / 9.9; 128 -> 256 14x14 (16 tiles) 6.5 / 8.2 / 8.9 / 10.1; 64 -> 64 28x28
-        // N=16 (392 quarters) 11.8 / 12.5 / 13.6 / 14.7.
+        // N=16 (392 quarters) 11.8 / 12.5 / 13.6 / 14.7; 5x5 77 -> 120 20x20 N=3 32.7 / 35.9 / 13.2 / 15.6; 4x4 stride 2 64 -> 64 64x64 17.5 / 19.9 / 10.3 / 11.7.
         const uint32_t quarters = ((P.npix + 31) / 32) * (uint32_t)((P.Co + 31) / 32);
-        if (quarters <= (uint32_t)ncu && !(P.Ci % 16 == 0 && 16 * blocks <= (uint32_t)ncu))
-            return P.Ci % CB != 0 ? launch_quarter_t<HF, WF, CB, JX, IMP, true>(P, dev, st, plan) : launch_quarter_t<HF, WF, CB, JX, IMP, false>(P, dev, st, plan);
+        if (P.Ci >= 8 && quarters <= (uint32_t)ncu && !(PIECEABLE && P.Ci % 16 == 0 && (P.Ci <= 32 ? 8 : 16) * blocks <= (uint32_t)ncu))
+            return P.Ci % 8 != 0 ? launch_quarter_t<HF, WF, 8, JX, IMP, true>(P, dev, st, plan) : launch_quarter_t<HF, WF, 8, JX, IMP, false>(P, dev, st, plan);
     }
     if (P.Ci % CB != 0) {
         // ragged last K block: whole tiles, one per workgroup, and leftover tiles as halves (below; only the 16-byte filter-fetch

@@ -110,7 +110,8 @@ static double fp32_estimate(const MfmaParams &P, const Shape &sh, uint32_t block
     const int nkb = (sh.Ci + CB - 1) / CB;
     const bool whole = sh.Ci % CB == 0, pieces = HF == 3 && WF == 3 && sh.Ci % 16 == 0;
     const double k = (double)(nkb * CB * HF * WF);
-    if (HF == 3 && WF == 3 && (uint32_t)((sh.npix + 31) / 32) * (uint32_t)((sh.Co + 31) / 32) <= (uint32_t)ncu) return 3.4 + k * 0.0048;   // quarter tiles
+    if (HF == WF && HF <= 5 && sh.Ci >= 8 && (uint32_t)((sh.npix + 31) / 32) * (uint32_t)((sh.Co + 31) / 32) <= (uint32_t)ncu)
+        return 3.4 + (double)((sh.Ci + 7) / 8 * 8 * HF * WF) * 0.0048;   // quarter tiles
     double rounds = 0.9 * up + 0.1 * std::max(r, up > 1.5 ? 0.0 : 0.84);
     if (whole && nkb % 2 == 0 && nkb <= 12 && sh.Co % MB == 0 && blocks >= 3 * RESIDENT * (uint32_t)ncu) {
         rounds = r;

@@ -24,6 +24,16 @@ SHAPES = [
     ((1, 3, 32, 32, 16, 3, 3, 1, 0), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"),     # less than a K block
     ((2, 1, 28, 27, 33, 3, 3, 1, 1), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, true>"),
     ((1, 7, 31, 30, 20, 3, 3, 2, 1), "conv_mfma_quarter_kernel<3, 3, 8, 2, false, true>"),
+    ((2, 10, 20, 33, 40, 5, 5, 1, 1), "conv_mfma_quarter_kernel<5, 5, 8, 2, false, true>"),    # two channels in the last K block
+    ((1, 16, 19, 90, 33, 5, 5, 1, 4), "conv_mfma_quarter_kernel<5, 5, 8, 2, false, false>"),
+    ((1, 17, 21, 90, 33, 5, 5, 1, 0), "conv_mfma_quarter_kernel<5, 5, 8, 2, false, true>"),
+    ((2, 8, 24, 100, 40, 5, 5, 2, 2), "conv_mfma_quarter_kernel<5, 5, 8, 3, false, false>"),
+    ((2, 31, 24, 50, 63, 5, 5, 2, 2), "conv_mfma_quarter_kernel<5, 5, 8, 3, false, true>"),
+    ((1, 24, 30, 41, 65, 5, 5, 1, 2), "conv_mfma_quarter_kernel<5, 5, 8, 2, false, false>"),
+    ((1, 9, 24, 21, 33, 4, 4, 1, 0), "conv_mfma_quarter_kernel<4, 4, 8, 2, false, true>"),
+    ((1, 24, 27, 31, 70, 4, 4, 1, 3), "conv_mfma_quarter_kernel<4, 4, 8, 2, false, false>"),
+    ((1, 16, 17, 60, 20, 4, 4, 2, 1), "conv_mfma_quarter_kernel<4, 4, 8, 3, false, false>"),
+    ((3, 23, 17, 60, 20, 4, 4, 2, 1), "conv_mfma_quarter_kernel<4, 4, 8, 3, false, true>"),
     ((2, 100, 45, 45, 120, 3, 3, 1, 1), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 2, false, false, false, true, true>"),
     ((3, 13, 50, 47, 120, 3, 3, 2, 1), "conv_mfma_quarter_kernel<3, 3, 8, 2, false, true>"),
     ((5, 20, 63, 44, 70, 3, 3, 2, 1), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, false, true, true>"),

@@ -285,6 +285,13 @@ ASYMMETRIC_SHAPES = [
     ((32, 32, 112, 112, 64, 2, 2, 2, 0), True),  # 2x2 stride 2: several tiles per workgroup
     ((2, 8, 24, 100, 40, 5, 5, 2, 2), True),     # 5x5 stride 2: three strip words per thread
     ((1, 10, 30, 110, 70, 5, 5, 2, 0), True),    # 5x5 stride 2, ten channels: half a K block left over
+    ((2, 16, 22, 106, 100, 4, 4, 1, 0), True),   # whole tiles of 4x4 and of 5x5 stride 2, with and without a ragged K block
+    ((11, 10, 41, 51, 130, 4, 4, 1, 2), True),
+    ((12, 12, 45, 100, 40, 4, 4, 2, 0), True),
+    ((10, 30, 35, 44, 130, 4, 4, 2, 2), True),
+    ((11, 24, 23, 69, 130, 5, 5, 2, 2), True),
+    ((7, 30, 55, 101, 40, 5, 5, 2, 2), True),
+    ((7, 24, 22, 83, 70, 5, 5, 2, 1), True),
 ]
 
 
@@ -292,7 +299,8 @@ ASYMMETRIC_SHAPES = [
 def test_asymmetric_filters(shape, pipelined):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
     name = im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
-    assert name.startswith("conv_mfma_fast_kernel<%d, %d," % (Hf, Wf)) == pipelined, name
+    # (few tiles run the pipeline as quarter tiles)
+    assert name.startswith(("conv_mfma_fast_kernel<%d, %d," % (Hf, Wf), "conv_mfma_quarter_kernel<%d, %d," % (Hf, Wf))) == pipelined, name
     I, F = workloads.random_layer_inputs(7700 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     print("asymmetric", shape, name, flush=True)
     check_layer(I, F, s, p, basic=False, twice=False)
