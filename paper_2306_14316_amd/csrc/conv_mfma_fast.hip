@@ -808,7 +808,7 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     const uint32_t left = ncu >= 8 && ncu % 8 == 0 ? blocks % (uint32_t)ncu : 0u, eighth = (uint32_t)ncu / 8, halfcu = (uint32_t)ncu / 2;
     if constexpr (HF == WF && HF >= 3 && HF <= 5 && CW == 4 && (HF < 5 || JX > 1)) {   // (K blocks of eight channels; two stages of 7x7 filters and strips pass 160 KB)
         // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths, as far as those have (or two of them one,
-        // where they are a group or two of channels long: 32 -> 130 14x11 stride 2 N=12, 21 tiles, 4.4 / 4.5 against 5.5 / 5.6).  Convolution alone, us, two
+        // where they are a group or two of channels long: 32 -> 130 14x11 stride 2 N=12, 21 tiles, 4.4 against 5.5 in two calls).  Convolution alone, us, two
         // calls / workspace-free, halves or sixteenths / quarters: 64 -> 64 channels 56x56 (196 quarters) 8.0 / 8.5 / 6.1 / 6.6; 344 -> 29 13x12 N=27
         // 29.3 / 32.7 / 18.2 / 21.4; 128 -> 128 28x28 (26 tiles) 9.7 / 12.0 / 8.9 / 9.9; 128 -> 256 14x14 (16 tiles) 6.5 / 8.2 / 8.9 / 10.1; 64 -> 64 28x28
         // N=16 (392 quarters) 11.8 / 12.5 / 13.6 / 14.7; 5x5 77 -> 120 20x20 N=3 32.7 / 35.9 / 13.2 / 15.6; 4x4 stride 2 64 -> 64 64x64 17.5 / 19.9 / 10.3 / 11.7.
