@@ -10,7 +10,7 @@ from parity_util import assert_conv_close, conv_errors, run_transform
 
 pytestmark = pytest.mark.gpu
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the kernel of the two-call path
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the kernel of the two-call path, which test_split_dispatch.py holds the dispatch to
 SHAPES = [
     ((1, 64, 56, 56, 64, 3, 3, 1, 1), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, false>"),
     ((1, 8, 40, 47, 97, 3, 3, 1, 0), "conv_mfma_quarter_kernel<3, 3, 8, 1, false, false>"),    # one K block; one channel and 14 pixels past a tile
@@ -45,8 +45,6 @@ SHAPES = [
 @pytest.mark.parametrize("shape,kernel", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
 def test_both_calls(shape, kernel):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
-    names = [im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] for w in (False, True)]
-    assert names[0] == kernel and names[0].split("<")[0] == names[1].split("<")[0], names
     I, F = workloads.random_layer_inputs(8800 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     print("few tiles", shape, kernel, flush=True)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)

@@ -41,8 +41,6 @@ def instance_name(Hf, instance, workspace_free):
 @pytest.mark.parametrize("shape,instance", SHAPES, ids=lambda v: "x".join(map(str, v)))
 def test_both_calls(shape, instance):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
-    for w in (False, True):
-        assert im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"] == instance_name(Hf, instance, w)
     I, F = workloads.random_layer_inputs(9600 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     Ho, Wo = im2win.im2win_out_shape(Hi, Wi, Hf, Wf, s, p)
     n = N * Co * Ho * Wo

@@ -16,7 +16,7 @@ def _split(shape, workspace_free=False):
     return im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=workspace_free)["kernel"].startswith("conv_split_kernel<")
 
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the configuration (0 / 1 / 4: long filter stages, tiles of 64 x 256 / 64 x 128 / 32 x 256; 2 and 3:
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p) and the configuration, which test_split_dispatch.py holds the dispatch to (0 / 1 / 4: long filter stages, tiles of 64 x 256 / 64 x 128 / 32 x 256; 2 and 3:
 # 64 x 256 with larger patches): every instance at channel counts off its K block and tile, with padding, on short images (a tile spans several)
 # and at the strides it takes
 SHAPES = [
@@ -133,9 +133,7 @@ OTHER_SHAPES = [(7, 78, 24, 30, 300, 3, 3, 1, 2), (43, 14, 16, 103, 64, 3, 3, 1,
 @pytest.mark.parametrize("shape,cfg", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_both_calls(shape, cfg):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
-    assert _split(shape) and _split(shape, True)
     name = im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
-    assert name == "conv_split_kernel<%d, %d, %d, false>" % (Hf, Wf, cfg), name
     I, F = workloads.random_layer_inputs(9100 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     print("pieces", shape, name, flush=True)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)

@@ -63,8 +63,6 @@ def _run(shape, I, F):
 @pytest.mark.parametrize("shape,instance", SHAPES, ids=lambda v: "x".join(map(str, v)))
 def test_both_calls(shape, instance):
     N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
-    for w in (False, True):
-        assert _plan(shape, w) == "conv_split_stem_kernel<%d, %d, %d, %d, %d, %s>" % (Hf, *instance, "true" if w else "false")
     I, F = workloads.random_layer_inputs(9700 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
     O_ref, B_ref = oracle.conv2d_direct(I.numpy(), F.numpy(), s, p)
     got, fp32 = _run(shape, I, F)

@@ -6,12 +6,56 @@ import pytest
 
 import paper_2306_14316_amd as im2win
 from perf import cases
+from test_gpu_few_tiles import SHAPES as FEW_TILE_SHAPES
+from test_gpu_parity import ASYMMETRIC_SHAPES, ONE_BY_ONE_SHAPES
 from test_gpu_shallow import SHAPES as SHALLOW_SHAPES
 from test_gpu_shallow import instance_name
 from test_gpu_split import SHAPES
+from test_gpu_split_1x1 import SHAPES as PIECE_1X1_SHAPES
 from test_gpu_split_stem import SHAPES as STEM_SHAPES
 
 FILTERS = [(3, 3), (5, 5), (7, 7), (1, 7), (7, 1), (1, 3), (3, 1), (4, 4)]
+
+
+def _tf(*flags):
+    return tuple("true" if f else "false" for f in flags)
+
+
+def _listed():
+    """(layer, the kernel of the two-call path, of the workspace-free call) as the lists of the GPU tests have them, or as far as they
+    have them.  The GPU tests compare numbers alone, so that they hold for any rule of the dispatch."""
+    for shape, cfg in SHAPES:
+        yield shape, *("conv_split_kernel<%d, %d, %d, %s>" % (*shape[5:7], cfg, *_tf(w)) for w in (False, True))
+    for shape, runs in PIECE_1X1_SHAPES:
+        yield shape, *("conv_split_1x1_kernel<%d, %s, %s>" % (runs, *_tf(shape[1] % 8, w)) for w in (False, True))
+    for shape, instance in STEM_SHAPES:
+        yield shape, *("conv_split_stem_kernel<%d, %d, %d, %d, %d, %s>" % (shape[5], *instance, *_tf(w)) for w in (False, True))
+    for shape, instance in SHALLOW_SHAPES:
+        yield shape, *(instance_name(shape[5], instance, w) for w in (False, True))
+    for shape, kernel in FEW_TILE_SHAPES:
+        yield shape, kernel, kernel.split("<")[0] + "<"
+
+
+@pytest.mark.parametrize("shape,two_call,workspace_free", _listed(), ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_the_layers_of_the_gpu_tests_run_the_instances_they_list(shape, two_call, workspace_free):
+    for w, want in ((False, two_call), (True, workspace_free)):
+        name = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"]
+        assert name.startswith(want), (name, want)
+
+
+@pytest.mark.parametrize("shape,pipelined", ASYMMETRIC_SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_which_filters_run_the_fp32_pipeline(shape, pipelined):
+    """(Few tiles run it as quarter tiles.)"""
+    name = im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
+    assert name.startswith(tuple("conv_mfma_%s_kernel<%d, %d," % (k, *shape[5:7]) for k in ("fast", "quarter"))) == pipelined, name
+
+
+@pytest.mark.parametrize("dims,form", ONE_BY_ONE_SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_which_1x1_layers_run_the_fp32_1x1_kernel(dims, form):
+    N, Ci, Hi, Wi, Co, s = dims
+    name = im2win.conv2d_im2win_fwd_launch_info(N, Ci, Hi, Wi, Co, 1, 1, s, 0)["kernel"]
+    assert name.startswith("conv_mfma_1x1_kernel<") == (form is not None), name
+    assert form is None or {"x4": ", false, ", "gather": ", true, "}[form] in name, name
 
 
 @pytest.mark.parametrize("filt", FILTERS, ids=lambda f: "%dx%d" % f)
