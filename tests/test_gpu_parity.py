@@ -215,15 +215,15 @@ def test_three_channel_3x3_layer_output_off_16_byte_alignment():
     assert bool(torch.isnan(buf[0]))
 
 
-# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p): short K loops and at least 2304 tiles, so that the pipelined
-# kernel gives every workgroup several tiles and runs its pipeline across tile boundaries
+# (N, Ci, Hi, Wi, Co, Hf, Wf, s, p): short K loops and enough tiles (six per compute unit, nine where three workgroups fit
+# one) for the pipelined kernel to give every workgroup several and run its pipeline across tile boundaries.  All but the 7x7, the
+# 5x5 stride 2, the 4x4 and the 1x3 layer run the bf16-piece kernel; PIPELINE_SHAPES has the other filters' persistent instances.
 MANY_TILE_SHAPES = [
     (48, 16, 56, 56, 64, 3, 3, 1, 1),    # two K blocks per tile
     (46, 64, 57, 57, 64, 3, 3, 1, 1),    # eight K blocks; ragged last tile; rows of 57 pixels
     (24, 32, 56, 56, 128, 3, 3, 1, 1),   # two M tiles per pixel tile
     (42, 8, 64, 64, 64, 5, 5, 1, 0),     # 5x5 instance
     (40, 4, 128, 128, 64, 7, 7, 2, 0),   # 7x7 stride-2 instance
-    # (the second, third and fourth have moved to the bf16-piece kernel; these run the persistent fp32 instances)
     (26, 8, 45, 70, 128, 5, 5, 1, 1),    # 5x5
     (19, 8, 104, 104, 128, 5, 5, 2, 3),  # 5x5 stride 2
     (213, 8, 16, 22, 64, 4, 4, 1, 3),    # 4x4
@@ -342,11 +342,11 @@ HALF_TILE_SHAPES = [
     (1, 8, 130, 130, 64, 3, 3, 1, 1),    # 265 tiles: 9 left; one K block; the last tile's second half is empty
     (1, 24, 96, 96, 88, 3, 3, 1, 0),     # 278 tiles: 22 left; three K blocks; second M tile: 24 of 64 rows
     (11, 40, 78, 78, 40, 3, 3, 2, 1),    # 262 tiles: 6 left; five K blocks; stride 2; tiles cross rows and images
-    (7, 64, 56, 56, 64, 3, 3, 1, 1),     # 343 tiles: 87 left; eight K blocks
+    (7, 64, 56, 56, 64, 3, 3, 1, 1),     # 343 tiles: 87 left; eight K blocks (the bf16-piece kernel)
     (9, 32, 50, 50, 128, 3, 3, 1, 0),    # 648 tiles (two M tiles each): 136 left -> 128 in halves, 8 in sixteenths
     (8, 32, 42, 42, 128, 3, 3, 1, 0),    # 400 tiles: 144 left -> 128 in halves, 16 in sixteenths
     (8, 24, 42, 42, 128, 3, 3, 1, 0),    # the same with 24 channels: no sixteenths, the 144 stay whole
-    (9, 32, 53, 53, 128, 3, 3, 1, 0),    # 732 tiles: 220 left: too many, all whole
+    (9, 32, 53, 53, 128, 3, 3, 1, 0),    # 732 tiles: 220 left: too many, all whole (the bf16-piece kernel)
     (5, 8, 68, 68, 64, 5, 5, 1, 0),      # the 5x5 instance: 320 tiles, 64 left, two K blocks
     (3, 12, 60, 60, 70, 5, 5, 1, 2),     # 5x5: 338 tiles, 82 left, three K blocks, second M tile: 6 of 64 rows
 ]
@@ -362,6 +362,46 @@ def test_leftover_tiles_in_halves(shape):
     dO = run_conv(dW, F, N, Ci, Hi, Wi, s, p)
     dO2 = torch.full_like(dO, float("nan"))
     im2win.conv2d_im2win_implicit_fwd(I.cuda(), F.cuda(), dO2, N, Ci, Hi, Wi, Co, Hf, Wf, s, p)
+    torch.cuda.synchronize()
+    assert torch.equal(dO.view(torch.int32), dO2.view(torch.int32))
+
+
+# Instances of the pipelined kernel that none of the layers above run (test_split_dispatch.py holds the dispatch to these names, and the
+# lists to every instance that it selects): whole tiles with a ragged last K block, halves and sixteenths with two strip words per
+# thread, several tiles per workgroup.
+PIPELINE_SHAPES = [
+    ((4, 11, 37, 37, 70, 3, 3, 1, 0), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, false, true>"),      # 3 of 8 channels, 6 of 64 rows
+    ((13, 14, 4, 106, 20, 3, 3, 1, 2), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, false, true>"),
+    ((2, 105, 101, 101, 113, 3, 3, 2, 0), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 3, false, false, false, false, true>"),   # 1 of 8 channels in the last of 14 K blocks
+    ((22, 21, 42, 42, 20, 3, 3, 2, 0), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 3, false, false, false, false, true>"),      # planes of 400 pixels: tiles cross images
+    ((5, 8, 25, 101, 65, 3, 3, 2, 4), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 3, false, false, false, false, false>"),      # one K block
+    ((9, 16, 135, 119, 256, 3, 3, 2, 4), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 3, false, true, false, false, false>"),
+    ((18, 16, 113, 5, 65, 3, 3, 2, 2), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, true, true, false>"),       # four pixels a row
+    ((9, 320, 38, 38, 134, 3, 3, 2, 1), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, true, true, false>"),
+    ((7, 4, 17, 33, 65, 5, 5, 1, 4), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, false>"),       # one K block
+    ((2, 27, 39, 39, 273, 5, 5, 1, 0), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, true>"),
+    ((4, 61, 33, 35, 245, 5, 5, 1, 0), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, true>"),
+    ((181, 8, 24, 22, 64, 5, 5, 1, 4), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, true, false, false, false>"),
+    ((5, 6, 40, 71, 65, 7, 7, 2, 3), "conv_mfma_fast_kernel<7, 7, 2, 4, 2, 2, false, false, false, false, false>"),
+    ((2, 8, 38, 38, 20, 7, 7, 1, 2), "conv_mfma_fast_kernel<7, 7, 2, 4, 2, 2, false, false, false, false, false>"),
+    ((5, 13, 12, 12, 65, 7, 7, 1, 2), "conv_mfma_fast_kernel<7, 7, 2, 4, 2, 2, false, false, false, false, true>"),
+    ((44, 53, 8, 8, 39, 1, 7, 1, 0), "conv_mfma_fast_kernel<1, 7, 8, 2, 4, 2, false, false, false, false, true>"),        # two pixels a row
+    ((160, 16, 225, 4, 256, 1, 7, 3, 4), "conv_mfma_fast_kernel<1, 7, 8, 2, 4, 2, false, true, false, false, false>"),
+    ((64, 16, 21, 21, 256, 7, 1, 1, 1), "conv_mfma_fast_kernel<7, 1, 8, 2, 4, 2, false, true, false, false, false>"),
+    ((2, 27, 30, 33, 130, 3, 1, 1, 1), "conv_mfma_fast_kernel<3, 1, 16, 1, 4, 2, false, false, false, false, true>"),
+    ((20, 40, 42, 42, 123, 3, 1, 1, 0), "conv_mfma_fast_kernel<3, 1, 16, 1, 4, 2, false, false, false, false, true>"),
+]
+
+
+@pytest.mark.parametrize("shape,kernel", PIPELINE_SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_other_instances_of_the_pipeline(shape, kernel):
+    N, Ci, Hi, Wi, Co, Hf, Wf, s, p = shape
+    I, F = workloads.random_layer_inputs(7960 + sum(shape), N, Ci, Hi, Wi, Co, Hf, Wf)
+    print("pipeline", shape, kernel, flush=True)
+    check_layer(I, F, s, p, basic=False, twice=True)
+    dO = run_conv(run_transform(I, Hf, Wf, s, p), F, N, Ci, Hi, Wi, s, p)
+    dO2 = torch.full_like(dO, float("nan"))
+    im2win.conv2d_im2win_implicit_fwd(I.cuda(), F.cuda(), dO2, *shape)
     torch.cuda.synchronize()
     assert torch.equal(dO.view(torch.int32), dO2.view(torch.int32))
 

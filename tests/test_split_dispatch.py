@@ -1,5 +1,5 @@
 """Host side of the bf16-piece kernels and of the fp32 kernel of three-channel layers (no GPU): the two calls of a layer always take the same instance, whatever the
-sizes, what the plan asks for fits the chip, and the GPU tests run every instance that the plan selects."""
+sizes, what the plan asks for fits the chip, and the GPU tests run every instance that the plan selects, of these kernels and of the fp32 pipeline."""
 import random
 
 import pytest
@@ -7,7 +7,7 @@ import pytest
 import paper_2306_14316_amd as im2win
 from perf import cases
 from test_gpu_few_tiles import SHAPES as FEW_TILE_SHAPES
-from test_gpu_parity import ASYMMETRIC_SHAPES, ONE_BY_ONE_SHAPES
+from test_gpu_parity import ASYMMETRIC_SHAPES, HALF_TILE_SHAPES, LEFTOVER_TILE_SHAPES, MANY_TILE_SHAPES, ONE_BY_ONE_SHAPES, PIPELINE_SHAPES
 from test_gpu_shallow import SHAPES as SHALLOW_SHAPES
 from test_gpu_shallow import instance_name
 from test_gpu_split import SHAPES
@@ -32,7 +32,7 @@ def _listed():
         yield shape, *("conv_split_stem_kernel<%d, %d, %d, %d, %d, %s>" % (shape[5], *instance, *_tf(w)) for w in (False, True))
     for shape, instance in SHALLOW_SHAPES:
         yield shape, *(instance_name(shape[5], instance, w) for w in (False, True))
-    for shape, kernel in FEW_TILE_SHAPES:
+    for shape, kernel in FEW_TILE_SHAPES + PIPELINE_SHAPES:
         yield shape, kernel, kernel.split("<")[0] + "<"
 
 
@@ -108,6 +108,30 @@ def test_every_selected_instance_has_a_gpu_test():
         if name.startswith("conv_split_kernel<"):
             seen.add(tuple(int(v) for v in name[len("conv_split_kernel<"):].split(", ")[:3]))
     assert len(seen) >= 28 and seen <= tested, (len(seen), sorted(seen - tested))
+
+
+def test_every_selected_fp32_pipeline_instance_has_a_gpu_test():
+    """The same for the fp32 pipeline: whole tiles, several to a workgroup, halves, sixteenths, quarters, ragged channel counts."""
+    def plan(shape):
+        return im2win.conv2d_im2win_fwd_launch_info(*shape)["kernel"]
+
+    tested = {plan(s) for s in [s for s, _ in FEW_TILE_SHAPES + PIPELINE_SHAPES + ASYMMETRIC_SHAPES] + MANY_TILE_SHAPES + LEFTOVER_TILE_SHAPES + HALF_TILE_SHAPES}
+    rng, seen = random.Random(23), {}
+    for i in range(150000):
+        if i % 3 == 0:
+            c = cases.draw(rng)
+            shape = tuple(c[k] for k in ("N", "Ci", "Hi", "Wi", "Co", "Hf", "Wf", "stride", "pad"))
+        else:
+            Hf, Wf = rng.choice(FILTERS + [(2, 2)])
+            Hi, s, p = int(2 ** rng.uniform(2, 8)), rng.choice([1, 1, 1, 2, 3]), rng.randint(0, 4)
+            Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(2, 8))
+            Ci = rng.choice([8, 16, 24, 32, 48, 64, 128, 256, int(2 ** rng.uniform(1, 10))])
+            shape = (int(2 ** rng.uniform(0, 8)), Ci, Hi, Wi, rng.choice([1, 20, 33, 64, 65, 100, 128, 130, 256, 300]), Hf, Wf, s, p)
+            if Hi + 2 * p < Hf or Wi + 2 * p < Wf or shape[0] * max(Ci, shape[4]) * (Hi + 2 * p) * Hf * (Wi + 2 * p) >= 2 ** 31:
+                continue
+        seen.setdefault(plan(shape), shape)
+    seen = {k: v for k, v in seen.items() if k.startswith(("conv_mfma_fast_kernel<", "conv_mfma_quarter_kernel<"))}
+    assert len(seen) >= 58 and set(seen) <= tested, (len(seen), {k: v for k, v in seen.items() if k not in tested})
 
 
 def test_a_kernel_name_is_one_kernel():
