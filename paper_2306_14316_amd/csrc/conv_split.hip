@@ -25,8 +25,12 @@ static bool split_params(SplitParams &Q, const MfmaParams &P, const Shape &sh, b
     if (CFG == 2 && HF == WF && HF <= 5 && HF != 4 && sh.s > 1) return false;
     const int rstep = std::max(1, HF / sh.s);
     long long best = -1, best_img = 0;
+    int tried = 0;
     for (int want : {512, 64, 48, 32, 28, 24, 16, 12, 8}) {
-        const int ns = (sh.Wo - 1) / want + 1, w = (sh.Wo - 1) / ns + 1, wl = sh.Wo - (ns - 1) * w;
+        const int ns = (sh.Wo - 1) / want + 1;
+        if (ns == tried) continue;   // (the widths follow from the number of strips)
+        tried = ns;
+        const int w = (sh.Wo - 1) / ns + 1, wl = sh.Wo - (ns - 1) * w;
         if (wl < 1 || wl < w / 2) continue;
         const long long PW = (long long)(w - 1) * sh.s + WF;
         if (std::min<long long>(sh.Wi, (long long)(wl - 1) * sh.s + WF - sh.p) < 4) continue;   // runs of at least four words
@@ -152,12 +156,20 @@ static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t bl
     auto consider = [&](auto cfg) {
         constexpr int CFG = decltype(cfg)::value;
         using KC = SplitK<HF, WF, CFG>;
-        if (!split_params<HF, WF, CFG>(Q[CFG], P, sh, IMP, &lds[CFG])) return;
+        using T = SplitTile<KC::SHAPE>;
+        constexpr int TM = T::WGM * T::FM * 32, TN = T::WGN * T::FN * 32;
         const double steps = (double)((sh.Ci + 8 * KC::CG - 1) / (8 * KC::CG)) * ((KC::CG * HF * WF + 1) / 2);
         constexpr bool SHORT = HF * WF == 3 || (HF == 4 && WF == 4);   // short K blocks, more patch to a step
-        const double t = KC::SHAPE == kWide     ? 5.3 + rounds(Q[CFG].nblocks, 0.65) * (SHORT ? 1.15 : 1.0) * (steps * 0.475 + 4.25)
-                         : KC::SHAPE == kNarrow ? 4.55 + rounds(Q[CFG].nblocks, 0.75) * (SHORT ? 1.16 : 1.0) * (steps * 0.3035 + 2.3)
-                                                : 5.05 + rounds(Q[CFG].nblocks, 0.65) * (SHORT ? 1.3 : HF * WF >= 25 ? 0.94 : 1.0) * (steps * 0.31 + 2.2);
+        auto time = [&](uint32_t tiles) {
+            return KC::SHAPE == kWide     ? 5.3 + rounds(tiles, 0.65) * (SHORT ? 1.15 : 1.0) * (steps * 0.475 + 4.25)
+                   : KC::SHAPE == kNarrow ? 4.55 + rounds(tiles, 0.75) * (SHORT ? 1.16 : 1.0) * (steps * 0.3035 + 2.3)
+                                          : 5.05 + rounds(tiles, 0.65) * (SHORT ? 1.3 : HF * WF >= 25 ? 0.94 : 1.0) * (steps * 0.31 + 2.2);
+        };
+        // (Strips only add tiles: what is too slow without them needs no search of their widths.  On the host, a search for every
+        // configuration takes 1.2 to 2 us of a call.)
+        if (time((uint32_t)((sh.npix + TN - 1) / TN) * (uint32_t)((sh.Co + TM - 1) / TM)) >= least) return;
+        if (!split_params<HF, WF, CFG>(Q[CFG], P, sh, IMP, &lds[CFG])) return;
+        const double t = time(Q[CFG].nblocks);
         if (t < least) { least = t; pick = CFG; }
     };
     using C0 = std::integral_constant<int, 0>;

@@ -1,10 +1,13 @@
 """Host side of the bf16-piece kernels and of the fp32 kernel of three-channel layers (no GPU): the two calls of a layer always take the same instance, whatever the
 sizes, what the plan asks for fits the chip, and the GPU tests run every instance that the plan selects, of these kernels and of the fp32 pipeline."""
+import ctypes
 import random
+import time
 
 import pytest
 
 import paper_2306_14316_amd as im2win
+from paper_2306_14316_amd import binding
 from perf import cases
 from test_gpu_few_tiles import SHAPES as FEW_TILE_SHAPES
 from test_gpu_parity import ASYMMETRIC_SHAPES, HALF_TILE_SHAPES, LEFTOVER_TILE_SHAPES, MANY_TILE_SHAPES, ONE_BY_ONE_SHAPES, PIPELINE_SHAPES
@@ -132,6 +135,23 @@ def test_every_selected_fp32_pipeline_instance_has_a_gpu_test():
         seen.setdefault(plan(shape), shape)
     seen = {k: v for k, v in seen.items() if k.startswith(("conv_mfma_fast_kernel<", "conv_mfma_quarter_kernel<"))}
     assert len(seen) >= 58 and set(seen) <= tested, (len(seen), {k: v for k, v in seen.items() if k not in tested})
+
+
+def test_layers_that_stay_on_the_fp32_pipeline_are_planned_as_fast_as_any():
+    """The rule looks for patches only where an estimate can win; a search for every configuration took 1.5 us of each call."""
+    lib, info = im2win.load_library(), binding.LaunchInfo()
+
+    def best(*dims):
+        t = []
+        for _ in range(60):
+            t0 = time.perf_counter()
+            for _ in range(200):
+                lib.conv2d_im2win_fwd_launch_info(*dims, 0, 0, ctypes.byref(info))
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    few, some = best(1, 64, 56, 56, 64, 3, 3, 1, 1), best(16, 64, 28, 28, 64, 3, 3, 1, 1)   # (no search at all: quarter tiles)
+    assert info.kernel.startswith(b"conv_mfma_fast_kernel<") and some < 1.3 * few, (few, some)   # (1.05 times; 1.6 to 2.1 with the searches)
 
 
 def test_a_kernel_name_is_one_kernel():
