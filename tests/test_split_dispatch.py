@@ -261,7 +261,7 @@ def test_one_by_one_layers():
     for _ in range(20000):
         Hi, s, p = int(2 ** rng.uniform(0, 8)), rng.choice([1, 1, 1, 2, 3]), rng.choice([0, 0, 0, 1])
         Wi = Hi if rng.random() < 0.5 else int(2 ** rng.uniform(0, 8))
-        Ci, Co = rng.choice([8, 16, 60, 64, 250, 256, 520, 1024]), rng.choice([1, 64, 65, 128, 130, 256, 1000])
+        Ci, Co = rng.choice([8, 16, 60, 64, 250, 256, 520, 1024, rng.randint(1, 40), rng.randint(1, 40)]), rng.choice([1, 64, 65, 128, 130, 256, 1000])
         shape = (int(2 ** rng.uniform(0, 12)), Ci, Hi, Wi, Co, 1, 1, s, p)
         if shape[0] * max(Ci, Co) * (Hi + 2 * p) * (Wi + 2 * p) >= 2 ** 31:
             continue
@@ -271,4 +271,33 @@ def test_one_by_one_layers():
         if split[0]:
             taken += 1
             assert p == 0 and Ci > 4 and plans[0]["grid"] == plans[1]["grid"] and plans[0]["lds_bytes"] <= 160 * 1024
-    assert taken > 500
+            assert [q["kernel"].split(", ", 1)[1] for q in plans] == ["%s, %s>" % _tf(Ci % 8, w) for w in (False, True)], plans
+        elif p == 0 and Ci > 16 and s <= 65536:
+            # the fp32 1x1 kernel, or words out of reach of the pieces' offsets
+            assert (Ci % 8 == 0 and Co % 4 == 0) or shape[0] * Ci * Hi * Wi >= 2 ** 29, (shape, plans)
+    assert taken > 5000
+
+
+# (layer, whether it runs in pieces): both sides of the lines where the fp32 1x1 kernel has no instance.  In us, generic kernel in two calls /
+# workspace-free / pieces:
+ONE_BY_ONE_LINES = [
+    ((64, 4, 40, 40, 33, 1, 1, 1, 0), False),     # four channels
+    ((37, 8, 63, 63, 6, 1, 1, 1, 0), False),      # 9.4 / 9.6 / 17.7
+    ((60, 6, 163, 163, 3, 1, 1, 2, 0), False),    # 26 / 28 / 42
+    ((121, 7, 102, 102, 2, 1, 1, 1, 0), False),   # 75 / 78 / 117
+    ((156, 7, 184, 184, 19, 1, 1, 1, 0), False),  # 365 / 374 / 491
+    ((102, 16, 77, 76, 9, 1, 1, 1, 0), False),    # 41 / 41 / 58
+    ((128, 5, 224, 224, 1, 1, 1, 1, 0), False),
+    ((233, 13, 1, 1, 28, 1, 1, 2, 0), True),      # 16 / 23 / 6.7
+    ((84, 10, 1, 1, 10, 1, 1, 2, 0), True),       # 15 / 21 / 5.6
+    ((3, 5, 16, 15, 20, 1, 1, 1, 0), True),
+    ((231, 8, 114, 114, 286, 1, 1, 2, 0), True),  # 330 / 335 / 237
+    ((58, 33, 9, 5, 94, 1, 1, 2, 0), True),
+]
+
+
+@pytest.mark.parametrize("shape,pieces", ONE_BY_ONE_LINES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_lines_between_the_kernels_of_1x1_layers(shape, pieces):
+    for w in (False, True):
+        name = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"]
+        assert name.startswith("conv_split_1x1_kernel<") == pieces, name
