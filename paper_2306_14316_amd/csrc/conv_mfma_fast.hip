@@ -807,13 +807,13 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     if (e != hipSuccess) return e;
     const uint32_t left = ncu >= 8 && ncu % 8 == 0 ? blocks % (uint32_t)ncu : 0u, eighth = (uint32_t)ncu / 8, halfcu = (uint32_t)ncu / 2;
     if constexpr (HF == WF && HF >= 3 && HF <= 5 && CW == 4 && (HF < 5 || JX > 1)) {   // (K blocks of eight channels; two stages of 7x7 filters and strips pass 160 KB)
-        // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths, as far as those have (or two of them one,
-        // where they are a group or two of channels long: 32 -> 130 14x11 stride 2 N=12, 21 tiles, 4.4 against 5.5 in two calls).  Convolution alone, us, two
-        // calls / workspace-free, halves or sixteenths / quarters: 64 -> 64 channels 56x56 (196 quarters) 8.0 / 8.5 / 6.1 / 6.6; 344 -> 29 13x12 N=27
+        // Few tiles: in quarters, as far as each has a compute unit of its own, or in sixteenths (few_tiles_in_sixteenths).  5x5 layers of twelve
+        // channels stay in halves, three blocks of four channels against two of eight: 12 -> 7 65x65 stride 2 N=2 6.0 against 6.9 us; with
+        // twenty channels there is no difference.  Convolution alone, us, two calls / workspace-free, halves or sixteenths / quarters: 64 -> 64 channels 56x56 (196 quarters) 8.0 / 8.5 / 6.1 / 6.6; 344 -> 29 13x12 N=27
         // 29.3 / 32.7 / 18.2 / 21.4; 128 -> 128 28x28 (26 tiles) 9.7 / 12.0 / 8.9 / 9.9; 128 -> 256 14x14 (16 tiles) 6.5 / 8.2 / 8.9 / 10.1; 64 -> 64 28x28
         // N=16 (392 quarters) 11.8 / 12.5 / 13.6 / 14.7; 5x5 77 -> 120 20x20 N=3 32.7 / 35.9 / 13.2 / 15.6; 4x4 stride 2 64 -> 64 64x64 17.5 / 19.9 / 10.3 / 11.7.
         const uint32_t quarters = ((P.npix + 31) / 32) * (uint32_t)((P.Co + 31) / 32);
-        if (P.Ci >= 8 && quarters <= (uint32_t)ncu && !(PIECEABLE && P.Ci % 16 == 0 && (P.Ci <= 32 ? 8 : 16) * blocks <= (uint32_t)ncu))
+        if (P.Ci >= 8 && quarters <= (uint32_t)ncu && !(PIECEABLE && few_tiles_in_sixteenths(P, blocks, ncu)) && !(HF == 5 && P.Ci == 12))
             return P.Ci % 8 != 0 ? launch_quarter_t<HF, WF, 8, JX, IMP, true>(P, dev, st, plan) : launch_quarter_t<HF, WF, 8, JX, IMP, false>(P, dev, st, plan);
     }
     if (P.Ci % CB != 0) {

@@ -102,6 +102,22 @@ __device__ __forceinline__ void store_tile_desc(const MfmaParams &P, const float
     }
 }
 
+// 3x3 layers of few tiles on the fp32 pipeline: whether they run as sixteenths of a tile (16x16 pieces over all of K, operands straight from
+// memory; those without an output channel end at once) or as quarters (32x32, operands through LDS).  Up to an eighth of the compute
+// units' number of tiles, in steps of 16 channels.  With a unit for every piece, or 32 channels at most, sixteenths are the faster ones.  Above
+// that quarters are where half of the units' number of pieces have outputs, a thread stages one strip word and the filter rows, multiples of
+// 1152 bytes apart, meet in the caches: 500 layers of 17 to 32 tiles, sixteenths / quarters, two calls and workspace-free: 1.02 to 1.16 and
+// 0.96 to 1.38 on those; channels an odd multiple of 16 0.86 to 0.96 and 0.79 to 1.34; two strip words 0.77 to 0.96 and 0.75 to 1.37; fewer pieces
+// down to 0.4 (us, two calls / workspace-free: 608 -> 1 channels 36x36 stride 2 N=6 16.5 / 32 and 41 / 50; 304 -> 51 21x8 N=9 14.5 / 18.8 and
+// 21.3 / 26.5; 256 -> 120 9x11 N=10 16.5 / 23.5 and 14.7 / 17.0).
+inline bool few_tiles_in_sixteenths(const MfmaParams &P, uint32_t blocks, int ncu)
+{
+    if (P.Ci % 16 != 0 || ncu < 8 || ncu % 8 != 0 || blocks > (uint32_t)ncu / 8) return false;
+    if (P.Ci <= 32 || 16 * blocks <= (uint32_t)ncu) return true;
+    const uint32_t live = ((P.npix + 15) / 16) * (uint32_t)((P.Co + 15) / 16);
+    return P.Ci % 32 != 0 || P.S > 256 || live <= (uint32_t)ncu / 2;
+}
+
 hipError_t launch_conv_mfma_fast(MfmaParams P, const Shape &sh, uint32_t blocks, hipStream_t st,
                                  bool implicit = false, int filter_fetch_floats = 4, LaunchPlan *plan = nullptr);
 // conv_split.hip: the layers that are faster on the bf16 matrix cores (blocks: tiles of the fp32 pipeline).

@@ -114,6 +114,8 @@ static double fp32_estimate(const MfmaParams &P, const Shape &sh, uint32_t block
     const int nkb = (sh.Ci + CB - 1) / CB;
     const bool whole = sh.Ci % CB == 0, pieces = HF == 3 && WF == 3 && sh.Ci % 16 == 0;
     const double k = (double)(nkb * CB * HF * WF);
+    if (HF == 3 && WF == 3 && few_tiles_in_sixteenths(P, blocks, ncu))   // (13 % off, in two calls)
+        return 3.1 + sh.Ci * (0.027 + (16 * blocks > (uint32_t)ncu ? 0.031 * (double)((P.npix + 15) / 16) * ((P.Co + 15) / 16) / ncu : 0.0));
     if (HF == WF && HF <= 5 && sh.Ci >= 8 && (uint32_t)((sh.npix + 31) / 32) * (uint32_t)((sh.Co + 31) / 32) <= (uint32_t)ncu)
         return 3.4 + (double)((sh.Ci + 7) / 8 * 8 * HF * WF) * 0.0048;   // quarter tiles
     double rounds = 0.9 * up + 0.1 * std::max(r, up > 1.5 ? 0.0 : 0.84);

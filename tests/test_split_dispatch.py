@@ -154,6 +154,30 @@ def test_layers_that_stay_on_the_fp32_pipeline_are_planned_as_fast_as_any():
     assert info.kernel.startswith(b"conv_mfma_fast_kernel<") and some < 1.3 * few, (few, some)   # (1.05 times; 1.6 to 2.1 with the searches)
 
 
+# (layer, form): layers of few tiles on both sides of the lines between quarters and sixteenths or halves of a tile.  In us, the sixteenths or
+# halves in two calls / workspace-free, quarters likewise:
+FEW_TILE_LINES = [
+    ((6, 608, 36, 36, 1, 3, 3, 2, 0), "sixteenths"),   # 16.5 / 32, 41 / 50: of 512 pieces 109 have outputs
+    ((9, 304, 21, 8, 51, 3, 3, 1, 0), "sixteenths"),   # 14.5 / 18.8, 21 / 27
+    ((9, 272, 13, 13, 52, 3, 3, 1, 0), "sixteenths"),  # channels an odd multiple of 16
+    ((5, 192, 15, 15, 262, 3, 3, 2, 0), "sixteenths"),  # 13.2 / 23.2, 14.9 / 18.3: two strip words per thread
+    ((1, 128, 16, 16, 256, 3, 3, 1, 0), "sixteenths"),  # a unit for every piece
+    ((10, 256, 9, 11, 120, 3, 3, 1, 0), "quarters"),   # 16.5 / 23.5, 14.7 / 17.0
+    ((3, 576, 21, 21, 39, 3, 3, 1, 0), "quarters"),    # 33 / 45, 29 / 34
+    ((1, 64, 56, 56, 64, 3, 3, 1, 1), "quarters"),
+    ((2, 12, 65, 65, 7, 5, 5, 2, 0), "halves"),        # 6.0 / 6.5, 6.9 / 7.0
+    ((2, 20, 65, 65, 7, 5, 5, 2, 0), "quarters"),
+]
+
+
+@pytest.mark.parametrize("shape,form", FEW_TILE_LINES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_lines_between_the_forms_of_few_tiles(shape, form):
+    for w in (False, True):
+        name, _, args = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"].partition("<")
+        tail, half = args.split(", ")[8:10] if name == "conv_mfma_fast_kernel" else (None, None)
+        assert {"conv_mfma_quarter_kernel": "quarters"}.get(name, "sixteenths" if tail == "true" else "halves" if half == "true" else name) == form, name
+
+
 def test_a_kernel_name_is_one_kernel():
     """A profiler's kernel name is the name the plan gives, so it has to tell the two bodies apart: the ragged fp32
     instance and the bf16-piece kernel once had the same one."""
