@@ -799,8 +799,13 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     constexpr bool PIECEABLE = HF == 3 && WF == 3 && CB == 8;
     constexpr bool HALFABLE = PIECEABLE || (HF == 5 && WF == 5 && CB == 4);   // (the 5x5 instance: halves only)
     // Instances with halves: two workgroups per compute unit, as the half tile's loop has half of the MFMAs to carry the same staging and
-    // holds more of it at once (three, at 168 registers each, spilled 27 to 147 of them).
-    constexpr int OCCH = HALFABLE && OCC > 2 ? 2 : OCC;
+    // holds more of it at once (three, at 168 registers each, spill 27 to 147 of them).  With one strip word per thread (27) the third workgroup is
+    // worth more than the registers beside sixteenths, and without them where a unit has more than two tiles of one, two or four K blocks:
+    // of 239 such layers three workgroups per unit were the faster ones in both calls in all but 23, which lost at most 2.5 %.  In us, three / two, two
+    // calls: 8 -> 127 56x56 N=32 29 / 33, 64 -> 8 73x13 N=12 9.6 / 11.2, 32 -> 291 7x81 N=5 7.6 / 8.7; three K blocks 1.04 to 1.40 times as long, five and
+    // more 0.99 to 1.14.  A ragged channel count runs whole tiles there up to three K blocks (in halves 2 to 9 % slower; from four on 0 to 4 % faster).
+    constexpr bool WORD = HALFABLE && OCC > 2 && JX == 1;
+    constexpr int OCCH = HALFABLE && OCC > 2 ? 2 : OCC, OCCHT = WORD ? OCC : OCCH;
     int dev = 0, ncu = 0;
     hipError_t e = device_cus(&dev, &ncu);
     if (e != hipSuccess && plan) { e = hipSuccess; ncu = 256; }   // planning without a device: an MI355X's 256 compute units
@@ -821,7 +826,7 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
         // instances exist)
         if constexpr (CW == ((HF == 7 && WF == 7) ? 2 : 4)) {
             MfmaParams Q = P;
-            Q.nblocks = blocks; Q.nhalf = HALFABLE && left <= halfcu ? left : 0u; Q.nmain = blocks - Q.nhalf;
+            Q.nblocks = blocks; Q.nhalf = HALFABLE && left <= halfcu && !(WORD && P.Ci < 3 * CB && blocks > 2 * (uint32_t)ncu) ? left : 0u; Q.nmain = blocks - Q.nhalf;
             const uint32_t grid = Q.nmain + 2 * Q.nhalf;
             Q.tail_at = grid;
             const int which = Q.nhalf ? 1 : 0;
@@ -878,18 +883,21 @@ static hipError_t launch_fast_t(const MfmaParams &P, uint32_t blocks, hipStream_
     Q.nhalf = nhalf;
     Q.tail_at = Q.nmain + 2 * nhalf;
     void (*kern)(MfmaParams) = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, false>;
-    int which = 0;   // which of this launcher's five kernel instances
+    const int nkb = Q.Ci / CB;
+    const bool third = WORD && nhalf && (npiece || (blocks > 2 * (uint32_t)ncu && (nkb == 1 || nkb == 2 || nkb == 4)));
+    int which = 0;   // which of this launcher's six kernel instances
     if (grid < blocks) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, true, false>; which = 1; }
     if (npiece && !nhalf) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, PIECEABLE>; which = 2; }
     if (nhalf && !npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCH, IMP, false, false, HALFABLE>; which = 3; }
-    if (nhalf && npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCH, IMP, false, PIECEABLE, HALFABLE>; which = 4; }
+    if (nhalf && npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCCHT, IMP, false, PIECEABLE, HALFABLE>; which = 4; }
+    if constexpr (WORD) if (third && !npiece) { kern = &conv_mfma_fast_kernel<HF, WF, CB, JX, CW, OCC, IMP, false, false, HALFABLE>; which = 5; }
     if (plan) {
-        const bool per = which == 1, tail = (which == 2 || which == 4) && PIECEABLE, half = (which == 3 || which == 4) && HALFABLE;
+        const bool per = which == 1, tail = (which == 2 || which == 4) && PIECEABLE, half = which >= 3 && HALFABLE;
         plan_record(plan, dim3(grid), 256, lds, "conv_mfma_fast_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, false>",
-                    HF, WF, CB, JX, CW, half ? OCCH : OCC, tf(IMP), tf(per), tf(tail), tf(half));
+                    HF, WF, CB, JX, CW, half && !third ? OCCH : OCC, tf(IMP), tf(per), tf(tail), tf(half));
         return hipSuccess;
     }
-    static KernelCache kc[5];
+    static KernelCache kc[6];
     if ((e = allow_dynamic_lds(kc[which], reinterpret_cast<const void *>(kern), lds, dev)) != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, Q);
     return hipGetLastError();

@@ -378,6 +378,8 @@ PIPELINE_SHAPES = [
     ((9, 16, 135, 119, 256, 3, 3, 2, 4), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 3, false, true, false, false, false>"),
     ((18, 16, 113, 5, 65, 3, 3, 2, 2), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, true, true, false>"),       # four pixels a row
     ((9, 320, 38, 38, 134, 3, 3, 2, 1), "conv_mfma_fast_kernel<3, 3, 8, 2, 4, 2, false, false, true, true, false>"),
+    ((2, 8, 75, 75, 170, 3, 3, 1, 1), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, true, false>"),       # 528 tiles: 16 left, one K block
+    ((19, 32, 30, 31, 100, 3, 3, 1, 1), "conv_mfma_fast_kernel<3, 3, 8, 1, 4, 3, false, false, false, true, false>"),     # 554 tiles: 42 left, four K blocks
     ((7, 4, 17, 33, 65, 5, 5, 1, 4), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, false>"),       # one K block
     ((2, 27, 39, 39, 273, 5, 5, 1, 0), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, true>"),
     ((4, 61, 33, 35, 245, 5, 5, 1, 0), "conv_mfma_fast_kernel<5, 5, 4, 2, 4, 2, false, false, false, false, true>"),

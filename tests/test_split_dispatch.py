@@ -178,6 +178,29 @@ def test_lines_between_the_forms_of_few_tiles(shape, form):
         assert {"conv_mfma_quarter_kernel": "quarters"}.get(name, "sixteenths" if tail == "true" else "halves" if half == "true" else name) == form, name
 
 
+# (layer, what follows the filter in the kernel's name): halves with two and with three workgroups per compute unit, ragged channel counts
+# in halves and in whole tiles
+HALF_TILE_LINES = [
+    ((7, 8, 41, 43, 190, 3, 3, 1, 1), "8, 1, 4, 3, {}, false, false, true, false"),     # 579 tiles, 67 left; one K block
+    ((4, 8, 41, 43, 190, 3, 3, 1, 1), "8, 1, 4, 2, {}, false, false, true, false"),     # two tiles to a unit at most
+    ((7, 24, 41, 43, 190, 3, 3, 1, 1), "8, 1, 4, 2, {}, false, false, true, false"),    # three K blocks
+    ((19, 32, 30, 31, 100, 3, 3, 1, 1), "8, 1, 4, 3, {}, false, false, true, false"),   # four
+    ((8, 40, 41, 43, 180, 3, 3, 1, 0), "8, 1, 4, 2, {}, false, false, true, false"),    # five
+    ((9, 32, 50, 50, 128, 3, 3, 1, 0), "8, 1, 4, 3, {}, false, true, true, false"),     # with sixteenths
+    ((9, 320, 38, 38, 134, 3, 3, 2, 1), "8, 2, 4, 2, {}, false, true, true, false"),    # two strip words per thread
+    ((7, 20, 43, 42, 190, 3, 3, 1, 1), "8, 1, 4, 3, {}, false, false, false, true"),    # ragged, 594 tiles, 82 left
+    ((7, 27, 43, 42, 190, 3, 3, 1, 1), "8, 1, 4, 2, {}, false, false, true, true"),
+    ((4, 20, 43, 42, 190, 3, 3, 1, 1), "8, 1, 4, 2, {}, false, false, true, true"),
+]
+
+
+@pytest.mark.parametrize("shape,args", HALF_TILE_LINES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_lines_between_the_forms_of_half_tiles(shape, args):
+    for w in (False, True):
+        name = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"]
+        assert name == "conv_mfma_fast_kernel<3, 3, %s>" % args.format(*_tf(w)), name
+
+
 def test_a_kernel_name_is_one_kernel():
     """A profiler's kernel name is the name the plan gives, so it has to tell the two bodies apart: the ragged fp32
     instance and the bf16-piece kernel once had the same one."""
