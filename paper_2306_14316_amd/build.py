@@ -1,4 +1,4 @@
-"""Build the gfx950 library in-tree: hipcc -> paper_2306_14316_amd/libim2win.so, and gcc -> paper_2306_14316_amd/_native.so."""
+"""Build the gfx950 library in-tree: hipcc -> paper_2306_14316_amd/libim2win.so, and, for the interpreter that runs this, gcc -> the module _native."""
 from __future__ import annotations
 
 import os
@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libim2win.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ("api.hip", "transform.hip", "conv_basic.hip", "conv_mfma.hip", "conv_mfma_fast.hip", "conv_split.hip",
            "conv_split_stem.hip", "conv_split_1x1.hip", "conv_mfma_shallow.hip", "conv_mfma_1x1.hip", "baselines.hip", "probes.hip")
@@ -39,23 +39,28 @@ def _compile(src: str) -> str:
 
 
 def _build_native() -> None:
-    """The binding's short path (host code, a CPython module)."""
+    """The binding's short path (host code, a CPython module).  Without gcc or Python's headers there is none, and the binding does without."""
     tmp = NATIVE + ".tmp.%d" % os.getpid()
-    subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
-                    os.path.join(CSRC, "native_call.c"), "-o", tmp], check=True)
-    os.replace(tmp, NATIVE)
+    try:
+        subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+                        os.path.join(CSRC, "native_call.c"), "-o", tmp], check=True)
+        os.replace(tmp, NATIVE)
+    except (OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(NATIVE):   # (of an earlier build, perhaps of other sources)
+            os.remove(NATIVE)
+        sys.stderr.write("warning: the module _native was not built (%s); calls take the general path, some 2 us slower\n" % e)
 
 
 def build(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link the shared library (always rebuilds); the binding's module with it."""
     os.makedirs(OBJDIR, exist_ok=True)
-    _build_native()
     with ThreadPoolExecutor(max_workers=4) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
+    _build_native()
     if verbose:
         print("built", LIB)
     return LIB

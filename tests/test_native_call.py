@@ -1,11 +1,13 @@
 """The binding's calls in C: what they take is what the general path takes, with the same results; everything else is left to that path."""
+import os
+import subprocess
 from types import SimpleNamespace
 
 import pytest
 import torch
 
 import paper_2306_14316_amd as im2win
-from paper_2306_14316_amd import binding
+from paper_2306_14316_amd import binding, build
 
 LAYER = (2, 3, 9, 8, 5, 3, 3, 1, 1)
 
@@ -29,6 +31,22 @@ def test_what_is_not_plain_is_left_to_the_general_path():
     with pytest.raises(TypeError):
         im2win.conv2d_im2win_implicit_fwd(x, f, o, *LAYER)
     assert conv(1, x, f, o, *LAYER[:7], 0, 1, None) is None         # stride 0
+
+
+@pytest.mark.parametrize("error", [FileNotFoundError("gcc"), subprocess.CalledProcessError(1, "gcc")], ids=["no compiler", "no headers"])
+def test_a_build_without_the_module_has_the_library(monkeypatch, tmp_path, capsys, error):
+    def run(cmd, check):
+        if cmd[0] == "gcc":
+            raise error
+        open(cmd[cmd.index("-o") + 1], "w").close()   # (the link)
+
+    for name in ("LIB", "NATIVE", "OBJDIR"):
+        monkeypatch.setattr(build, name, str(tmp_path / name))
+    open(build.NATIVE, "w").close()
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build() == build.LIB and os.path.exists(build.LIB)
+    assert not os.path.exists(build.NATIVE) and "warning" in capsys.readouterr().err   # a stale module is not left behind
 
 
 @pytest.mark.gpu
