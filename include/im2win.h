@@ -129,9 +129,11 @@ im2win_status conv2d_im2win_fwd_basic(const float *window_dev, const float *filt
  *                                    their runs being 4-byte aligned only).  There are such
  *                                    instances for 3x3 filters, Ci a multiple of 8; other
  *                                    layers run the default kernel.  Compare with DEFAULT on
- *                                    a layer where that is the same kernel (a small batch;
- *                                    conv2d_im2win_fwd_launch_info names it), not the bf16
- *                                    pieces;
+ *                                    a layer where that is the same kernel,
+ *                                    conv_mfma_fast_kernel (conv2d_im2win_fwd_launch_info
+ *                                    names it; 64 -> 64 channels at 56x56, batch 8), not
+ *                                    quarters of a tile (smaller batches) or the bf16 pieces
+ *                                    (larger ones);
  *   IM2WIN_VARIANT_NO_MFMA           none of the above at once -- no LDS, no register
  *                                    tile, no matrix cores: one thread per output
  *                                    (Algorithm 2, conv2d_im2win_fwd_basic).
@@ -155,12 +157,14 @@ im2win_status conv2d_im2win_fwd_variant(const float *window_dev, const float *fi
  * input.  Each workgroup builds the im2win strips of its tile (Section 3.1, Eq. 2),
  * or the patch they come from, in LDS instead of reading an im2win tensor, so no
  * workspace and no transform call are needed; the MFMA loop and the result are those
- * of conv2d_im2win_fwd.  Any layer is accepted.  Layers with a kernel of their own (3x3
- * filters with Ci a multiple of 8, 5x5 with Ci a multiple of 4, 7x7 with Ci even,
- * filter_dev 16-byte aligned; 1x1 without padding, Ci a multiple of 8; three-channel 3x3,
- * 7x7 and 11x11 stems; the bf16-piece filters) run at about the speed of
- * conv2d_im2win_fwd alone; the others take the generic, unpipelined kernel and may be
- * slower than the two-call path.
+ * of conv2d_im2win_fwd.  Any layer is accepted.  Layers with a kernel of their own run at
+ * about the speed of conv2d_im2win_fwd alone: three-channel 3x3, 7x7 and 11x11 stems;
+ * 1x1 without padding and more than four channels; and, at strides of a few words,
+ * 3x3, 1x7 and 7x1 filters from 8 channels on, 5x5 and 4x4 from 4, 7x7 from 2, 1x3, 3x1
+ * and 2x2 from 16 (filter_dev 16-byte aligned where the fp32 kernels run; 3x3 layers of
+ * few tiles with fewer channels too).  The others take the generic, unpipelined kernel
+ * and may be slower than the two-call path (conv2d_im2win_fwd_launch_info names the
+ * kernel: conv_mfma_kernel).
  *   input_dev   device, N*Ci*Hi*Wi floats, read only
  *   filter_dev  device, Co*Ci*Hf*Wf floats, [Co][Ci][Hf][Wf]
  *   output_dev  device, N*Co*Ho*Wo floats, fully overwritten
