@@ -143,7 +143,9 @@ static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t bl
     // worst).  A body takes its start and end, and per round of tiles the tile's steps and its own start and stores.  Measured, fp32
     // pipeline / wide / narrow / low: 3x3 64 channels 56x56 N=32 62 / 48 / 58 / 57; 3x3 256 channels 14x14 N=128 213 / 140 / 183 / 181;
     // 3x3 512 channels 7x7 N=128 151 / 160 / 101 / 95; 3x3 100 -> 130 29x27 N=61 130 / 99 / 101 / 88; 5x5 96 -> 100 24x24 N=50
-    // - / 68 / 94 / 81; 7x7 stride 2 64 -> 20 134x134 N=16 - / 104 / 129 / 74.
+    // - / 68 / 94 / 81; 7x7 stride 2 64 -> 20 134x134 N=16 - / 104 / 129 / 74.  Strided 1x7 layers read rows that their windows skip and take a
+    // tenth longer, without a workspace above all (16 -> 64 123x123 stride 2 N=106, fp32 / narrow, two calls and workspace-free: 64 / 71 and 68 / 82; 120
+    // layers on whose kernel that decides: fp32 1.01 and 1.16 times as fast as the pieces).
     // `mix`: how far a last round that leaves units idle counts in full (it runs at a higher clock).
     auto rounds = [&](uint32_t tiles, double mix) {
         const double r = (double)tiles / ncu, up = (double)((tiles + ncu - 1) / ncu);
@@ -161,10 +163,11 @@ static hipError_t launch_split(const MfmaParams &P, const Shape &sh, uint32_t bl
         using T = SplitTile<KC::SHAPE>;
         constexpr int TM = T::WGM * T::FM * 32, TN = T::WGN * T::FN * 32;
         const double steps = (double)((sh.Ci + 8 * KC::CG - 1) / (8 * KC::CG)) * ((KC::CG * HF * WF + 1) / 2);
+        const bool strided = HF == 1 && WF == 7 && sh.s > 1;
         constexpr bool SHORT = HF * WF == 3 || (HF == 4 && WF == 4);   // short K blocks, more patch to a step
         auto time = [&](uint32_t tiles) {
             return KC::SHAPE == kWide     ? 5.3 + rounds(tiles, 0.65) * (SHORT ? 1.15 : 1.0) * (steps * 0.475 + 4.25)
-                   : KC::SHAPE == kNarrow ? 4.55 + rounds(tiles, 0.75) * (SHORT ? 1.16 : 1.0) * (steps * 0.3035 + 2.3)
+                   : KC::SHAPE == kNarrow ? 4.55 + rounds(tiles, 0.75) * (SHORT ? 1.16 : strided ? 1.12 : 1.0) * (steps * 0.3035 + 2.3)
                                           : 5.05 + rounds(tiles, 0.65) * (SHORT ? 1.3 : HF * WF >= 25 ? 0.94 : 1.0) * (steps * 0.31 + 2.2);
         };
         // (Strips only add tiles: what is too slow without them needs no search of their widths.  On the host, a search for every

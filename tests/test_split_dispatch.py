@@ -201,6 +201,18 @@ def test_lines_between_the_forms_of_half_tiles(shape, args):
         assert name == "conv_mfma_fast_kernel<3, 3, %s>" % args.format(*_tf(w)), name
 
 
+@pytest.mark.parametrize("shape,pieces", [
+    ((106, 16, 123, 123, 64, 1, 7, 2, 4), False),   # fp32 pipeline / pieces, two calls and workspace-free: 64 / 71, 68 / 82
+    ((86, 32, 28, 28, 65, 1, 7, 2, 1), False),      # 11.3 / 10.8, 11.3 / 12.2
+    ((51, 48, 69, 69, 64, 1, 7, 2, 0), True),       # 1.41 and 1.21 times as fast in pieces
+    ((137, 32, 6, 84, 300, 1, 7, 2, 4), True),      # 1.17, 1.03
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_lines_between_the_kernels_of_strided_row_filters(shape, pieces):
+    for w in (False, True):
+        name = im2win.conv2d_im2win_fwd_launch_info(*shape, workspace_free=w)["kernel"]
+        assert name.startswith("conv_split_kernel<1, 7,") == pieces, name
+
+
 def test_a_kernel_name_is_one_kernel():
     """A profiler's kernel name is the name the plan gives, so it has to tell the two bodies apart: the ragged fp32
     instance and the bf16-piece kernel once had the same one."""
