@@ -312,7 +312,8 @@ hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out,
     // the fp32 1x1 kernel does not take (Ci no multiple of 8, Co none of 4) ran the generic kernels, which take up to eight times as long:
     // in us, generic two calls / workspace-free / pieces: 43 -> 100 channels 28x28 N=29 28 / 27 / 8.6, 285 -> 94 8x5 N=58 20 / 126 / 16, 870 -> 102
     // 16x16 stride 2 N=8 59 / 391 / 40, 226 -> 19 44x44 N=6 16 / 93 / 15.  Up to sixteen channels they may be the faster ones (a block of the pieces is
-    // 32 channels long) and have an estimate too, fitted to 804 layers (8 % off in two calls; 985 more, of 17 to 200 channels, are all faster in pieces):
+    // 32 channels long) and have an estimate too, fitted to 1166 layers (8 % off the geometric mean of both calls; the pick takes 1.003 times
+    // the best one's time on average; 985 layers of 17 to 200 channels are all faster in pieces):
     // 8 -> 6 63x63 N=37 9.4 / 9.6 / 17.7, 7 -> 19 184x184 N=156 365 / 374 / 491, 16 -> 9 77x76 N=102 41 / 41 / 58, 10 -> 10 on 84 images of one pixel 15 / 21 / 5.6; up to four
     // they stay there.  The price of one rule for both calls is 229 rows of 1624 -> 90 channels, in two calls 88 us generic, 102 here.  Measured, fp32 / 128 / 256 pixels, the
     // one that runs in brackets: 256 -> 256 28x28 N=64 62 / 51 / [44], 14x14 N=32 [12.7] / 14.4 / 21, N=128 34 / 27 / [25]; 512 -> 512 14x14 N=32
@@ -329,11 +330,11 @@ hipError_t launch_conv_split_1x1(const float *src, const float *flt, float *out,
         const double r = tiles(64, 64), up = (double)(long long)(r + 0.9999);
         if (std::min(t1, t2) > 0.9 * (3.56 + (0.25 * up + 0.75 * std::max(r, up > 1.5 ? 0.0 : 1.0)) * (sh.Ci * 0.0213 + 0.28))) return hipErrorNotSupported;
     } else if (sh.Ci <= 16) {
-        // tiles of 64 x 64 in K blocks of eight channels (vector loads where the blocks are whole), `rows` of the output to a tile; half a us
-        // is added, as the pieces take that much less than t1 in a single round
+        // tiles of 64 x 64 in K blocks of eight channels (vector loads where the blocks are whole), `rows` of the output to a tile; 0.3 us
+        // is added, as the pieces take some less than t1 in a single round
         const double r = std::max(tiles(64, 64) - 1.0, 0.0), kb = (sh.Ci + 7) / 8, rows = std::min(std::min(64, (62 + sh.Wo) / sh.Wo + 1), (int)((P.npix + sh.Wo - 1) / sh.Wo));
-        const double generic = 4.55 + kb * ((ragged ? 2.2 : 0.48) + 0.07 * rows) +
-                               r * (0.25 + kb * ((ragged ? 0.56 : 0.3) + 0.01 * rows + 0.06 * (sh.s - 1)) + 0.54 * std::min(sh.Co, 64) / 64.0);
+        const double generic = 4.68 + kb * ((ragged ? 2.0 : 0.3) + 0.1 * rows) +
+                               r * (0.26 + kb * ((ragged ? 0.54 : 0.29) + 0.015 * rows + 0.05 * (sh.s - 1)) + 0.54 * std::min(sh.Co, 64) / 64.0);
         if (sh.Ci <= 4 || std::min(t1, t2) > generic) return hipErrorNotSupported;
     }
     if (t2 < t1) {

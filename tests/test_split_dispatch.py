@@ -350,6 +350,7 @@ ONE_BY_ONE_LINES = [
     ((233, 13, 1, 1, 28, 1, 1, 2, 0), True),      # 16 / 23 / 6.7
     ((84, 10, 1, 1, 10, 1, 1, 2, 0), True),       # 15 / 21 / 5.6
     ((3, 5, 16, 15, 20, 1, 1, 1, 0), True),
+    ((152, 7, 197, 3, 10, 1, 1, 1, 0), True),     # 16 / 18 / 12: three pixels a row
     ((231, 8, 114, 114, 286, 1, 1, 2, 0), True),  # 330 / 335 / 237
     ((58, 33, 9, 5, 94, 1, 1, 2, 0), True),
 ]
