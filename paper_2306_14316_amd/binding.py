@@ -60,6 +60,12 @@ def load_library():
             raise FileNotFoundError(
                 "%s not found: build it with `python -m paper_2306_14316_amd.build` "
                 "(or __graft_entry__.build())" % _LIB_PATH)
+        # torch brings a HIP runtime of its own, which the library then shares.  Loaded before torch, the library would bring the system's, and a
+        # launch on torch's streams and tensors would fail.
+        try:
+            _torch or _load_torch()
+        except ImportError:
+            pass   # (the size and planning calls need no torch)
         lib = ctypes.CDLL(_LIB_PATH)
         i, vp, sp = ctypes.c_int, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)
         ip = ctypes.POINTER(ctypes.c_int)

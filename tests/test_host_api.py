@@ -4,6 +4,8 @@ argument into an error code without launching anything."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -255,3 +257,14 @@ def test_bench_traffic_constants_are_the_profiled_ones():
     assert got["conv"] == bench.MEASURED_CONV_TRAFFIC_BYTES
     assert got["transform"] == bench.MEASURED_TRANSFORM_TRAFFIC_BYTES
     assert set(got["conv"]) == {L.name for L in workloads.LAYERS}
+
+
+def test_the_library_is_loaded_after_torch():
+    """A size query before the program's own `import torch`: one HIP runtime in the process, torch's."""
+    code = ("import sys, paper_2306_14316_amd as im2win\n"
+            "assert 'torch' not in sys.modules and im2win.im2win_out_shape(5, 5, 3, 3, 1, 0) == (3, 3)\n"
+            "import torch\n"
+            "print(len({l.split()[-1] for l in open('/proc/self/maps') if 'libamdhip64' in l}))")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=root)
+    assert r.returncode == 0 and r.stdout.split() == ["1"], (r.stdout, r.stderr)
