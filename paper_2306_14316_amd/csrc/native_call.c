@@ -1,6 +1,6 @@
 /* The host side of the binding's three calls (transform, convolution over the im2win tensor, workspace-free convolution) as one C call each:
  * the checks on tensors and sizes, the current stream and the library call.  A layer of a few microseconds is bound by its host side: a call
- * through ctypes and the checks in Python take 5.4 us, of which the launch is 2; see binding.py for what a call takes here.
+ * through ctypes and the checks in Python take 5.4 us, of which the library, from its checks to the enqueued launch, 3.6; see binding.py for what a call takes here.
  *
  * Only what needs no judgement is decided here: exact ints, exact torch tensors (or Parameters), fp32, on the GPU, contiguous, of the expected number of
  * elements.  For anything else, and for any error on the way, the call returns None with nothing launched, and the binding's general path
